@@ -18,7 +18,7 @@ constexpr int MAX_FRAMES = 8;
 enum EpiKind {
   EPI_F32 = 0,   // out_f32[m, n] = v + bias[n] + rowadd[m % period, n]
   EPI_T,         // out_T[m, n] = T(v + bias[n])
-  EPI_RESID,     // resid[m, n] += v + bias[n]                 (fp32 residual stream)
+  EPI_RESID,     // resid[m, n] += colscale[n] * (v + bias[n]) (fp32 residual stream; skinny kernels)
   EPI_GELU,      // out_T[m, n] = T(gelu_tanh(v + bias[n]))
   EPI_SWISH,     // out_T[m, n] = T(swish(v + bias[n]))
   EPI_GEGLU,     // gate/up interleaved in 16-row blocks: out_T[m, 16g+j] = T(gelu(gate) * up)
@@ -129,25 +129,35 @@ struct Epi {
   // and RoPE positions pos0 + m % blk_rows. Row-major outputs use row m.
   int blk_rows = 0;
   size_t blk_out = 0, blk_xop = 0, blk_k = 0, blk_v = 0;
-  // RMSNorm folded across a split-K skinny GEMM and the next skinny GEMM
-  // (one frame, M <= 64, N <= 64 x 32):
-  // * producer (EPI_PART with norm_g set): the last split to arrive for a
-  //   32-column pair sums the pair's partials in split order into the fp32
-  //   residual x (ldx), writes norm_out = T(x * norm_g) (per column; in the
-  //   row-block operand layout when afrag) and the pair's per-row sum of
-  //   squares rowss[pair][m]. cnt: one counter per pair, zero before the
-  //   first launch and left at zero;
-  // * consumer (any other kind, rowss set): the product of each row m is
-  //   scaled by 1 / sqrt(sum over the rowss_n pairs of rowss[pair][m] /
-  //   rowss_d + 1e-6) before the epilogue; the pairs are summed in a fixed
+  // Residual update (EPI_RESID, skinny kernels): resid[m, n] += colscale[n] *
+  // (v + bias[n]) (colscale NULL: 1). With norm_g set (one frame, M <= 64, at
+  // most 64 column blocks, see slim_blocks) the RMSNorm before the next
+  // skinny GEMM is folded across the two launches:
+  // * this launch also writes norm_out = T(new x * norm_g) in the row-block
+  //   operand layout and each column block's per-row sum of squares
+  //   rowss[block][m] of the new x;
+  // * the consumer (any other kind, rowss set) scales the product of each
+  //   row m by 1 / sqrt(sum over the rowss_n blocks of rowss[block][m] /
+  //   rowss_d + 1e-6) before the epilogue, the blocks summed in a fixed
   //   order. Since the scale is per row it commutes with the product, so
   //   the two launches compute the RMSNorm of x with gain norm_g followed
   //   by the GEMM, with T rounding before the scale instead of after.
+  const float* colscale = nullptr;
   const float* norm_g = nullptr;
   void* norm_out = nullptr;
   float* rowss = nullptr;
   int rowss_n = 0, rowss_d = 0;
-  unsigned* cnt = nullptr;
+};
+
+// LayerNorm applied to the A operand as a skinny GEMM loads it: A[m] =
+// T((x[m] - mean) / sqrt(var + 1e-6) * g + b), g = gain (or 1 + gain with
+// g_plus_one), x fp32 row-major with leading dimension ldx.
+struct LnOperand {
+  const float* x = nullptr;
+  int ldx = 0;
+  const float* g = nullptr;
+  int g_plus_one = 0;
+  const float* b = nullptr;
 };
 
 struct GemmDesc {
@@ -175,11 +185,20 @@ struct GemmDesc {
   // one-frame call; batched action loops pass a fixed reference (the largest
   // group), so the reduction does not depend on the group size.
   int plan_m = 0;
+  // Skinny kernels, where slim_ln_fits: A is the LayerNorm of ln.x (A and
+  // a_blk unused).
+  LnOperand ln;
   // The most plan_m-row blocks a launch of this plan stacks (a prefill
   // batch). The split count may then be planned for that launch as well
   // (fixed for every batch, so the reduction stays the same).
   int plan_batch = 1;
 };
+
+// Column blocks of an N-column EPI_RESID launch (the rowss blocks it writes).
+int slim_blocks(int N);
+// Whether a one-frame GEMM over fragment-ordered weights can take its
+// operand through GemmDesc::ln.
+bool slim_ln_fits(int dtype, int M, int N, int K, int kind);
 
 // Offset of element (n, k) of a weight stored in MFMA fragment order with KS
 // K-slabs (of frag_slab(dtype) elements) per 16-row n-block.

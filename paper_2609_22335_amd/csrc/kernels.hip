@@ -90,6 +90,20 @@ __device__ __forceinline__ float wave_sum_x16_x32(float x) {
   return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
+// Sum over the 16 lanes of a row (lanes 16 g .. 16 g + 15), by rotations inside
+// the row; every lane gets the same value.
+template <int CTRL>
+__device__ __forceinline__ float dpp_mov(float x) {
+  return __uint_as_float(__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), CTRL, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float row16_sum(float x) {
+  x += dpp_mov<0x128>(x);  // row_ror:8
+  x += dpp_mov<0x124>(x);
+  x += dpp_mov<0x122>(x);
+  x += dpp_mov<0x121>(x);
+  return x;
+}
+
 template <typename T>
 struct TT;
 template <>
@@ -1170,69 +1184,8 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(const float* __restrict__
 // 4 * SPW slabs; each wave takes SPW consecutive slabs and issues every load
 // of its range at once (one memory round trip), then the four waves' partial
 // sums are added in wave order through LDS. K-ranges beyond one workgroup
-// are split: EPI_PART leaves the split partials to the consumer, other
-// epilogues go through the split-K reduce kernel.
+// are split, with the split-K reduce kernel applying the epilogue.
 // ---------------------------------------------------------------------------
-
-// The last split of a 32-column pair of a folded-norm producer (one frame):
-// thread t takes row t / 4 and columns 8 (t % 4) .. + 7 of the pair; the
-// pair's split partials are summed in split order (all loads in flight at
-// once) and added to the residual x, as the norm kernel adds them; then the
-// operand x * g and the row's sum of squares over the pair's columns (eight
-// in order per thread, then the row's four threads in order) are written.
-template <typename T>
-__device__ __forceinline__ void fold_pair(const Epi& e, int np, int M, int N, int splits, int tid,
-                                          float (&sPart)[64][4]) {
-  constexpr int DT = sizeof(T) == 2 ? DT_BF16 : DT_F32;
-  constexpr int MAXS = 8;  // splits (checked on the host)
-  const int row = tid >> 2, c0 = np * 32 + (tid & 3) * 8;
-  const bool ok = row < M && c0 < N;
-  const Rsrc rp = rsrc(e.out, (size_t)splits * M * N * 4);
-  f32x4 pa[MAXS], pb[MAXS];
-#pragma unroll
-  for (int q = 0; q < MAXS; ++q) {
-    const uint32_t off = (uint32_t)((((size_t)q * M + row) * N + c0) * 4);
-    const bool okq = ok && q < splits;
-    pa[q] = bld16_sc1(rp, okq ? off : OOB);
-    pb[q] = bld16_sc1(rp, okq ? off + 16 : OOB);
-  }
-  const Rsrc rx = rsrc(e.x, span(M, e.ldx, N, 4));
-  const Rsrc rg = rsrc(e.norm_g, (size_t)N * 4);
-  const uint32_t xo = (uint32_t)(((size_t)row * e.ldx + c0) * 4);
-  f32x4 xa = bld4f(rx, ok ? xo : OOB), xb = bld4f(rx, ok ? xo + 16 : OOB);
-  const f32x4 ga = bld4f(rg, ok ? (uint32_t)(c0 * 4) : OOB), gb = bld4f(rg, ok ? (uint32_t)(c0 * 4 + 16) : OOB);
-  f32x4 sa = {0.f, 0.f, 0.f, 0.f}, sb = sa;
-#pragma unroll
-  for (int q = 0; q < MAXS; ++q)
-    if (q < splits) {
-      sa += pa[q];
-      sb += pb[q];
-    }
-  xa += sa;
-  xb += sb;
-  float ss = 0.f;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) ss += xa[k] * xa[k];
-#pragma unroll
-  for (int k = 0; k < 4; ++k) ss += xb[k] * xb[k];
-  if (ok) {
-    *(f32x4*)(e.x + (size_t)row * e.ldx + c0) = xa;
-    *(f32x4*)(e.x + (size_t)row * e.ldx + c0 + 4) = xb;
-    const f32x4 ya = xa * ga, yb = xb * gb;
-    if constexpr (sizeof(T) == 2) {
-      *(uint4*)((T*)e.norm_out + afrag_index(DT, row, c0)) =
-          make_uint4(f2bf2(ya[0], ya[1]), f2bf2(ya[2], ya[3]), f2bf2(yb[0], yb[1]), f2bf2(yb[2], yb[3]));
-    } else {
-      *(f32x4*)((T*)e.norm_out + afrag_index(DT, row, c0)) = ya;
-      *(f32x4*)((T*)e.norm_out + afrag_index(DT, row, c0 + 4)) = yb;
-    }
-  }
-  sPart[row][tid & 3] = ss;
-  __syncthreads();
-  if ((tid & 3) == 0 && row < M)
-    e.rowss[(size_t)np * M + row] = ((sPart[row][0] + sPart[row][1]) + sPart[row][2]) + sPart[row][3];
-  __syncthreads();  // sPart is free again
-}
 
 // Frames (a batched action phase): `frames` row blocks of M rows, block f of
 // A at A + f a_blk elements. Every (column pair, K-range) tile is computed
@@ -1264,15 +1217,14 @@ __global__ __launch_bounds__(256) void k_skinny(const T* __restrict__ A, size_t 
   const int G = gridDim.x;
   const int first = frames > 1 && G % 8 == 0 ? (int)(blockIdx.x % 8) * (G / 8) + (int)(blockIdx.x / 8)
                                              : (int)blockIdx.x;
-  // Folded RMSNorm (see Epi::rowss). Consumer: thread t holds the partial
-  // sums of squares of row t / 4 for the pairs congruent to t % 4 (mod 4),
+  // Folded RMSNorm (see Epi::rowss): thread t holds the partial
+  // sums of squares of row t / 4 for the blocks congruent to t % 4 (mod 4),
   // requested before the first tile's loads (waiting for those covers them)
   // and turned into the rows' scales at the first epilogue.
   __shared__ float sPart[64][4];
   __shared__ float sInv[64];
-  __shared__ int sLast;
-  constexpr int SSQ = 16;  // pairs per thread: at most 64 pairs
-  const bool rowscale = KIND != EPI_PART && e.rowss != nullptr;
+  constexpr int SSQ = 16;  // column blocks per thread: at most 64 blocks
+  const bool rowscale = e.rowss != nullptr;
   const int srow = tid >> 2, squ = tid & 3;
   float ssq[SSQ];
   if (rowscale) {
@@ -1344,7 +1296,7 @@ __global__ __launch_bounds__(256) void k_skinny(const T* __restrict__ A, size_t 
       if (!inv_ready) {
         float t = 0.f;
 #pragma unroll
-        for (int k = 0; k < SSQ; ++k) t += ssq[k];  // pairs in increasing order (absent ones read 0)
+        for (int k = 0; k < SSQ; ++k) t += ssq[k];  // blocks in increasing order (absent ones read 0)
         sPart[srow][squ] = t;
         __syncthreads();
         if (squ == 0)
@@ -1361,41 +1313,15 @@ __global__ __launch_bounds__(256) void k_skinny(const T* __restrict__ A, size_t 
         v1[r] *= sc;
       }
     }
-    if (KIND != EPI_PART && splits == 1) {
+    if (splits == 1) {
       epi_pairs<T, 4, KIND>(e, Mt, N, mg, nn, v0, v1);
     } else {
-      const bool fold = KIND == EPI_PART && e.norm_g != nullptr;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         if (mg[r] >= Mt) continue;
-        float* P = (KIND == EPI_PART ? (float*)e.out : part) + (size_t)s * Mt * N + (size_t)mg[r] * N;
-        if (fold) {
-          // write-through: the pair's last split, on any XCD, reads them
-          if (n < N) __hip_atomic_store((uint32_t*)P + n, __float_as_uint(v0[r]), __ATOMIC_RELAXED,
-                                        __HIP_MEMORY_SCOPE_AGENT);
-          if (n + 16 < N) __hip_atomic_store((uint32_t*)P + n + 16, __float_as_uint(v1[r]), __ATOMIC_RELAXED,
-                                             __HIP_MEMORY_SCOPE_AGENT);
-        } else {
-          if (n < N) P[n] = v0[r];
-          if (n + 16 < N) P[n + 16] = v1[r];
-        }
-      }
-      if constexpr (KIND == EPI_PART) {
-        if (fold) {
-          // Every thread's partial stores have completed (vmcnt counts
-          // stores here) before thread 0 counts this split in; the split
-          // that counts last finishes the pair. No split waits for another.
-          __builtin_amdgcn_s_waitcnt(VMCNT0);
-          __syncthreads();
-          if (tid == 0) {
-            const unsigned old = __hip_atomic_fetch_add(e.cnt + np, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            sLast = old == (unsigned)(splits - 1);
-            // back to zero for the next launch (and graph replay)
-            if (sLast) __hip_atomic_store(e.cnt + np, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          }
-          __syncthreads();
-          if (sLast) fold_pair<T>(e, np, M, N, splits, tid, sPart);
-        }
+        float* P = part + (size_t)s * Mt * N + (size_t)mg[r] * N;
+        if (n < N) P[n] = v0[r];
+        if (n + 16 < N) P[n + 16] = v1[r];
       }
     }
   }
@@ -1466,11 +1392,9 @@ size_t frag_index(int n, int k, int KS, int dtype) {
 
 int frag_slab(int dtype) { return dtype == DT_BF16 ? 32 : 16; }
 
-static int skinny_spw(const GemmDesc& g) { return g.epi.kind == EPI_PART ? 4 : 8; }
-
-int skinny_splits(const GemmDesc& g) {
-  const int sw = frag_slab(g.dtype);
-  const int per_wg = 4 * skinny_spw(g) * sw;
+constexpr int SKINNY_SPW = 8;
+static int skinny_splits(const GemmDesc& g) {
+  const int per_wg = 4 * SKINNY_SPW * frag_slab(g.dtype);
   return std::max(1, (g.K + per_wg - 1) / per_wg);
 }
 
@@ -1482,7 +1406,7 @@ static hipError_t run_skinny_t(const GemmDesc& g, int splits, const Scratch& s,
   hipExtLaunchKernelGGL((k_skinny<T, SPW, KIND>), dim3(grid), dim3(256), 0, st, caps.ev_start,
                         caps.ev_stop, 0, (const T*)g.A, g.a_blk, g.frames, (const T*)g.W, g.frag_ks,
                         g.frag_ks0, g.M, g.N, g.K, splits, g.epi, s.ptr);
-  if (splits > 1 && g.epi.kind != EPI_PART) {
+  if (splits > 1) {
     const int Mt = g.M * g.frames;
     const long long total = (long long)Mt * ((g.N + 31) / 32) * 16;
     int rgrid = (int)std::min<long long>((total + 255) / 256, 4096);
@@ -1496,43 +1420,431 @@ template <typename T>
 static hipError_t run_skinny_kind(const GemmDesc& g, int splits, const Scratch& s, const LaunchCaps& caps,
                                   hipStream_t st) {
   switch (g.epi.kind) {
-    case EPI_F32: return run_skinny_t<T, 8, EPI_F32>(g, splits, s, caps, st);
-    case EPI_T: return run_skinny_t<T, 8, EPI_T>(g, splits, s, caps, st);
-    case EPI_RESID: return run_skinny_t<T, 8, EPI_RESID>(g, splits, s, caps, st);
-    case EPI_GELU: return run_skinny_t<T, 8, EPI_GELU>(g, splits, s, caps, st);
-    case EPI_SWISH: return run_skinny_t<T, 8, EPI_SWISH>(g, splits, s, caps, st);
-    case EPI_GEGLU: return run_skinny_t<T, 8, EPI_GEGLU>(g, splits, s, caps, st);
-    case EPI_QKV_ROPE: return run_skinny_t<T, 8, EPI_QKV_ROPE>(g, splits, s, caps, st);
-    case EPI_QKV_PLAIN: return run_skinny_t<T, 8, EPI_QKV_PLAIN>(g, splits, s, caps, st);
-    case EPI_EULER: return run_skinny_t<T, 8, EPI_EULER>(g, splits, s, caps, st);
-    case EPI_PART: return run_skinny_t<T, 4, EPI_PART>(g, splits, s, caps, st);
+    case EPI_F32: return run_skinny_t<T, SKINNY_SPW, EPI_F32>(g, splits, s, caps, st);
+    case EPI_T: return run_skinny_t<T, SKINNY_SPW, EPI_T>(g, splits, s, caps, st);
+    case EPI_GELU: return run_skinny_t<T, SKINNY_SPW, EPI_GELU>(g, splits, s, caps, st);
+    case EPI_SWISH: return run_skinny_t<T, SKINNY_SPW, EPI_SWISH>(g, splits, s, caps, st);
+    case EPI_GEGLU: return run_skinny_t<T, SKINNY_SPW, EPI_GEGLU>(g, splits, s, caps, st);
+    case EPI_QKV_ROPE: return run_skinny_t<T, SKINNY_SPW, EPI_QKV_ROPE>(g, splits, s, caps, st);
+    case EPI_QKV_PLAIN: return run_skinny_t<T, SKINNY_SPW, EPI_QKV_PLAIN>(g, splits, s, caps, st);
     default: return hipErrorInvalidValue;
   }
 }
+
+// ---------------------------------------------------------------------------
+// Slim GEMM: the skinny GEMM in 16-row tiles. A workgroup of NW waves owns
+// 16 rows x 16 NB columns of the result and the whole of K: wave w takes the
+// w-th part of the K-slabs with all its loads in flight at once, the waves'
+// sums are added in wave order through LDS, and 256 threads run the epilogue,
+// whose own operands were requested with the tile's. No split leaves the
+// workgroup, so a residual update needs neither partials nor a counter.
+//
+// What bounds these launches is latency (a launch with nothing to do takes
+// 1.5 us in a graph, one that only streams 16.8 MB 4.2 us), then the bytes a
+// CU draws from L2: the 64-row tile of k_skinny reads all of A into each of
+// its few workgroups, this one a quarter of A (50 rows: 4 row tiles) and the
+// weights 4 times from L2 (the row tiles of a column block are neighbours on
+// one XCD, so HBM serves them once).
+// ---------------------------------------------------------------------------
+
+constexpr int SLIM_NW = 8, SLIM_LN_NW = 16;
+
+// LNR > 0: the operand is the LayerNorm of ln.x over K <= 256 LNR columns
+// (NW = 16).
+template <typename T, int NW, int SPW, int NB, int KIND, int LNR>
+__global__ __launch_bounds__(64 * NW) void k_slim(const T* __restrict__ A, size_t a_blk, LnOperand ln, int frames,
+                                                  const T* __restrict__ Wf, int KS, int ks0, int M, int N, int K,
+                                                  Epi e) {
+  VLA_WAVE_BEGIN(KK_SKINNY);
+  constexpr int DT = sizeof(T) == 2 ? DT_BF16 : DT_F32;
+  constexpr int VEC = 16 / sizeof(T);
+  constexpr int SW = 4 * VEC;
+  constexpr bool PAIRED = KIND == EPI_GEGLU || KIND == EPI_QKV_ROPE;
+  constexpr bool LN = LNR > 0;
+  static_assert(!PAIRED || NB == 2, "paired epilogues need 32 columns");
+  static_assert(!LN || (NW == 16 && 256 * LNR <= NW * SPW * SW), "a wave per row, all of K in one request");
+  __shared__ float red[NW][NB][4][64];  // [wave][n-block][r][lane]
+  __shared__ float sInv[16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g4 = lane >> 4;
+  const int mt = (M + 15) / 16, ncb = (N + 16 * NB - 1) / (16 * NB);
+  const int nslab = (K + SW - 1) / SW, pw = (nslab + NW - 1) / NW;
+  const int per_cb = mt * frames, total = ncb * per_cb;
+  const T dummy = T();
+  constexpr uint32_t CH = 1024;  // bytes of a fragment chunk
+  const bool rowscale = !LN && KIND != EPI_RESID && e.rowss != nullptr;
+  // each XCD takes a contiguous range of tiles (see k_gemm)
+  const int G = gridDim.x;
+  const int first = G % 8 == 0 ? (int)(blockIdx.x % 8) * (G / 8) + (int)(blockIdx.x / 8) : (int)blockIdx.x;
+  for (int w = first; w < total; w += G) {
+    const int cb = w / per_cb, q = w - cb * per_cb;
+    const int f = q / mt, mi = q - f * mt;
+    const int arow = mi * 16 + (lane & 15);  // this lane's A row
+    // Folded RMSNorm: rows 2 wave, 2 wave + 1 of the tile (half a wave each),
+    // lane's blocks l, l + 32; requested before the operands, so waiting for
+    // them does not wait for those
+    float ssq[2] = {0.f, 0.f};
+    if (rowscale && NW == 8) {
+      const Rsrc rs = rsrc(e.rowss, (size_t)e.rowss_n * M * 4);
+      const int row = mi * 16 + 2 * wave + (lane >> 5);
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const int p = (lane & 31) + 32 * k;
+        ssq[k] = bld1(rs, p < e.rowss_n && row < M ? (uint32_t)(((size_t)p * M + row) * 4) : OOB);
+      }
+    }
+    const int s0 = wave * pw, s1 = min(nslab, s0 + pw);
+    f32x4 acc[NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) acc[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // The wave's part of a column block's weights (and, below, of a row tile's
+    // operand) is a buffer of its own that ends at slab s1, so slabs past the
+    // end read as zero and no load carries a condition.
+    Rsrc rw[NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+      rw[nb] = rsrc((const char*)Wf + ((size_t)(cb * NB + nb) * KS + ks0) * CH, (size_t)max(s1, 0) * CH);
+    auto load_w = [&](int sb, uint4 (&bf)[SPW][NB]) {
+      // (the offset runs along in a vector register, opaque to the compiler
+      // every fourth slab: as constants, the offsets past an instruction's
+      // 4 KB reach would be kept in scalar registers, more than there are)
+      uint32_t off = (uint32_t)sb * CH + lane * 16;
+#pragma unroll
+      for (int u = 0; u < SPW; ++u) {
+        if (u > 0 && u % 4 == 0) {
+          off += 4 * CH;
+          asm("" : "+v"(off));
+        }
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) bf[u][nb] = bld16(rw[nb], off + (u % 4) * CH);
+      }
+    };
+
+    // the epilogue's operands: thread tid < 256 finishes row erow, columns
+    // n (and n + 16)
+    const int eloc = (lane >> 4) * 4 + (wave & 3), erow = mi * 16 + eloc;
+    const int n = cb * 16 * NB + (lane & 15);
+    const bool eok = tid < 256 && erow < M;
+    const int m = f * M + erow;  // row over all frames
+    float b0 = 0.f, b1 = 0.f, o0 = 0.f, o1 = 0.f, g0 = 0.f, g1 = 0.f, c0 = 1.f, c1 = 1.f;
+    auto load_epi = [&]() {
+      if (tid >= 256) return;
+      auto two = [&](Rsrc r, size_t base, float& x0, float& x1) {
+        x0 = bld1(r, eok && n < N ? (uint32_t)((base + n) * 4) : OOB);
+        if (NB == 2) x1 = bld1(r, eok && n + 16 < N ? (uint32_t)((base + n + 16) * 4) : OOB);
+      };
+      if (KIND != EPI_GEGLU && KIND != EPI_QKV_ROPE && KIND != EPI_QKV_PLAIN && e.bias)
+        two(rsrc(e.bias, (size_t)N * 4), 0, b0, b1);
+      if (KIND == EPI_F32 && e.rowadd)
+        two(rsrc(e.rowadd, span(e.rowadd_period, e.ldra, N, 4)), (size_t)(m % e.rowadd_period) * e.ldra, o0, o1);
+      if (KIND == EPI_EULER) two(rsrc(e.x, span(M * frames, e.ldx, N, 4)), (size_t)m * e.ldx, o0, o1);
+      if (KIND == EPI_RESID) {
+        two(rsrc(e.resid, span(M * frames, e.ldr, N, 4)), (size_t)m * e.ldr, o0, o1);
+        if (e.norm_g) two(rsrc(e.norm_g, (size_t)N * 4), 0, g0, g1);
+        if (e.colscale) two(rsrc(e.colscale, (size_t)N * 4), 0, c0, c1);
+      }
+      if (KIND == EPI_QKV_ROPE && eok && n + 16 < N && n < (e.nq + e.nkv) * e.hd) {
+        const int pp = n % e.hd;
+        const size_t t = (size_t)(e.pos0 + epi_key(e, m)) * (e.hd / 2) + 16 * (pp >> 5) + (pp & 15);
+        o0 = e.rope_cos[t];
+        o1 = e.rope_sin[t];
+      }
+    };
+
+    if constexpr (LN) {
+      // Wave w normalises row w of the tile: lane l holds columns 4 l + 256 j,
+      // the statistics stay inside the wave, and the operand goes through LDS
+      // into fragment order (16-byte chunk c = k / VEC of row i at LNP c + 16 i
+      // bytes; the padded stride spreads the chunks of one row over the banks).
+      constexpr int R = LNR, LNP = 16 * 16 + 16;
+      __shared__ __attribute__((aligned(16))) unsigned char sA[256 * R / VEC * LNP];
+      const int xrow = mi * 16 + wave;
+      const Rsrc rx = rsrc(ln.x + (size_t)xrow * ln.ldx, xrow < M ? (size_t)K * 4 : 0);
+      const Rsrc rg = rsrc(ln.g, (size_t)K * 4), rb = rsrc(ln.b ? ln.b : ln.g, ln.b ? (size_t)K * 4 : 0);
+      f32x4 xv[R], gv[R], bv[R];
+      uint4 bf[SPW][NB];
+#pragma unroll
+      for (int j = 0; j < R; ++j) xv[j] = bld4f(rx, (uint32_t)(lane * 16 + j * 1024));
+#pragma unroll
+      for (int j = 0; j < R; ++j) {
+        gv[j] = bld4f(rg, (uint32_t)(lane * 16 + j * 1024));
+        bv[j] = bld4f(rb, (uint32_t)(lane * 16 + j * 1024));
+      }
+      load_w(s0, bf);
+      load_epi();
+      __builtin_amdgcn_sched_barrier(0);  // every load is out before the first wait
+      float p1 = 0.f, p2 = 0.f;
+#pragma unroll
+      for (int j = 0; j < R; ++j) p1 += (xv[j][0] + xv[j][1]) + (xv[j][2] + xv[j][3]);
+      const float mean = wave_sum_x16_x32(row16_sum(p1)) / K;
+#pragma unroll
+      for (int j = 0; j < R; ++j) {
+        const bool ok = lane * 4 + j * 256 < K;  // (K is a multiple of 4)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const float d = ok ? xv[j][c] - mean : 0.f;
+          p2 += d * d;
+        }
+      }
+      const float inv = 1.f / sqrtf(wave_sum_x16_x32(row16_sum(p2)) / K + 1e-6f);
+#pragma unroll
+      for (int j = 0; j < R; ++j) {
+        const int k = lane * 4 + j * 256;
+        f32x4 y;
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          y[c] = k < K ? (xv[j][c] - mean) * inv * (ln.g_plus_one ? 1.f + gv[j][c] : gv[j][c]) + bv[j][c] : 0.f;
+        unsigned char* d = sA + (size_t)(k / VEC) * LNP + wave * 16 + (k % VEC) * sizeof(T);
+        if constexpr (sizeof(T) == 2)
+          *(uint2*)d = make_uint2(f2bf2(y[0], y[1]), f2bf2(y[2], y[3]));
+        else
+          *(f32x4*)d = y;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < SPW; ++u) {
+        // (slabs past the wave's range multiply zero weights)
+        const int c = min(4 * (s0 + u) + g4, 256 * R / VEC - 1);
+        const uint4 af = *(const uint4*)(sA + (size_t)c * LNP + (lane & 15) * 16);
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) acc[nb] = mfma_step(af, bf[u][nb], acc[nb], dummy);
+      }
+    } else {
+      const Rsrc ra = rsrc(A + (size_t)f * a_blk, (size_t)max(s1, 0) * 4 * CH);  // frame f's block
+      const uint32_t aoff = arow < M ? (uint32_t)(mi * CH + lane * 16) : OOB;
+      const bool tail = K % SW != 0 && s1 == nslab;  // K ends inside this wave's last slab
+      for (int sb = s0; sb < max(s1, s0 + 1); sb += SPW) {
+        uint4 bf[SPW][NB], af[SPW];
+        load_w(sb, bf);
+        uint32_t ao = aoff + (uint32_t)sb * 4 * CH;
+#pragma unroll
+        for (int u = 0; u < SPW; ++u) {
+          af[u] = bld16(ra, ao);
+          ao += 4 * CH;
+          asm("" : "+v"(ao));
+        }
+        if (sb == s0) load_epi();
+        __builtin_amdgcn_sched_barrier(0);  // every load is out before the first wait
+        if (tail) {
+          int kl = K - sb * SW - g4 * VEC;  // (opaque, so that nothing of this leaves the branch)
+          asm("" : "+v"(kl));
+#pragma unroll
+          for (int u = 0; u < SPW; ++u)
+            if (u * SW >= kl) af[u] = make_uint4(0u, 0u, 0u, 0u);
+        }
+#pragma unroll
+        for (int u = 0; u < SPW; ++u)
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) acc[nb] = mfma_step(af[u], bf[u][nb], acc[nb], dummy);
+      }
+      if (rowscale) {
+        float t = ssq[0] + ssq[1];
+        t = row16_sum(t);
+        t += __shfl_xor(t, 16);
+        if ((lane & 31) == 0) sInv[2 * wave + (lane >> 5)] = 1.f / sqrtf(t / e.rowss_d + 1e-6f);
+      }
+    }
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) red[wave][nb][r][lane] = acc[nb][r];
+    __syncthreads();
+    if (tid < 256) {
+      // lane (g, i) of wave r holds row 4 g + r, column i of the tile
+      const int r = wave & 3;
+      float v0 = 0.f, v1 = 0.f;
+#pragma unroll
+      for (int u = 0; u < NW; ++u) {
+        v0 += red[u][0][r][lane];
+        if (NB == 2) v1 += red[u][NB - 1][r][lane];
+      }
+      if (rowscale) {
+        const float sc = sInv[eloc];
+        v0 *= sc;
+        v1 *= sc;
+      }
+      v0 += b0;
+      v1 += b1;
+      if constexpr (KIND == EPI_RESID) {
+        float x0 = __builtin_fmaf(c0, v0, o0), x1 = __builtin_fmaf(c1, v1, o1);
+        const bool k0 = eok && n < N, k1 = NB == 2 && eok && n + 16 < N;
+        float* xr = e.resid + (size_t)m * e.ldr + n;
+        if (k0) xr[0] = x0;
+        if (k1) xr[16] = x1;
+        if (e.norm_g) {
+          T* h = (T*)e.norm_out;
+          if (k0) TT<T>::st(h + afrag_index(DT, m, n), x0 * g0);
+          if (k1) TT<T>::st(h + afrag_index(DT, m, n + 16), x1 * g1);
+          float ss = (k0 ? x0 * x0 : 0.f) + (k1 ? x1 * x1 : 0.f);
+          ss = row16_sum(ss);
+          if ((lane & 15) == 0 && eok) e.rowss[(size_t)cb * M + erow] = ss;
+        }
+      } else if constexpr (KIND == EPI_EULER) {
+        auto put = [&](int col, float v, float x) {
+          const float xn = __builtin_fmaf(e.dt, v, x * e.xs);
+          e.x[(size_t)m * e.ldx + col] = xn;
+          TT<T>::st((T*)e.xop + out_at<T>(e, m, col, e.ldxop, e.blk_xop), xn);
+        };
+        if (eok && n < N) put(n, v0, o0);
+        if (NB == 2 && eok && n + 16 < N) put(n + 16, v1, o1);
+      } else if constexpr (KIND == EPI_F32) {
+        float* o = (float*)e.out + (size_t)m * e.ldo + n;
+        if (eok && n < N) o[0] = v0 + o0;
+        if (NB == 2 && eok && n + 16 < N) o[16] = v1 + o1;
+      } else if constexpr (KIND == EPI_QKV_ROPE) {
+        if (eok && n + 16 < N) {
+          const int hd = e.hd, qcols = e.nq * hd, kcols = e.nkv * hd;
+          if (n < qcols + kcols) {
+            const bool isq = n < qcols;
+            const int rn = isq ? n : n - qcols;
+            const int head = rn / hd, pp = rn - head * hd;
+            const int i = 16 * (pp >> 5) + (pp & 15);
+            const float x0 = v0 * o0 - v1 * o1, x1 = v1 * o0 + v0 * o1;
+            if (isq) {
+              T* dst = (T*)e.q + (size_t)m * e.ldq + head * hd;
+              TT<T>::st(dst + i, x0);
+              TT<T>::st(dst + i + hd / 2, x1);
+            } else {
+              const int key = epi_key(e, m);
+              T* dst = (T*)e.k + epi_kblk(e, m, e.blk_k);
+              TT<T>::st(dst + kv_kidx(DT, e.kv_nb, hd, head, key, i), x0);
+              TT<T>::st(dst + kv_kidx(DT, e.kv_nb, hd, head, key, i + hd / 2), x1);
+            }
+          } else {
+            epi_pair<T, KIND>(e, M * frames, N, m, n, v0, v1);  // V columns: stores only
+          }
+        }
+      } else {
+        Epi s = e;  // the rest only store, with the bias added
+        s.bias = nullptr;
+        if (eok) {
+          if constexpr (NB == 2)
+            epi_pair<T, KIND>(s, M * frames, N, m, n, v0, v1);
+          else if (n < N)
+            epi_one<T, KIND>(s, m, n, v0);
+        }
+      }
+    }
+    __syncthreads();  // the LDS is free again
+  }
+  VLA_WAVE_END(KK_SKINNY);
+}
+
+// n-blocks (16 columns) per slim tile: two for the paired epilogues and the
+// wide ones, one for the narrow outputs (twice the workgroups); a residual
+// update of more than 1024 columns that writes row sums takes two, so they
+// are at most 64 blocks
+static int slim_nb(const Epi& e, int N) {
+  if (e.kind == EPI_RESID) return e.norm_g && N > 1024 ? 2 : 1;
+  return e.kind == EPI_F32 || e.kind == EPI_T || e.kind == EPI_SWISH || e.kind == EPI_EULER ? 1 : 2;
+}
+int slim_blocks(int N) { return N > 1024 ? (N + 31) / 32 : (N + 15) / 16; }
+static int slim_tiles(const GemmDesc& g) {
+  const int cols = 16 * slim_nb(g.epi, g.N);
+  return (g.N + cols - 1) / cols * ((g.M + 15) / 16);
+}
+// The slim kernel where its tiles of one frame come in at most two rounds on
+// the chip (the expert's gate/up, 256 column blocks of four row tiles, would
+// draw 384 KB per CU from L2 against k_skinny's 164 KB). The frame count does
+// not enter: a frame's sums are the same in every group. A residual update
+// has no other kernel.
+constexpr int SLIM_MAX_TILES = 512;
+static bool use_slim(const GemmDesc& g) {
+  return g.epi.kind == EPI_RESID || g.epi.kind == EPI_EULER || slim_tiles(g) <= SLIM_MAX_TILES;
+}
+// The operand's LayerNorm inside the GEMM: K as wide as the registers of a
+// wave per row hold (x, gain, shift and the weights in flight).
+constexpr int slim_ln_max_k(int dtype) { return dtype == DT_BF16 ? 1536 : 1024; }
+bool slim_ln_fits(int dtype, int M, int N, int K, int kind) {
+  if (kind != EPI_T && kind != EPI_QKV_PLAIN && kind != EPI_GELU && kind != EPI_EULER) return false;
+  GemmDesc g{};
+  g.M = M;
+  g.N = N;
+  g.epi.kind = kind;
+  return K % 8 == 0 && K <= slim_ln_max_k(dtype) && M <= 64 && slim_tiles(g) <= SLIM_MAX_TILES;
+}
+
+template <typename T, int NW, int SPW, int NB, int KIND, int LNR>
+static hipError_t run_slim_t(const GemmDesc& g, const LaunchCaps& caps, hipStream_t st) {
+  int grid = (g.N + 16 * NB - 1) / (16 * NB) * ((g.M + 15) / 16) * g.frames;
+  if (caps.max_wgs > 0) grid = std::min(grid, caps.max_wgs);
+  hipExtLaunchKernelGGL((k_slim<T, NW, SPW, NB, KIND, LNR>), dim3(grid), dim3(64 * NW), 0, st, caps.ev_start,
+                        caps.ev_stop, 0, (const T*)g.A, g.a_blk, g.ln, g.frames, (const T*)g.W, g.frag_ks,
+                        g.frag_ks0, g.M, g.N, g.K, g.epi);
+  return hipGetLastError();
+}
+
+// K-slabs a wave requests at once: its whole share where the registers
+// allow (NB = 1: 24 slabs, NB = 2: 16), else in rounds
+template <typename T, int NB, int KIND>
+static hipError_t run_slim_spw(const GemmDesc& g, const LaunchCaps& caps, hipStream_t st) {
+  const int nslab = (g.K + frag_slab(g.dtype) - 1) / frag_slab(g.dtype), pw = (nslab + SLIM_NW - 1) / SLIM_NW;
+  if (pw <= 4) return run_slim_t<T, SLIM_NW, 4, NB, KIND, 0>(g, caps, st);
+  if (pw <= 8) return run_slim_t<T, SLIM_NW, 8, NB, KIND, 0>(g, caps, st);
+  if (NB == 2 || pw <= 16) return run_slim_t<T, SLIM_NW, 16, NB, KIND, 0>(g, caps, st);
+  return run_slim_t<T, SLIM_NW, NB == 1 ? 24 : 16, NB, KIND, 0>(g, caps, st);
+}
+
+template <typename T>
+static hipError_t run_slim_kind(const GemmDesc& g, const LaunchCaps& caps, hipStream_t st) {
+  switch (g.epi.kind) {
+    case EPI_F32: return run_slim_spw<T, 1, EPI_F32>(g, caps, st);
+    case EPI_T: return run_slim_spw<T, 1, EPI_T>(g, caps, st);
+    case EPI_SWISH: return run_slim_spw<T, 1, EPI_SWISH>(g, caps, st);
+    case EPI_EULER: return run_slim_spw<T, 1, EPI_EULER>(g, caps, st);
+    case EPI_GELU: return run_slim_spw<T, 2, EPI_GELU>(g, caps, st);
+    case EPI_GEGLU: return run_slim_spw<T, 2, EPI_GEGLU>(g, caps, st);
+    case EPI_QKV_ROPE: return run_slim_spw<T, 2, EPI_QKV_ROPE>(g, caps, st);
+    case EPI_QKV_PLAIN: return run_slim_spw<T, 2, EPI_QKV_PLAIN>(g, caps, st);
+    case EPI_RESID:
+      return slim_nb(g.epi, g.N) == 1 ? run_slim_spw<T, 1, EPI_RESID>(g, caps, st)
+                                          : run_slim_spw<T, 2, EPI_RESID>(g, caps, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+template <typename T, int NB, int KIND>
+static hipError_t run_slim_ln_k(const GemmDesc& g, const LaunchCaps& caps, hipStream_t st) {
+  constexpr int S = sizeof(T) == 2 ? 1 : 2;  // slabs of a wave per 512 columns of K
+  if (g.K <= 512) return run_slim_t<T, SLIM_LN_NW, S, NB, KIND, 2>(g, caps, st);
+  if (g.K <= 1024) return run_slim_t<T, SLIM_LN_NW, 2 * S, NB, KIND, 4>(g, caps, st);
+  if constexpr (sizeof(T) == 2) return run_slim_t<T, SLIM_LN_NW, 3, NB, KIND, 6>(g, caps, st);
+  return hipErrorInvalidValue;
+}
+template <typename T>
+static hipError_t run_slim_ln(const GemmDesc& g, const LaunchCaps& caps, hipStream_t st) {
+  switch (g.epi.kind) {
+    case EPI_T: return run_slim_ln_k<T, 1, EPI_T>(g, caps, st);
+    case EPI_EULER: return run_slim_ln_k<T, 1, EPI_EULER>(g, caps, st);
+    case EPI_GELU: return run_slim_ln_k<T, 2, EPI_GELU>(g, caps, st);
+    case EPI_QKV_PLAIN: return run_slim_ln_k<T, 2, EPI_QKV_PLAIN>(g, caps, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+
 
 static hipError_t launch_skinny(const GemmDesc& g, const Scratch& s, const LaunchCaps& caps,
                                 hipStream_t st) {
   if (g.M > 64 || g.frames < 1 || g.frames > MAX_FRAMES ||
       (g.frames > 1 && (g.epi.blk_rows != g.M || g.a_blk < afrag_elems(g.dtype, g.K))))
     return hipErrorInvalidValue;
-  const int splits = skinny_splits(g);
-  const size_t need = (size_t)splits * g.M * g.frames * g.N;
   const Epi& e = g.epi;
-  // folded RMSNorm (Epi::rowss): one frame; a producer's partials in at most
-  // 8 splits, whole 8-column groups, its operand output in the row-block
-  // layout; a consumer's product unsplit (the scale precedes the epilogue)
-  if (e.kind == EPI_PART && e.norm_g &&
-      (g.frames != 1 || splits > 8 || g.N % 8 || (g.N + 31) / 32 > 64 || !e.x || e.ldx < g.N || !e.norm_out ||
-       !e.rowss || !e.cnt || !e.afrag))
-    return hipErrorInvalidValue;
-  if (e.kind != EPI_PART && e.rowss &&
-      (g.frames != 1 || splits != 1 || e.rowss_n < 1 || e.rowss_n > 64 || e.rowss_d < 1))
-    return hipErrorInvalidValue;
-  if (g.epi.kind == EPI_PART) {
-    if (!g.epi.out || need > (size_t)g.epi.ldo) return hipErrorInvalidValue;
-  } else if (splits > 1 && need > s.floats) {
+  // folded RMSNorm (Epi::rowss): one frame, at most 64 column blocks
+  if (e.kind == EPI_RESID) {
+    if (!e.resid || (e.norm_g && (g.frames != 1 || !e.norm_out || !e.rowss || slim_blocks(g.N) > 64)))
+      return hipErrorInvalidValue;
+  } else if (e.rowss && (g.frames != 1 || e.rowss_n < 1 || e.rowss_n > 64 || e.rowss_d < 1)) {
     return hipErrorInvalidValue;
   }
+  if (g.ln.x) {
+    if (!slim_ln_fits(g.dtype, g.M, g.N, g.K, e.kind) || g.frames != 1 || e.rowss || !g.ln.g || g.ln.ldx % 4 ||
+        (((uintptr_t)g.ln.x | (uintptr_t)g.ln.g | (uintptr_t)g.ln.b) & 15))
+      return hipErrorInvalidValue;
+    return g.dtype == DT_BF16 ? run_slim_ln<uint16_t>(g, caps, st) : run_slim_ln<float>(g, caps, st);
+  }
+  if (use_slim(g)) return g.dtype == DT_BF16 ? run_slim_kind<uint16_t>(g, caps, st) : run_slim_kind<float>(g, caps, st);
+  const int splits = skinny_splits(g);
+  if (splits > 1 && (e.rowss || (size_t)splits * g.M * g.frames * g.N > s.floats)) return hipErrorInvalidValue;
   if (g.dtype == DT_BF16) return run_skinny_kind<uint16_t>(g, splits, s, caps, st);
   return run_skinny_kind<float>(g, splits, s, caps, st);
 }
@@ -1548,11 +1860,16 @@ static const TileCfg kF32Cfg[] = {{64, 64, 32}, {32, 64, 32}};
 
 GemmPlan plan_gemm(const GemmDesc& g) {
   GemmPlan p{};
-  if (g.frag_ks > 0) {  // fragment-ordered weights: skinny kernel
+  if (g.frag_ks > 0) {  // fragment-ordered weights: the skinny kernels
     p.cfg = -1;
+    if (g.ln.x || use_slim(g)) {
+      p.splits = 1;
+      p.tiles = slim_tiles(g) * g.frames;
+      return p;
+    }
     p.splits = skinny_splits(g);
     p.tiles = ((g.N + 31) / 32) * p.splits * g.frames;
-    p.scratch_floats = (p.splits > 1 || g.epi.kind == EPI_PART) ? (size_t)p.splits * g.M * g.frames * g.N : 0;
+    p.scratch_floats = p.splits > 1 ? (size_t)p.splits * g.M * g.frames * g.N : 0;
     return p;
   }
   const TileCfg* cfgs = g.dtype == DT_BF16 ? kBf16Cfg : kF32Cfg;

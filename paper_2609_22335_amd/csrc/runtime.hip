@@ -282,14 +282,12 @@ struct ActWs {
   unsigned* acnt = nullptr;
   int acnt_n = 0;
   // one-frame expert layers fold each RMSNorm into the GEMMs around it
-  // (Epi::rowss): the per-pair row sums of squares [pair][row] and the pair
-  // counters of the split-K producers (zero between launches)
+  // (Epi::rowss): the column blocks' row sums of squares [block][row]
   float* rowss = nullptr;
-  unsigned* pcnt = nullptr;
   size_t blk_xop = 0, blk_de = 0, blk_att = 0, blk_mlp = 0, blk_k = 0, blk_v = 0;
   Scratch scr;
 };
-constexpr int FOLD_MAX_PAIRS = 64;  // expert width <= 64 x 32
+constexpr int FOLD_MAX_BLOCKS = 64;  // expert width <= 64 x 32
 
 struct vla_ctx {
   vla_model* m = nullptr;
@@ -813,36 +811,65 @@ static int gemm_part(const Run& r, const char* tag, const void* A, int lda, int 
   e.kind = EPI_PART;
   e.out = r.scr->ptr;
   e.ldo = (int)std::min<size_t>(r.scr->floats, (size_t)INT32_MAX);
-  if (fr.n > 1) e.blk_rows = M;
   *splits = plan_gemm(gemm_desc(m, A, lda, W, M, N, K, e, 0, fr)).splits;
   return gemm(r, tag, A, lda, W, M, N, K, e, 0, fr);
 }
 
-// Split-K skinny GEMM whose partials the kernel itself adds to the residual
-// x, leaving h = x * gain (row-block operand layout) and the rows' sums of
-// squares for the next GEMM: an RMSNorm folded across two launches (see
-// Epi::rowss). One frame.
-static int gemm_part_fold(const Run& r, const char* tag, const void* A, int lda, int W, int M, int N, int K,
-                          float* x, int g, void* h) {
+// Skinny GEMM added to the residual: x += gate * (A W^T) (gate NULL: 1). With
+// g >= 0 it also leaves h = x * gain g (row-block operand layout) and the rows'
+// sums of squares for the next GEMM: an RMSNorm folded across two launches
+// (see Epi::rowss). One frame.
+static int gemm_resid(const Run& r, const char* tag, const void* A, int lda, int W, int M, int N, int K, float* x,
+                      const float* gate, int g = -1, void* h = nullptr) {
   Epi e;
-  e.kind = EPI_PART;
-  e.out = r.scr->ptr;
-  e.ldo = (int)std::min<size_t>(r.scr->floats, (size_t)INT32_MAX);
-  e.x = x;
-  e.ldx = N;
-  e.norm_g = r.m->f32(g);
-  e.norm_out = h;
-  e.afrag = 1;
-  e.rowss = r.aw->rowss;
-  e.cnt = r.aw->pcnt;
-  return gemm(r, tag, A, lda, W, M, N, K, e, 0, Frames());
+  e.kind = EPI_RESID;
+  e.resid = x;
+  e.ldr = N;
+  e.colscale = gate;
+  if (g >= 0) {
+    e.norm_g = r.m->f32(g);
+    e.norm_out = h;
+    e.rowss = r.aw->rowss;
+  }
+  return gemm(r, tag, A, lda, W, M, N, K, e);
 }
 
 // the consumer side: scale each row of the product by the folded norm's 1/rms
 static void fold_consumer(const Run& r, Epi& e, int d) {
   e.rowss = r.aw->rowss;
-  e.rowss_n = (d + 31) / 32;
+  e.rowss_n = slim_blocks(d);
   e.rowss_d = d;
+}
+
+// Skinny GEMM over the LayerNorm of the fp32 rows ln.x: the norm is applied as
+// the operand is loaded where the kernel can (slim_ln_fits), else it is a
+// launch of its own into h (row-block operand layout). One frame.
+static int gemm_ln(const Run& r, const char* tag, const LnOperand& ln, void* h, int W, int M, int N, int K,
+                   const Epi& e) {
+  vla_model* m = r.m;
+  if (!slim_ln_fits(m->dt, M, N, K, e.kind)) {
+    NormDesc n;
+    n.x = const_cast<float*>(ln.x);
+    n.ldx = ln.ldx;
+    n.rows = M;
+    n.d = K;
+    n.g = ln.g;
+    n.g_plus_one = ln.g_plus_one;
+    n.b = ln.b;
+    n.out = h;
+    n.afrag = 1;
+    VLA_TRY(run_norm(r, n));
+    return gemm(r, tag, h, K, W, M, N, K, e);
+  }
+  GemmDesc g = gemm_desc(m, nullptr, K, W, M, N, K, e);
+  g.ln = ln;
+  LaunchCaps caps = r.caps;
+  VLA_TRY(timer_events(r, tag, &caps));
+  hipError_t err = launch_gemm(g, *r.scr, caps, r.st);
+  if (err != hipSuccess)
+    return fail(VLA_EHIP, std::string("gemm ") + std::to_string(M) + "x" + std::to_string(N) + "x" +
+                              std::to_string(K) + " over a LayerNorm: " + hipGetErrorString(err));
+  return VLA_OK;
 }
 
 static Epi epi_kind(int kind, void* out = nullptr, int ldo = 0, const float* bias = nullptr) {
@@ -859,7 +886,7 @@ static Epi epi_kind(int kind, void* out = nullptr, int ldo = 0, const float* bia
 // RMSNorm (after adding O) -> GeGLU -> down. The down projection is left
 // pending in the scratch (*pend = its split count) for the next norm. In a
 // one-frame expert layer both norms are folded into the GEMMs around them
-// (gemm_part_fold, fold_consumer): the O projection leaves h = x * rms2 for
+// (gemm_resid, fold_consumer): the O projection leaves h = x * rms2 for
 // the gate/up GEMM, and the down projection x * next_g (the next norm's
 // gain) with *pend = -1, so the layer is five launches.
 // Several frames may run together, `rows` rows each:
@@ -869,8 +896,8 @@ static Epi epi_kind(int kind, void* out = nullptr, int ldo = 0, const float* bia
 //  * expert layers of a batched action loop, wide (wl set): the same
 //    stacked rows and row-major operands, the tiled GEMM over all frames'
 //    rows with the row-major copies of the layer's matrices in *wl;
-//  * otherwise expert layers take frame blocks in the row-block operand
-//    layout (skinny GEMMs, one launch for all frames).
+//  * a one-frame expert layer (no wl) takes the row-block operand layout and
+//    the skinny GEMMs.
 // Frame f of a batched expert layer reads the past K/V kpast[f] / vpast[f]
 // and the action workspace's per-frame blocks. Stacked rows get split-K
 // factors planned for a fixed row count (one frame's prefix in the LM, the
@@ -885,34 +912,23 @@ static int decoder_layer(const Run& r, bool lm, const DecLayer& L, float* x, int
   const vla_config& c = m->c;
   const Dims& d = m->d;
   const bool wide = !lm && wl;
-  const bool stacked = lm || wide;  // row-major operands, frames' rows stacked into M
-  const bool af = !stacked;         // skinny operands: row-block operand layout
+  const bool fold = !lm && !wide;   // one-frame expert layer: skinny operands, folded norms
   const bool fb = frames > 1;       // frame blocks
   const ActWs* aw = r.aw;
-  if (!lm && fb && !aw) return fail(VLA_EINVAL, "batched frames: expert layers need an action workspace");
+  if (!lm && (!aw || (fold && (fb || !aw->rowss))))
+    return fail(VLA_EINVAL, "expert layers need an action workspace, several frames the row-major weights, "
+                            "and one frame an expert width of at most 2048");
   if (lm && fb && (kstride == 0 || vstride == 0)) return fail(VLA_EINVAL, "batched prefill: cache strides");
-  const int gm = stacked ? frames * rows : rows;
-  auto frm = [&](size_t a_blk) {
-    Frames f;
-    if (stacked) {
-      // splits: those of one frame's prefix rows (LM; planned for prefill
-      // batches of up to MAX_VLM_BATCH frames), or of the largest batched
-      // action loop (expert): fixed for every group size
-      f.plan_m = lm ? rows : MAX_ACT_BATCH * rows;
-      if (lm) f.plan_batch = MAX_VLM_BATCH;
-    } else {
-      f.n = frames;
-      f.a_blk = fb ? a_blk : 0;
-    }
-    return f;
-  };
-  const bool skin_fb = fb && !stacked;  // skinny frame blocks
-  const int nblk = skin_fb ? rows : 0;   // norm output frame blocks (operand layout)
-  const size_t nblk_out = skin_fb ? aw->blk_de : 0;
-  const bool fold = !lm && af && !fb && aw && aw->rowss;
+  const int gm = frames * rows;
+  // splits of stacked rows: those of one frame's prefix rows (LM; planned for
+  // prefill batches of up to MAX_VLM_BATCH frames), or of the largest batched
+  // action loop (expert): fixed for every group size
+  Frames frm;
+  if (!fold) frm.plan_m = lm ? rows : MAX_ACT_BATCH * rows;
+  if (lm) frm.plan_batch = MAX_VLM_BATCH;
   const bool folded_in = *pend < 0;  // h holds x * rms1 already
   if (folded_in && !fold) return fail(VLA_ESTATE, "a folded norm is pending outside a one-frame expert layer");
-  if (!folded_in) VLA_TRY(norm(r, x, frames * rows, dim, *pend, nullptr, L.rms1, -1, true, h, af, nblk, nblk_out));
+  if (!folded_in) VLA_TRY(norm(r, x, gm, dim, *pend, nullptr, L.rms1, -1, true, h, fold));
   *pend = 0;
   Epi e;
   e.kind = EPI_QKV_ROPE;
@@ -935,9 +951,9 @@ static int decoder_layer(const Run& r, bool lm, const DecLayer& L, float* x, int
   if (folded_in) fold_consumer(r, e, dim);
   const char* tq = lm ? "lm.qkv" : "ex.qkv";
   if (wide)
-    VLA_TRY(gemm_rm(r, tq, h, dim, wl->qkv, dim, gm, d.qkv_n, dim, e, frm(0)));
+    VLA_TRY(gemm_rm(r, tq, h, dim, wl->qkv, dim, gm, d.qkv_n, dim, e, frm));
   else
-    VLA_TRY(gemm(r, tq, h, dim, L.qkv, gm, d.qkv_n, dim, e, 0, frm(skin_fb ? aw->blk_de : 0)));
+    VLA_TRY(gemm(r, tq, h, dim, L.qkv, gm, d.qkv_n, dim, e, 0, frm));
   if (kv_only) return VLA_OK;
   AttnKvDesc a{};
   a.dtype = m->dt;
@@ -957,7 +973,7 @@ static int decoder_layer(const Run& r, bool lm, const DecLayer& L, float* x, int
   }
   a.out = att;
   a.ldo = d.qd;
-  a.out_afrag = af;
+  a.out_afrag = fold;
   a.Sq = rows;
   a.nq = c.lm_heads;
   a.nkv = c.lm_kv_heads;
@@ -979,40 +995,36 @@ static int decoder_layer(const Run& r, bool lm, const DecLayer& L, float* x, int
     }
     a.k1_blk = aw->blk_k;
     a.v1_blk = aw->blk_v;
-    a.out_blk = wide ? (size_t)rows * d.qd : aw->blk_att;
+    a.out_blk = (size_t)rows * d.qd;
   }
   VLA_TRY(attn_kv(r, lm ? "lm.attn" : "ex.attn", a));
   int so = 0;
   const char* to = lm ? "lm.o" : "ex.o";
   if (fold) {
-    VLA_TRY(gemm_part_fold(r, to, att, d.qd, L.o, gm, dim, d.qd, x, L.rms2, h));
+    VLA_TRY(gemm_resid(r, to, att, d.qd, L.o, gm, dim, d.qd, x, nullptr, L.rms2, h));
   } else {
     if (wide)
-      VLA_TRY(gemm_part_rm(r, to, att, d.qd, wl->o, d.qd, gm, dim, d.qd, &so, frm(0)));
+      VLA_TRY(gemm_part_rm(r, to, att, d.qd, wl->o, d.qd, gm, dim, d.qd, &so, frm));
     else
-      VLA_TRY(gemm_part(r, to, att, d.qd, L.o, gm, dim, d.qd, &so, frm(skin_fb ? aw->blk_att : 0)));
-    VLA_TRY(norm(r, x, frames * rows, dim, so, nullptr, L.rms2, -1, true, h, af, nblk, nblk_out));
+      VLA_TRY(gemm_part(r, to, att, d.qd, L.o, gm, dim, d.qd, &so, frm));
+    VLA_TRY(norm(r, x, gm, dim, so, nullptr, L.rms2, -1, true, h));
   }
   Epi eg = epi_kind(EPI_GEGLU, mlpbuf, mlp);
-  eg.afrag = af;
+  eg.afrag = fold;
   if (fold) fold_consumer(r, eg, dim);
-  if (skin_fb) {
-    eg.blk_rows = rows;
-    eg.blk_out = aw->blk_mlp;
-  }
   const char* tg = lm ? "lm.gateup" : "ex.gateup";
   if (wide)
-    VLA_TRY(gemm_rm(r, tg, h, dim, wl->gu, dim, gm, 2 * mlp, dim, eg, frm(0)));
+    VLA_TRY(gemm_rm(r, tg, h, dim, wl->gu, dim, gm, 2 * mlp, dim, eg, frm));
   else
-    VLA_TRY(gemm(r, tg, h, dim, L.gu, gm, 2 * mlp, dim, eg, 0, frm(skin_fb ? aw->blk_de : 0)));
+    VLA_TRY(gemm(r, tg, h, dim, L.gu, gm, 2 * mlp, dim, eg, 0, frm));
   const char* td = lm ? "lm.down" : "ex.down";
-  if (fold && next_g >= 0) {
-    VLA_TRY(gemm_part_fold(r, td, mlpbuf, mlp, L.down, gm, dim, mlp, x, next_g, h));
+  if (fold) {
+    VLA_TRY(gemm_resid(r, td, mlpbuf, mlp, L.down, gm, dim, mlp, x, nullptr, next_g, h));
     *pend = -1;
   } else if (wide) {
-    VLA_TRY(gemm_part_rm(r, td, mlpbuf, mlp, wl->down, mlp, gm, dim, mlp, pend, frm(0)));
+    VLA_TRY(gemm_part_rm(r, td, mlpbuf, mlp, wl->down, mlp, gm, dim, mlp, pend, frm));
   } else {
-    VLA_TRY(gemm_part(r, td, mlpbuf, mlp, L.down, gm, dim, mlp, pend, frm(skin_fb ? aw->blk_mlp : 0)));
+    VLA_TRY(gemm_part(r, td, mlpbuf, mlp, L.down, gm, dim, mlp, pend, frm));
   }
   return VLA_OK;
 }
@@ -1180,22 +1192,8 @@ static int run_denoise_dit(const Run& r, const vla_ctx* ctx, const float* noise,
   const int H = c.chunk_len, de = c.ex_dim, A = c.action_dim, L = c.ex_layers;
   const size_t xe = cross_elems(m) * m->esz;
   HIP_TRY(launch_cvt_pad(m->dt, noise, H, A, w.xop, d.a_pad, true, x, r.st));
-  auto adanorm = [&](int pend, const float* gate, const float* shift, const float* scale) {
-    NormDesc n;
-    n.x = w.u;
-    n.ldx = de;
-    n.rows = H;
-    n.d = de;
-    n.splits = pend;
-    n.colscale = gate;
-    n.g = scale;
-    n.g_plus_one = 1;
-    n.b = shift;
-    n.out = w.h;
-    n.ldo = de;
-    n.afrag = 1;
-    return run_norm(r, n);
-  };
+  // adaLN: LayerNorm with gain 1 + scale and the given shift
+  auto adanorm = [&](const float* shift, const float* scale) { return LnOperand{w.u, de, scale, 1, shift}; };
   for (int k = 0; k < c.n_steps; ++k) {
     {
       Epi e = epi_kind(EPI_F32, w.u, de, m->f32(m->in_b));
@@ -1204,12 +1202,10 @@ static int run_denoise_dit(const Run& r, const vla_ctx* ctx, const float* noise,
       e.ldra = de;
       VLA_TRY(gemm(r, "ex.in", w.xop, d.a_pad, m->in_w, H, de, d.a_pad, e));
     }
-    int pend = 0;
-    const float* pgate = nullptr;
     for (int l = 0; l < L; ++l) {
       const DitLayer& D = m->dit[l];
       const float* ad = m->ada + ((size_t)k * L + l) * 6 * de;
-      VLA_TRY(adanorm(pend, pgate, ad, ad + de));
+      const LnOperand ln1 = adanorm(ad, ad + de);
       AttnKvDesc a{};
       a.dtype = m->dt;
       a.q = w.q;
@@ -1220,7 +1216,7 @@ static int run_denoise_dit(const Run& r, const vla_ctx* ctx, const float* noise,
       a.out = w.att;
       a.out_afrag = 1;
       if (l % 2 == 0) {
-        VLA_TRY(gemm(r, "ex.q", w.h, de, D.q, H, de, de, epi_kind(EPI_T, w.q, de)));
+        VLA_TRY(gemm_ln(r, "ex.q", ln1, w.h, D.q, H, de, de, epi_kind(EPI_T, w.q, de)));
         a.k0 = (const char*)ctx->XK + (l / 2) * xe;
         a.v0 = (const char*)ctx->XV + (l / 2) * xe;
         a.S0 = d.prefix;
@@ -1235,23 +1231,19 @@ static int run_denoise_dit(const Run& r, const vla_ctx* ctx, const float* noise,
         e.k = w.kown;
         e.v = w.vown;
         e.kv_nb = d.chunk_pad / 32;
-        VLA_TRY(gemm(r, "ex.qkv", w.h, de, D.qkv, H, 3 * de, de, e));
+        VLA_TRY(gemm_ln(r, "ex.qkv", ln1, w.h, D.qkv, H, 3 * de, de, e));
         a.k0 = w.kown;
         a.v0 = w.vown;
         a.S0 = H;
       }
       VLA_TRY(attn_kv(r, "ex.attn", a));
-      int so = 0;
-      VLA_TRY(gemm_part(r, "ex.o", w.att, de, D.o, H, de, de, &so));
-      VLA_TRY(adanorm(so, ad + 2 * de, ad + 3 * de, ad + 4 * de));
+      VLA_TRY(gemm_resid(r, "ex.o", w.att, de, D.o, H, de, de, w.u, ad + 2 * de));
       Epi e1 = epi_kind(EPI_GELU, w.mlp, c.ex_mlp);
       e1.afrag = 1;
-      VLA_TRY(gemm(r, "ex.fc1", w.h, de, D.fc1, H, c.ex_mlp, de, e1));
-      VLA_TRY(gemm_part(r, "ex.fc2", w.mlp, c.ex_mlp, D.fc2, H, de, c.ex_mlp, &pend));
-      pgate = ad + 5 * de;
+      VLA_TRY(gemm_ln(r, "ex.fc1", adanorm(ad + 3 * de, ad + 4 * de), w.h, D.fc1, H, c.ex_mlp, de, e1));
+      VLA_TRY(gemm_resid(r, "ex.fc2", w.mlp, c.ex_mlp, D.fc2, H, de, c.ex_mlp, w.u, ad + 5 * de));
     }
     const float* fa = m->fada + (size_t)k * 2 * de;
-    VLA_TRY(adanorm(pend, pgate, fa, fa + de));
     Epi e;
     e.kind = EPI_EULER;
     e.afrag = 1;
@@ -1262,7 +1254,7 @@ static int run_denoise_dit(const Run& r, const vla_ctx* ctx, const float* noise,
     e.ldxop = d.a_pad;
     e.dt = m->step_b[k];
     e.xs = m->step_a[k];
-    VLA_TRY(gemm(r, "ex.out", w.h, de, m->out_w, H, A, de, e));
+    VLA_TRY(gemm_ln(r, "ex.out", adanorm(fa, fa + de), w.h, m->out_w, H, A, de, e));
   }
   return VLA_OK;
 }
@@ -1282,20 +1274,7 @@ static int run_denoise_cog(const Run& r, const vla_ctx* ctx, const float* noise,
   const int H = c.chunk_len, de = c.ex_dim, A = c.action_dim, S = d.arows;
   if (!ctx->cog) return fail(VLA_ESTATE, "context has no cognition vector");
   HIP_TRY(launch_cvt_pad(m->dt, noise, H, A, w.xop, d.a_pad, true, x, r.st));
-  auto ln = [&](int pend, int g, int b) {
-    NormDesc n;
-    n.x = w.u;
-    n.ldx = de;
-    n.rows = S;
-    n.d = de;
-    n.splits = pend;
-    n.g = m->f32(g);
-    n.b = m->f32(b);
-    n.out = w.h;
-    n.ldo = de;
-    n.afrag = 1;
-    return run_norm(r, n);
-  };
+  auto ln = [&](int g, int b) { return LnOperand{w.u, de, m->f32(g), 0, m->f32(b)}; };
   for (int k = 0; k < c.n_steps; ++k) {
     {
       Epi e = epi_kind(EPI_F32, w.u, de, m->f32(m->in_b));
@@ -1306,10 +1285,8 @@ static int run_denoise_cog(const Run& r, const vla_ctx* ctx, const float* noise,
     }
     HIP_TRY(launch_copy(w.u + (size_t)H * de, ctx->cog, (size_t)de * 4, r.st));
     HIP_TRY(launch_copy(w.u + (size_t)(H + 1) * de, m->ttok + (size_t)k * de, (size_t)de * 4, r.st));
-    int pend = 0;
     for (int l = 0; l < c.ex_layers; ++l) {
       const CogLayer& L = m->cogl[l];
-      VLA_TRY(ln(pend, L.ln1_g, L.ln1_b));
       Epi e;
       e.kind = EPI_QKV_PLAIN;
       e.q = w.q;
@@ -1320,7 +1297,7 @@ static int run_denoise_cog(const Run& r, const vla_ctx* ctx, const float* noise,
       e.k = w.kown;
       e.v = w.vown;
       e.kv_nb = d.chunk_pad / 32;
-      VLA_TRY(gemm(r, "ex.qkv", w.h, de, L.qkv, S, 3 * de, de, e));
+      VLA_TRY(gemm_ln(r, "ex.qkv", ln(L.ln1_g, L.ln1_b), w.h, L.qkv, S, 3 * de, de, e));
       AttnKvDesc a{};
       a.dtype = m->dt;
       a.q = w.q;
@@ -1334,15 +1311,12 @@ static int run_denoise_cog(const Run& r, const vla_ctx* ctx, const float* noise,
       a.out = w.att;
       a.out_afrag = 1;
       VLA_TRY(attn_kv(r, "ex.attn", a));
-      int so = 0;
-      VLA_TRY(gemm_part(r, "ex.o", w.att, de, L.o, S, de, de, &so));
-      VLA_TRY(ln(so, L.ln2_g, L.ln2_b));
+      VLA_TRY(gemm_resid(r, "ex.o", w.att, de, L.o, S, de, de, w.u, nullptr));
       Epi e1 = epi_kind(EPI_GELU, w.mlp, c.ex_mlp);
       e1.afrag = 1;
-      VLA_TRY(gemm(r, "ex.fc1", w.h, de, L.fc1, S, c.ex_mlp, de, e1));
-      VLA_TRY(gemm_part(r, "ex.fc2", w.mlp, c.ex_mlp, L.fc2, S, de, c.ex_mlp, &pend));
+      VLA_TRY(gemm_ln(r, "ex.fc1", ln(L.ln2_g, L.ln2_b), w.h, L.fc1, S, c.ex_mlp, de, e1));
+      VLA_TRY(gemm_resid(r, "ex.fc2", w.mlp, c.ex_mlp, L.fc2, S, de, c.ex_mlp, w.u, nullptr));
     }
-    VLA_TRY(ln(pend, m->fin_g, m->fin_b));
     Epi e;
     e.kind = EPI_EULER;
     e.afrag = 1;
@@ -1353,7 +1327,7 @@ static int run_denoise_cog(const Run& r, const vla_ctx* ctx, const float* noise,
     e.ldxop = d.a_pad;
     e.dt = m->step_b[k];
     e.xs = m->step_a[k];
-    VLA_TRY(gemm(r, "ex.out", w.h, de, m->out_w, H, A, de, e));
+    VLA_TRY(gemm_ln(r, "ex.out", ln(m->fin_g, m->fin_b), w.h, m->out_w, H, A, de, e));
   }
   return VLA_OK;
 }
@@ -1707,9 +1681,7 @@ static int add_act_lane(vla_model* m) {
     upd(sa, gemm_scratch(dt, N, 2 * de, de, false, true));
     upd(sa, gemm_scratch(dt, H, de, de, false, true));
     upd(sa, gemm_scratch(dt, H, 3 * de, de, false, true));
-    upd(sa, gemm_scratch(dt, H, de, de, true, true));
     upd(sa, gemm_scratch(dt, H, c.ex_mlp, de, false, true));
-    upd(sa, gemm_scratch(dt, H, de, c.ex_mlp, true, true));
     upd(sa, gemm_scratch(dt, H, c.action_dim, de, false, true));
   }
   if (c.head == VLA_HEAD_COG) {
@@ -1718,9 +1690,7 @@ static int add_act_lane(vla_model* m) {
     upd(sa, gemm_scratch(dt, N, de, DIT_TIME_DIM, false, true));
     upd(sa, gemm_scratch(dt, N, de, de, false, true));
     upd(sa, gemm_scratch(dt, S, 3 * de, de, false, true));
-    upd(sa, gemm_scratch(dt, S, de, de, true, true));
     upd(sa, gemm_scratch(dt, S, c.ex_mlp, de, false, true));
-    upd(sa, gemm_scratch(dt, S, de, c.ex_mlp, true, true));
     upd(sa, gemm_scratch(dt, H, c.action_dim, de, false, true));
   }
   // (split partials of all frames of a batched action phase)
@@ -1728,9 +1698,7 @@ static int add_act_lane(vla_model* m) {
   upd(sa, gemm_scratch(dt, F * H, de, de, false, true));
   upd(sa, gemm_scratch(dt, c.n_steps, de, de, false, true));
   upd(sa, gemm_scratch(dt, F * H, d.qkv_n, de, false, true));
-  upd(sa, gemm_scratch(dt, F * H, de, d.qd, true, true));
   upd(sa, gemm_scratch(dt, F * H, 2 * c.ex_mlp, de, false, true));
-  upd(sa, gemm_scratch(dt, F * H, de, c.ex_mlp, true, true));
   // batched loops: tiled GEMMs over all frames' rows, splits of one frame
   // (groups of 1 .. F frames, each planned for the largest group's rows)
   upd(sa, gemm_scratch(dt, H, d.qkv_n, de, false, false, F, 1, F * H));
@@ -1765,11 +1733,8 @@ static int add_act_lane(vla_model* m) {
       a.acnt_n = nc;
     }
   }
-  if (c.head == VLA_HEAD_PI0 && (c.ex_dim + 31) / 32 <= FOLD_MAX_PAIRS && c.ex_dim % 8 == 0 && H <= 64) {
-    VLA_TRY(dmalloc(m, (void**)&a.rowss, (size_t)FOLD_MAX_PAIRS * 64 * 4));
-    VLA_TRY(dmalloc(m, (void**)&a.pcnt, (size_t)FOLD_MAX_PAIRS * 4));
-    HIP_TRY(hipMemset(a.pcnt, 0, (size_t)FOLD_MAX_PAIRS * 4));
-  }
+  if (c.head == VLA_HEAD_PI0 && slim_blocks(c.ex_dim) <= FOLD_MAX_BLOCKS && H <= 64)
+    VLA_TRY(dmalloc(m, (void**)&a.rowss, (size_t)FOLD_MAX_BLOCKS * 64 * 4));
   VLA_TRY(dmalloc(m, (void**)&a.xg, (size_t)F * H * c.action_dim * 4));
   VLA_TRY(dmalloc(m, (void**)&a.nstage, (size_t)F * H * c.action_dim * 4));
   m->aws.push_back(std::move(lane));
@@ -2810,9 +2775,11 @@ int vla_debug_gemm_epi(int32_t dtype, int32_t M, int32_t N, int32_t K, const voi
         x.dt = e.dt;
         x.xs = e.xs;
         break;
-      default:  // RESID_NORM: raw split-K partials, summed by the norm
-        x.kind = EPI_PART;
+      default:  // RESID_NORM: raw split-K partials, summed by the norm (skinny: the residual update itself)
+        x.kind = e.skinny ? EPI_RESID : EPI_PART;
         x.afrag = 0;
+        x.resid = e.resid;
+        x.ldr = N;
         break;
     }
     GemmDesc g{dt, dA, K, dW, K, M, N, K, x};
@@ -2826,7 +2793,7 @@ int vla_debug_gemm_epi(int32_t dtype, int32_t M, int32_t N, int32_t K, const voi
       VLA_TRY(dalloc(p.scratch_floats * 4, (void**)&s.ptr));
       s.floats = p.scratch_floats;
     }
-    if (kind == VLA_DEBUG_EPI_RESID_NORM) {
+    if (kind == VLA_DEBUG_EPI_RESID_NORM && !e.skinny) {
       g.epi.out = s.ptr;
       g.epi.ldo = (int)std::min<size_t>(s.floats, (size_t)INT32_MAX);
     }
@@ -2845,7 +2812,7 @@ int vla_debug_gemm_epi(int32_t dtype, int32_t M, int32_t N, int32_t K, const voi
       n.rows = M;
       n.d = N;
       n.part = s.ptr;
-      n.splits = p.splits;
+      n.splits = e.skinny ? 0 : p.splits;
       n.g = e.gain;
       n.rms = 1;
       n.out = dout;
@@ -3066,6 +3033,7 @@ int vla_debug_gemm_plan(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t 
     if (skinny) {
       g.frag_ks = (K + frag_slab(dt) - 1) / frag_slab(dt);
       g.epi.afrag = 1;
+      if (g.epi.kind == EPI_PART) g.epi.kind = EPI_RESID;  // the residual update needs no partials
     }
     const GemmPlan p = plan_gemm(g);
     plan_tile(g, p, &out[0], &out[1]);
