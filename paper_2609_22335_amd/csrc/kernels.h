@@ -160,6 +160,19 @@ struct LnOperand {
   const float* b = nullptr;
 };
 
+// Read-only data that launches soon after this one read: extra workgroups of
+// the launch, on CUs that its own few workgroups leave idle, read it into the
+// L2 of the XCD that will use it. `whole` 0: a fragment-ordered weight, the
+// x-th eighth on XCD x, as the skinny kernels deal their column blocks out;
+// 1: all of it on every XCD (the prefix's K and V of a layer). A hint: nothing
+// waits for it and no result depends on it.
+struct Prefetch {
+  const void* p[2] = {};
+  uint32_t bytes[2] = {};
+  int whole = 0;
+  int wgs = 0;  // workgroups for it (a multiple of 8; 0: none)
+};
+
 struct GemmDesc {
   int dtype;
   const void* A;
@@ -188,6 +201,7 @@ struct GemmDesc {
   // Skinny kernels, where slim_ln_fits: A is the LayerNorm of ln.x (A and
   // a_blk unused).
   LnOperand ln;
+  Prefetch pf;  // skinny kernels, one frame
   // The most plan_m-row blocks a launch of this plan stacks (a prefill
   // batch). The split count may then be planned for that launch as well
   // (fixed for every batch, so the reduction stays the same).
@@ -294,6 +308,7 @@ struct AttnKvDesc {
   size_t part_floats = 0;
   unsigned* cnt = nullptr;
   int cnt_n = 0;
+  Prefetch pf;  // one frame
 };
 hipError_t launch_attention_kv(const AttnKvDesc& d, const LaunchCaps& caps, hipStream_t st);
 // Floats of partials (and, in *counters, the counters) a launch of these

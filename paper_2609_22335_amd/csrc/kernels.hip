@@ -1173,6 +1173,26 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(const float* __restrict__
   VLA_WAVE_END(KK_SPLITK);
 }
 
+// A prefetch workgroup (see Prefetch): the i-th of them, on XCD blockIdx % 8;
+// one dword per 64-byte half line. The values go nowhere.
+__device__ __forceinline__ void prefetch_wg(const Prefetch& pf, int i) {
+  const uint32_t x = blockIdx.x & 7, j = (uint32_t)i >> 3, n = (uint32_t)pf.wgs >> 3, nt = blockDim.x;
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    if (!pf.p[t]) continue;
+    const Rsrc r = rsrc(pf.p[t], pf.bytes[t]);
+    const uint32_t part = ((pf.bytes[t] + 7) / 8 + 63) & ~63u;
+    const uint32_t lo = pf.whole ? 0 : x * part, hi = pf.whole ? pf.bytes[t] : min(lo + part, pf.bytes[t]);
+    const uint32_t step = n * nt * 64;
+    for (uint32_t off = lo + (j * nt + threadIdx.x) * 64; off < hi; off += 4 * step) {
+      float v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = bld1(r, off + u * step < hi ? off + u * step : OOB);
+      asm volatile("" ::"v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]));
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Skinny GEMM for M <= 64 (the action expert's rows): C[M, N] = A[M, K] W^T
 // with W stored in MFMA fragment order (see frag_index): the 16 x SW fragment
@@ -1200,8 +1220,13 @@ template <typename T, int SPW, int KIND>
 __global__ __launch_bounds__(256) void k_skinny(const T* __restrict__ A, size_t a_blk, int frames,
                                                 const T* __restrict__ Wf, int KS, int ks0, int M,
                                                 int N, int K, int splits, Epi e,
-                                                float* __restrict__ part) {
+                                                float* __restrict__ part, int G, Prefetch pf) {
   VLA_WAVE_BEGIN(KK_SKINNY);
+  if ((int)blockIdx.x >= G) {
+    prefetch_wg(pf, (int)blockIdx.x - G);
+    VLA_WAVE_END(KK_SKINNY);
+    return;
+  }
   constexpr int VEC = 16 / sizeof(T);
   constexpr int SW = 4 * VEC;
   __shared__ float red[4][8][4][64];  // [wave][n-block * 4 + m-tile][r][lane]
@@ -1214,9 +1239,7 @@ __global__ __launch_bounds__(256) void k_skinny(const T* __restrict__ A, size_t 
   const Rsrc rw = rsrc(Wf, (size_t)npairs * 2 * KS * 64 * VEC * sizeof(T));
   // row-block operand layout, one block per frame
   const Rsrc ra = rsrc(A, ((size_t)(frames - 1) * a_blk + (size_t)nslab * 4 * 64 * VEC) * sizeof(T));
-  const int G = gridDim.x;
-  const int first = frames > 1 && G % 8 == 0 ? (int)(blockIdx.x % 8) * (G / 8) + (int)(blockIdx.x / 8)
-                                             : (int)blockIdx.x;
+  const int first = G % 8 == 0 ? (int)(blockIdx.x % 8) * (G / 8) + (int)(blockIdx.x / 8) : (int)blockIdx.x;
   // Folded RMSNorm (see Epi::rowss): thread t holds the partial
   // sums of squares of row t / 4 for the blocks congruent to t % 4 (mod 4),
   // requested before the first tile's loads (waiting for those covers them)
@@ -1392,6 +1415,11 @@ size_t frag_index(int n, int k, int KS, int dtype) {
 
 int frag_slab(int dtype) { return dtype == DT_BF16 ? 32 : 16; }
 
+// none under a workgroup cap or for several frames
+static int prefetch_wgs(const Prefetch& p, int frames, const LaunchCaps& caps) {
+  return caps.max_wgs > 0 || frames > 1 || p.wgs <= 0 || p.wgs % 8 || (!p.p[0] && !p.p[1]) ? 0 : p.wgs;
+}
+
 constexpr int SKINNY_SPW = 8;
 static int skinny_splits(const GemmDesc& g) {
   const int per_wg = 4 * SKINNY_SPW * frag_slab(g.dtype);
@@ -1403,9 +1431,10 @@ static hipError_t run_skinny_t(const GemmDesc& g, int splits, const Scratch& s,
                                const LaunchCaps& caps, hipStream_t st) {
   int grid = ((g.N + 31) / 32) * splits * g.frames;
   if (caps.max_wgs > 0) grid = std::min(grid, caps.max_wgs);
-  hipExtLaunchKernelGGL((k_skinny<T, SPW, KIND>), dim3(grid), dim3(256), 0, st, caps.ev_start,
+  const int pf = prefetch_wgs(g.pf, g.frames, caps);
+  hipExtLaunchKernelGGL((k_skinny<T, SPW, KIND>), dim3(grid + pf), dim3(256), 0, st, caps.ev_start,
                         caps.ev_stop, 0, (const T*)g.A, g.a_blk, g.frames, (const T*)g.W, g.frag_ks,
-                        g.frag_ks0, g.M, g.N, g.K, splits, g.epi, s.ptr);
+                        g.frag_ks0, g.M, g.N, g.K, splits, g.epi, s.ptr, grid, g.pf);
   if (splits > 1) {
     const int Mt = g.M * g.frames;
     const long long total = (long long)Mt * ((g.N + 31) / 32) * 16;
@@ -1454,8 +1483,13 @@ constexpr int SLIM_NW = 8, SLIM_LN_NW = 16;
 template <typename T, int NW, int SPW, int NB, int KIND, int LNR>
 __global__ __launch_bounds__(64 * NW) void k_slim(const T* __restrict__ A, size_t a_blk, LnOperand ln, int frames,
                                                   const T* __restrict__ Wf, int KS, int ks0, int M, int N, int K,
-                                                  Epi e) {
+                                                  Epi e, int G, Prefetch pf) {
   VLA_WAVE_BEGIN(KK_SKINNY);
+  if ((int)blockIdx.x >= G) {
+    prefetch_wg(pf, (int)blockIdx.x - G);
+    VLA_WAVE_END(KK_SKINNY);
+    return;
+  }
   constexpr int DT = sizeof(T) == 2 ? DT_BF16 : DT_F32;
   constexpr int VEC = 16 / sizeof(T);
   constexpr int SW = 4 * VEC;
@@ -1474,7 +1508,6 @@ __global__ __launch_bounds__(64 * NW) void k_slim(const T* __restrict__ A, size_
   constexpr uint32_t CH = 1024;  // bytes of a fragment chunk
   const bool rowscale = !LN && KIND != EPI_RESID && e.rowss != nullptr;
   // each XCD takes a contiguous range of tiles (see k_gemm)
-  const int G = gridDim.x;
   const int first = G % 8 == 0 ? (int)(blockIdx.x % 8) * (G / 8) + (int)(blockIdx.x / 8) : (int)blockIdx.x;
   for (int w = first; w < total; w += G) {
     const int cb = w / per_cb, q = w - cb * per_cb;
@@ -1768,9 +1801,10 @@ template <typename T, int NW, int SPW, int NB, int KIND, int LNR>
 static hipError_t run_slim_t(const GemmDesc& g, const LaunchCaps& caps, hipStream_t st) {
   int grid = (g.N + 16 * NB - 1) / (16 * NB) * ((g.M + 15) / 16) * g.frames;
   if (caps.max_wgs > 0) grid = std::min(grid, caps.max_wgs);
-  hipExtLaunchKernelGGL((k_slim<T, NW, SPW, NB, KIND, LNR>), dim3(grid), dim3(64 * NW), 0, st, caps.ev_start,
+  const int pf = prefetch_wgs(g.pf, g.frames, caps);
+  hipExtLaunchKernelGGL((k_slim<T, NW, SPW, NB, KIND, LNR>), dim3(grid + pf), dim3(64 * NW), 0, st, caps.ev_start,
                         caps.ev_stop, 0, (const T*)g.A, g.a_blk, g.ln, g.frames, (const T*)g.W, g.frag_ks,
-                        g.frag_ks0, g.M, g.N, g.K, g.epi);
+                        g.frag_ks0, g.M, g.N, g.K, g.epi, grid, g.pf);
   return hipGetLastError();
 }
 
@@ -2481,6 +2515,8 @@ struct Attn2Args {
   int nsplit, bps;
   float* part;
   unsigned* cnt;
+  int grid;  // workgroups that take items; those behind them prefetch
+  Prefetch pf;
 };
 
 constexpr float ATT_TAU = 8.f;  // lazy-rescaling slack, log2 units
@@ -2503,6 +2539,11 @@ constexpr int att2_waves() {
 template <typename T, int HDP, int NW>
 __global__ __launch_bounds__(64 * NW) void k_attn2(Attn2Args a) {
   VLA_WAVE_BEGIN(KK_ATTN2);
+  if ((int)blockIdx.x >= a.grid) {
+    prefetch_wg(a.pf, (int)blockIdx.x - a.grid);
+    VLA_WAVE_END(KK_ATTN2);
+    return;
+  }
   constexpr int VEC = 16 / sizeof(T);
   constexpr int SW = 4 * VEC;
   constexpr int NQF = HDP / SW;   // Q fragments (also K fragments per 16-key tile)
@@ -2527,7 +2568,7 @@ __global__ __launch_bounds__(64 * NW) void k_attn2(Attn2Args a) {
   const Rsrc rq = rsrc(a.q, span(a.Sq * a.frames, a.ldq, a.nq * a.hd, sizeof(T)));
 
   __shared__ int sLast;
-  for (int w = blockIdx.x; w < total * a.frames * a.nsplit; w += gridDim.x) {
+  for (int w = blockIdx.x; w < total * a.frames * a.nsplit; w += a.grid) {
     // item w: split sp of query tile wt; frame f: its queries, its two key
     // segments and its output block
     const int sp = w % a.nsplit, wt = w / a.nsplit;
@@ -2814,6 +2855,212 @@ __global__ __launch_bounds__(64 * NW) void k_attn2(Attn2Args a) {
   VLA_WAVE_END(KK_ATTN2);
 }
 
+// ---------------------------------------------------------------------------
+// Cache attention at head dims 128 and 256 (bf16): the same transposed
+// products, with the two halves of the work dealt out differently to the
+// eight waves of a 16-row query tile. Scores: wave w takes key blocks w and
+// w + 8 of a chunk of VB blocks, with all their K in one request. The waves
+// exchange their row maxima, and then their probabilities (in the B-operand
+// fragments of P V, high and remainder parts), through LDS. Output: wave w
+// multiplies every block of the chunk into its own head-dim tiles, so no
+// partial output is merged, and its V fragments, requested when the scores'
+// registers are free, come in under the softmax. Chunks repeat with a running
+// maximum; most calls are one chunk.
+//
+// k_attn2 takes each wave through its blocks one after another (a K round
+// trip, a V round trip and the merge of eight 16 x HDP outputs on the chain),
+// which is what bounds it at these head dims: 25 workgroups of the expert's
+// 355 keys take it 13 us.
+// ---------------------------------------------------------------------------
+
+template <int HDP, int VB>
+__global__ __launch_bounds__(512) void k_attn3(Attn2Args a) {
+  VLA_WAVE_BEGIN(KK_ATTN2);
+  if ((int)blockIdx.x >= a.grid) {
+    prefetch_wg(a.pf, (int)blockIdx.x - a.grid);
+    VLA_WAVE_END(KK_ATTN2);
+    return;
+  }
+  typedef uint16_t T;
+  constexpr int NW = 8, CB = (VB + NW - 1) / NW;  // waves; score blocks per wave and chunk
+  constexpr int NQF = HDP / 32, NOT = HDP / 16, DT = NOT / NW;
+  constexpr int QS = HDP + 8;
+  constexpr uint32_t CH = 1024;  // bytes of a fragment chunk
+  __shared__ __attribute__((aligned(16))) T sQ[16 * QS];
+  __shared__ uint4 sP[NW * CB][2][64];
+  __shared__ float sM[NW][16], sL[NW][16];
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g4 = lane >> 4;
+  const int group = a.nq / a.nkv;
+  const int R = a.Sq * group;
+  const int nblk = a.nb0 + a.nb1;
+  const int total = a.rtiles * a.nkv, all = total * a.frames;
+  const T dummy = T();
+  const Rsrc rq = rsrc(a.q, span(a.Sq * a.frames, a.ldq, a.nq * HDP, sizeof(T)));
+  // each XCD takes a contiguous range of tiles, so the tiles of a frame (and
+  // of a KV head) share their K and V in one L2
+  const int first = a.grid % 8 == 0 ? (int)(blockIdx.x % 8) * (a.grid / 8) + (int)(blockIdx.x / 8) : (int)blockIdx.x;
+  for (int w = first; w < all; w += a.grid) {
+    const int f = __builtin_amdgcn_readfirstlane(w / total), wl = w % total;
+    const int rt = wl % a.rtiles, j = wl / a.rtiles;
+    // KV head j of both segments (nb 32-key blocks of HDP / 16 K chunks and as many V chunks)
+    const size_t h0 = (size_t)a.nb0 * NOT * CH, h1 = (size_t)a.nb1 * NOT * CH;
+    const Rsrc rk0 = rsrc((const char*)a.k0[f] + j * h0, h0), rv0 = rsrc((const char*)a.v0[f] + j * h0, h0);
+    const Rsrc rk1 = rsrc(a.k1 ? (const char*)((const T*)a.k1 + f * a.k1_blk) + j * h1 : (const char*)a.k0[f], h1);
+    const Rsrc rv1 = rsrc(a.v1 ? (const char*)((const T*)a.v1 + f * a.v1_blk) + j * h1 : (const char*)a.v0[f], h1);
+
+    constexpr int QCH = 16 * (HDP / 8);  // 16-byte pieces of the query rows
+    uint4 qld;
+    {
+      const int rr = tid / (HDP / 8), d = (tid % (HDP / 8)) * 8;
+      const int r = rt * 16 + rr;
+      const int sq = f * a.Sq + r / group, h = j * group + r % group;
+      qld = bld16(rq, tid < QCH && r < R ? (uint32_t)(((size_t)sq * a.ldq + h * HDP + d) * sizeof(T)) : OOB);
+    }
+    // block b's chunks start NOT CH b bytes into its segment; blocks at or
+    // past nblk lie past the range of segment 1 and read as zero
+    uint4 kf[CB][2][NQF];
+    auto load_k = [&](int base) {
+#pragma unroll
+      for (int t = 0; t < CB; ++t) {
+        const int b = base + wave + NW * t;
+        const bool seg1 = b >= a.nb0;
+        const Rsrc r = seg1 ? rk1 : rk0;
+        uint32_t off = (uint32_t)(seg1 ? b - a.nb0 : b) * (NOT * CH) + lane * 16;
+#pragma unroll
+        for (int c = 0; c < 2 * NQF; ++c) kf[t][c / NQF][c % NQF] = bld16(r, off + c * CH);
+      }
+    };
+    load_k(0);
+    if (tid < QCH) *(uint4*)&sQ[(tid / (HDP / 8)) * QS + (tid % (HDP / 8)) * 8] = qld;
+    __syncthreads();
+    uint4 qf[NQF];
+#pragma unroll
+    for (int ks = 0; ks < NQF; ++ks) qf[ks] = *(const uint4*)&sQ[(lane & 15) * QS + ks * 32 + g4 * 8];
+
+    float mrun = -INFINITY, lpart = 0.f;  // the lane's query: running maximum, this wave's sum
+    f32x4 o[DT];
+#pragma unroll
+    for (int d = 0; d < DT; ++d) o[d] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    for (int base = 0;;) {
+      f32x4 s[CB][2];
+#pragma unroll
+      for (int t = 0; t < CB; ++t)
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt) s[t][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int t = 0; t < CB; ++t)
+#pragma unroll
+        for (int ks = 0; ks < NQF; ++ks)
+#pragma unroll
+          for (int nt = 0; nt < 2; ++nt) s[t][nt] = mfma_step(kf[t][nt][ks], qf[ks], s[t][nt], dummy);
+      // this wave's V: head-dim tiles DT wave .. + DT - 1 of every block, into
+      // the registers that K held
+      __builtin_amdgcn_sched_barrier(0);
+      uint4 vf[VB][DT];
+#pragma unroll
+      for (int u = 0; u < VB; ++u) {
+        const int b = base + u;
+        const bool seg1 = b >= a.nb0;
+        const Rsrc r = seg1 ? rv1 : rv0;
+        const uint32_t off = (uint32_t)(seg1 ? b - a.nb0 : b) * (NOT * CH) + wave * (DT * CH) + lane * 16;
+#pragma unroll
+        for (int d = 0; d < DT; ++d) vf[u][d] = bld16(r, off + d * CH);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      // scores of key 32 b + 8 g4 + 4 nt + r (the cache layout's order)
+      float p[CB][2][4], mx = -INFINITY;
+#pragma unroll
+      for (int t = 0; t < CB; ++t) {
+        const int u = wave + NW * t, b = base + u;
+        const bool seg1 = b >= a.nb0;
+        const int left = u < VB ? (seg1 ? a.S1 - (b - a.nb0) * 32 : a.S0 - b * 32) - 8 * g4 : 0;  // valid keys from 8 g4 on
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            p[t][nt][r] = 4 * nt + r < left ? s[t][nt][r] * a.scale_log2 : -INFINITY;
+            mx = fmaxf(mx, p[t][nt][r]);
+          }
+      }
+      mx = wave_max_x16_x32(mx);
+      if (lane < 16) sM[wave][lane] = mx;
+      __syncthreads();
+      float mnew = mrun;
+#pragma unroll
+      for (int u = 0; u < NW; ++u) mnew = fmaxf(mnew, sM[u][lane & 15]);
+      const float alpha = mrun == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mrun - mnew);
+      mrun = mnew;
+      float sum = 0.f;
+#pragma unroll
+      for (int t = 0; t < CB; ++t) {
+        uint32_t hi[4], lo[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          // (a row of no valid key has mnew -inf; -inf scores give 0)
+          float x[2];
+#pragma unroll
+          for (int c = 0; c < 2; ++c) {
+            const float sv = p[t][q >> 1][2 * (q & 1) + c];
+            x[c] = sv == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sv - mnew);
+            sum += x[c];
+          }
+          hi[q] = f2bf2(x[0], x[1]);
+          lo[q] = f2bf2(x[0] - bf2f((uint16_t)hi[q]), x[1] - bf2f((uint16_t)(hi[q] >> 16)));
+        }
+        sP[wave + NW * t][0][lane] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+        sP[wave + NW * t][1][lane] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+      }
+      lpart = lpart * alpha + sum;
+      __syncthreads();
+      if (base > 0) {
+#pragma unroll
+        for (int d = 0; d < DT; ++d) o[d] *= alpha;
+      }
+      f32x4 o2[DT];  // the remainder parts' products, a chain of their own
+#pragma unroll
+      for (int d = 0; d < DT; ++d) o2[d] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int u = 0; u < VB; ++u) {
+        const uint4 hi = sP[u][0][lane], lo = sP[u][1][lane];
+#pragma unroll
+        for (int d = 0; d < DT; ++d) {
+          o[d] = mfma_step(vf[u][d], hi, o[d], dummy);
+          o2[d] = mfma_step(vf[u][d], lo, o2[d], dummy);
+        }
+      }
+#pragma unroll
+      for (int d = 0; d < DT; ++d) o[d] += o2[d];
+      base += VB;
+      if (base >= nblk) break;
+      __syncthreads();  // sP and sM are free again
+      load_k(base);
+    }
+    lpart = wave_sum_x16_x32(lpart);
+    if (lane < 16) sL[wave][lane] = lpart;
+    __syncthreads();
+    float den = 0.f;
+#pragma unroll
+    for (int u = 0; u < NW; ++u) den += sL[u][lane & 15];
+    const float inv = 1.f / den;
+    const int prow = rt * 16 + (lane & 15);
+    if (prow < R) {
+      const int sq = prow / group, col = (j * group + prow % group) * HDP + wave * (16 * DT) + 4 * g4;
+      T* ob = (T*)a.out + f * a.out_blk;
+#pragma unroll
+      for (int d = 0; d < DT; ++d) {
+        const int c = col + 16 * d;
+        *(uint2*)(ob + (a.out_afrag ? afrag_index(DT_BF16, sq, c) : (size_t)sq * a.ldo + c)) =
+            make_uint2(f2bf2(o[d][0] * inv, o[d][1] * inv), f2bf2(o[d][2] * inv, o[d][3] * inv));
+      }
+    }
+    __syncthreads();  // the LDS is free again
+  }
+  VLA_WAVE_END(KK_ATTN2);
+}
+
 // Key splits of the cache attention. A split gives each wave ATT_BPW 32-key
 // blocks; there are at most ATT_MAX_SPLITS of them, and splits stop where the
 // launch would exceed ATT_SPLIT_WGS workgroups (enough query tiles fill the
@@ -2846,6 +3093,23 @@ static void attn2_split(Attn2Args& a, float* part, size_t part_floats, unsigned*
   a.cnt = cnt;
 }
 
+// k_attn3: bf16, head dim exactly 128 or 256 (no unused head-dim positions to
+// mask). The chunk is the smallest that holds the call's key blocks.
+static bool use_attn3(int dtype, int hd) { return dtype == DT_BF16 && (hd == 128 || hd == 256); }
+static hipError_t run_attn3(Attn2Args& a, const LaunchCaps& caps, hipStream_t st) {
+  a.nsplit = 1;
+  a.grid = a.rtiles * a.nkv * a.frames;
+  if (caps.max_wgs > 0) a.grid = std::min(a.grid, caps.max_wgs);
+  const int grid = a.grid + prefetch_wgs(a.pf, a.frames, caps);
+  const int nblk = a.nb0 + a.nb1;
+  auto go = [&](auto k) {
+    hipExtLaunchKernelGGL(k, dim3(grid), dim3(512), 0, st, caps.ev_start, caps.ev_stop, 0, a);
+    return hipGetLastError();
+  };
+  if (a.hd == 256) return nblk <= 8 ? go(k_attn3<256, 8>) : nblk <= 12 ? go(k_attn3<256, 12>) : go(k_attn3<256, 16>);
+  return nblk <= 8 ? go(k_attn3<128, 8>) : go(k_attn3<128, 16>);
+}
+
 template <typename T>
 static hipError_t run_attn2_t(Attn2Args& a, int hdp, const LaunchCaps& caps, hipStream_t st, float* part,
                               size_t part_floats, unsigned* cnt, int cnt_n) {
@@ -2860,6 +3124,8 @@ static hipError_t run_attn2_t(Attn2Args& a, int hdp, const LaunchCaps& caps, hip
   }
   int grid = a.rtiles * a.nkv * a.frames * a.nsplit;
   if (caps.max_wgs > 0) grid = std::min(grid, caps.max_wgs);
+  a.grid = grid;
+  grid += prefetch_wgs(a.pf, a.frames, caps);
 #define VLA_ATTN2(H)                                                                           \
   hipExtLaunchKernelGGL((k_attn2<T, H, att2_waves<T, H>()>), dim3(grid),                        \
                         dim3(64 * att2_waves<T, H>()), 0, st, caps.ev_start, caps.ev_stop, 0, a)
@@ -2911,10 +3177,12 @@ hipError_t launch_attention_kv(const AttnKvDesc& d, const LaunchCaps& caps, hipS
   a.hd = d.hd;
   a.S0 = d.S0;
   a.S1 = d.S1;
+  a.pf = d.pf;
   a.nb0 = (d.S0 + 31) / 32;
   a.nb1 = (d.S1 + 31) / 32;
   a.rtiles = (d.Sq * (d.nq / d.nkv) + 15) / 16;
   a.scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)d.hd));
+  if (use_attn3(d.dtype, d.hd)) return run_attn3(a, caps, st);
   if (d.dtype == DT_BF16) return run_attn2_t<uint16_t>(a, hdp, caps, st, d.part, d.part_floats, d.cnt, d.cnt_n);
   return run_attn2_t<float>(a, hdp, caps, st, d.part, d.part_floats, d.cnt, d.cnt_n);
 }
@@ -2922,7 +3190,7 @@ hipError_t launch_attention_kv(const AttnKvDesc& d, const LaunchCaps& caps, hipS
 size_t attn_kv_split_floats(int dtype, int frames, int Sq, int nq, int nkv, int hd, int S0, int S1, int* counters) {
   const int hdp = attn_hdp(hd, dtype);
   *counters = 0;
-  if (hdp < 0 || nkv <= 0 || nq % nkv) return 0;
+  if (hdp < 0 || nkv <= 0 || nq % nkv || use_attn3(dtype, hd)) return 0;
   const int nw = dtype == DT_BF16 ? (hdp * 2 >= 512 ? 4 : 8) : (hdp * 4 >= 512 ? 4 : 8);
   const int nblk = (S0 + 31) / 32 + (S1 + 31) / 32;
   const int tiles = (Sq * (nq / nkv) + 15) / 16 * nkv * frames;

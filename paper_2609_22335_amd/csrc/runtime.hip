@@ -381,7 +381,8 @@ struct vla_model {
   // graph replay: frame inputs staged into fixed buffers, graphs cached per
   // (context, VLM grid cap) and (action lane, context)
   std::map<std::tuple<int, int, int, int>, hipGraphExec_t> pre_graphs;  // (VLM lane, first context, WG cap, frames)
-  std::map<std::pair<int, std::vector<int>>, hipGraphExec_t> den_graphs;  // (lane, contexts of the items)
+  // (lane, or -1 for lane 0 in the serial mode, which reads ahead; contexts of the items)
+  std::map<std::pair<int, std::vector<int>>, hipGraphExec_t> den_graphs;
   std::mutex mu;
 
   // per-tag kernel timer: every launch whose tag matches is bracketed by
@@ -658,6 +659,9 @@ struct Run {
   const Scratch* scr;
   ActWs* aw = nullptr;  // action phase only
   VlmWs* vw = nullptr;  // VLM phase only
+  // the phases run one after another on one stream, so a one-frame action
+  // launch has the CUs it does not fill to itself: it may read ahead
+  bool alone = false;
 };
 
 // Kernel timer: a launch whose tag matches gets a pair of events that its
@@ -703,10 +707,29 @@ static GemmDesc gemm_desc(vla_model* m, const void* A, int lda, int W, int M, in
   return g;
 }
 
+// The tensors (fragment-ordered weights, -1: none) that `wgs` extra workgroups
+// of a one-frame action-phase launch read ahead. Only where the launch has
+// the chip to itself: beside a prefill or other action lanes the CUs and L2s
+// are in use.
+static Prefetch ahead(const Run& r, int wgs, int t0, int t1 = -1) {
+  Prefetch p;
+  if (!r.alone) return p;
+  const vla_model* m = r.m;
+  p.wgs = wgs;
+  const int t[2] = {t0, t1};
+  for (int i = 0; i < 2; ++i)
+    if (t[i] >= 0 && m->T[t[i]].bytes() < (1u << 30)) {
+      p.p[i] = m->tptr(t[i]);
+      p.bytes[i] = (uint32_t)m->T[t[i]].bytes();
+    }
+  return p;
+}
+
 static int gemm(const Run& r, const char* tag, const void* A, int lda, int W, int M, int N, int K,
-                const Epi& e, int koff = 0, Frames fr = Frames()) {
+                const Epi& e, int koff = 0, Frames fr = Frames(), Prefetch pf = Prefetch()) {
   vla_model* m = r.m;
-  const GemmDesc g = gemm_desc(m, A, lda, W, M, N, K, e, koff, fr);
+  GemmDesc g = gemm_desc(m, A, lda, W, M, N, K, e, koff, fr);
+  g.pf = pf;
   LaunchCaps caps = r.caps;
   VLA_TRY(timer_events(r, tag, &caps));
   hipError_t err = launch_gemm(g, *r.scr, caps, r.st);
@@ -820,7 +843,7 @@ static int gemm_part(const Run& r, const char* tag, const void* A, int lda, int 
 // sums of squares for the next GEMM: an RMSNorm folded across two launches
 // (see Epi::rowss). One frame.
 static int gemm_resid(const Run& r, const char* tag, const void* A, int lda, int W, int M, int N, int K, float* x,
-                      const float* gate, int g = -1, void* h = nullptr) {
+                      const float* gate, int g = -1, void* h = nullptr, Prefetch pf = Prefetch()) {
   Epi e;
   e.kind = EPI_RESID;
   e.resid = x;
@@ -831,7 +854,7 @@ static int gemm_resid(const Run& r, const char* tag, const void* A, int lda, int
     e.norm_out = h;
     e.rowss = r.aw->rowss;
   }
-  return gemm(r, tag, A, lda, W, M, N, K, e);
+  return gemm(r, tag, A, lda, W, M, N, K, e, 0, Frames(), pf);
 }
 
 // the consumer side: scale each row of the product by the folded norm's 1/rms
@@ -845,7 +868,7 @@ static void fold_consumer(const Run& r, Epi& e, int d) {
 // the operand is loaded where the kernel can (slim_ln_fits), else it is a
 // launch of its own into h (row-block operand layout). One frame.
 static int gemm_ln(const Run& r, const char* tag, const LnOperand& ln, void* h, int W, int M, int N, int K,
-                   const Epi& e) {
+                   const Epi& e, Prefetch pf = Prefetch()) {
   vla_model* m = r.m;
   if (!slim_ln_fits(m->dt, M, N, K, e.kind)) {
     NormDesc n;
@@ -859,10 +882,11 @@ static int gemm_ln(const Run& r, const char* tag, const LnOperand& ln, void* h, 
     n.out = h;
     n.afrag = 1;
     VLA_TRY(run_norm(r, n));
-    return gemm(r, tag, h, K, W, M, N, K, e);
+    return gemm(r, tag, h, K, W, M, N, K, e, 0, Frames(), pf);
   }
   GemmDesc g = gemm_desc(m, nullptr, K, W, M, N, K, e);
   g.ln = ln;
+  g.pf = pf;
   LaunchCaps caps = r.caps;
   VLA_TRY(timer_events(r, tag, &caps));
   hipError_t err = launch_gemm(g, *r.scr, caps, r.st);
@@ -880,6 +904,9 @@ static Epi epi_kind(int kind, void* out = nullptr, int ldo = 0, const float* bia
   e.bias = bias;
   return e;
 }
+
+// workgroups that read weights ahead, per launch of a one-frame layer
+constexpr int PF_ATTN = 192, PF_O = 128, PF_GU = 64, PF_KV = 64, PF_MLP = 64;
 
 // One Gemma-style decoder layer: RMSNorm (after adding the pending residual
 // partials) -> QKV (+RoPE, K/V stored) -> attention over [past; own] -> O ->
@@ -907,7 +934,7 @@ static int decoder_layer(const Run& r, bool lm, const DecLayer& L, float* x, int
                          void* h, void* q, void* kout, void* vout, int pos0, const void* const* kpast,
                          const void* const* vpast, int npast, void* att, void* mlpbuf, bool kv_only,
                          int* pend, int frames = 1, size_t kstride = 0, size_t vstride = 0,
-                         const vla_model::WideLayer* wl = nullptr, int next_g = -1) {
+                         const vla_model::WideLayer* wl = nullptr, int next_g = -1, int next_w = -1) {
   vla_model* m = r.m;
   const vla_config& c = m->c;
   const Dims& d = m->d;
@@ -950,10 +977,19 @@ static int decoder_layer(const Run& r, bool lm, const DecLayer& L, float* x, int
   }
   if (folded_in) fold_consumer(r, e, dim);
   const char* tq = lm ? "lm.qkv" : "ex.qkv";
+  Prefetch pkv;  // the prefix's K and V of this layer, for the attention
+  if (fold && r.alone) {
+    pkv.wgs = PF_KV;
+    pkv.whole = 1;
+    pkv.p[0] = kpast[0];
+    pkv.p[1] = vpast[0];
+    pkv.bytes[0] = (uint32_t)(ctx_layer_k(m) * m->esz);
+    pkv.bytes[1] = (uint32_t)(ctx_layer_v(m) * m->esz);
+  }
   if (wide)
     VLA_TRY(gemm_rm(r, tq, h, dim, wl->qkv, dim, gm, d.qkv_n, dim, e, frm));
   else
-    VLA_TRY(gemm(r, tq, h, dim, L.qkv, gm, d.qkv_n, dim, e, 0, frm));
+    VLA_TRY(gemm(r, tq, h, dim, L.qkv, gm, d.qkv_n, dim, e, 0, frm, pkv));
   if (kv_only) return VLA_OK;
   AttnKvDesc a{};
   a.dtype = m->dt;
@@ -997,11 +1033,13 @@ static int decoder_layer(const Run& r, bool lm, const DecLayer& L, float* x, int
     a.v1_blk = aw->blk_v;
     a.out_blk = (size_t)rows * d.qd;
   }
+  if (fold) a.pf = ahead(r, PF_ATTN, L.o, L.gu);
   VLA_TRY(attn_kv(r, lm ? "lm.attn" : "ex.attn", a));
   int so = 0;
   const char* to = lm ? "lm.o" : "ex.o";
   if (fold) {
-    VLA_TRY(gemm_resid(r, to, att, d.qd, L.o, gm, dim, d.qd, x, nullptr, L.rms2, h));
+    VLA_TRY(gemm_resid(r, to, att, d.qd, L.o, gm, dim, d.qd, x, nullptr, L.rms2, h,
+                       ahead(r, PF_O, L.down)));
   } else {
     if (wide)
       VLA_TRY(gemm_part_rm(r, to, att, d.qd, wl->o, d.qd, gm, dim, d.qd, &so, frm));
@@ -1016,7 +1054,7 @@ static int decoder_layer(const Run& r, bool lm, const DecLayer& L, float* x, int
   if (wide)
     VLA_TRY(gemm_rm(r, tg, h, dim, wl->gu, dim, gm, 2 * mlp, dim, eg, frm));
   else
-    VLA_TRY(gemm(r, tg, h, dim, L.gu, gm, 2 * mlp, dim, eg, 0, frm));
+    VLA_TRY(gemm(r, tg, h, dim, L.gu, gm, 2 * mlp, dim, eg, 0, frm, fold ? ahead(r, PF_GU, next_w) : Prefetch()));
   const char* td = lm ? "lm.down" : "ex.down";
   if (fold) {
     VLA_TRY(gemm_resid(r, td, mlpbuf, mlp, L.down, gm, dim, mlp, x, nullptr, next_g, h));
@@ -1236,12 +1274,15 @@ static int run_denoise_dit(const Run& r, const vla_ctx* ctx, const float* noise,
         a.v0 = w.vown;
         a.S0 = H;
       }
+      a.pf = ahead(r, PF_ATTN, D.o, D.fc1);
       VLA_TRY(attn_kv(r, "ex.attn", a));
       VLA_TRY(gemm_resid(r, "ex.o", w.att, de, D.o, H, de, de, w.u, ad + 2 * de));
       Epi e1 = epi_kind(EPI_GELU, w.mlp, c.ex_mlp);
       e1.afrag = 1;
-      VLA_TRY(gemm_ln(r, "ex.fc1", adanorm(ad + 3 * de, ad + 4 * de), w.h, D.fc1, H, c.ex_mlp, de, e1));
-      VLA_TRY(gemm_resid(r, "ex.fc2", w.mlp, c.ex_mlp, D.fc2, H, de, c.ex_mlp, w.u, ad + 5 * de));
+      VLA_TRY(gemm_ln(r, "ex.fc1", adanorm(ad + 3 * de, ad + 4 * de), w.h, D.fc1, H, c.ex_mlp, de, e1,
+                      ahead(r, PF_MLP, D.fc2)));
+      VLA_TRY(gemm_resid(r, "ex.fc2", w.mlp, c.ex_mlp, D.fc2, H, de, c.ex_mlp, w.u, ad + 5 * de, -1, nullptr,
+                         ahead(r, PF_MLP, l + 1 < L ? (l % 2 ? m->dit[l + 1].q : m->dit[l + 1].qkv) : m->dit[0].q)));
     }
     const float* fa = m->fada + (size_t)k * 2 * de;
     Epi e;
@@ -1310,12 +1351,14 @@ static int run_denoise_cog(const Run& r, const vla_ctx* ctx, const float* noise,
       a.Sq = S;
       a.out = w.att;
       a.out_afrag = 1;
+      a.pf = ahead(r, PF_ATTN, L.o, L.fc1);
       VLA_TRY(attn_kv(r, "ex.attn", a));
-      VLA_TRY(gemm_resid(r, "ex.o", w.att, de, L.o, S, de, de, w.u, nullptr));
+      VLA_TRY(gemm_resid(r, "ex.o", w.att, de, L.o, S, de, de, w.u, nullptr, -1, nullptr, ahead(r, PF_O, L.fc2)));
       Epi e1 = epi_kind(EPI_GELU, w.mlp, c.ex_mlp);
       e1.afrag = 1;
       VLA_TRY(gemm_ln(r, "ex.fc1", ln(L.ln2_g, L.ln2_b), w.h, L.fc1, S, c.ex_mlp, de, e1));
-      VLA_TRY(gemm_resid(r, "ex.fc2", w.mlp, c.ex_mlp, L.fc2, S, de, c.ex_mlp, w.u, nullptr));
+      VLA_TRY(gemm_resid(r, "ex.fc2", w.mlp, c.ex_mlp, L.fc2, S, de, c.ex_mlp, w.u, nullptr, -1, nullptr,
+                         ahead(r, PF_O, m->cogl[(l + 1) % c.ex_layers].qkv)));
     }
     Epi e;
     e.kind = EPI_EULER;
@@ -1421,7 +1464,8 @@ static int run_denoise_n(const Run& r, const vla_ctx* const* ctxs, int frames, c
       }
       VLA_TRY(decoder_layer(r, false, m->ex[l], w.u, H, de, c.ex_mlp, w.h, w.q, w.kown, w.vown, d.prefix,
                             K, V, d.prefix, w.att, w.mlp, false, &pend, frames, 0, 0,
-                            fb ? &m->exw[l] : nullptr, l + 1 < c.ex_layers ? m->ex[l + 1].rms1 : m->fin_g));
+                            fb ? &m->exw[l] : nullptr, l + 1 < c.ex_layers ? m->ex[l + 1].rms1 : m->fin_g,
+                            l + 1 < c.ex_layers ? m->ex[l + 1].qkv : m->ex[0].qkv));
     }
     // (pend < 0: the last down projection left h = x * fin_g and its row sums)
     if (pend >= 0) VLA_TRY(norm(r, w.u, frames * H, de, pend, nullptr, m->fin_g, -1, true, w.h, true, blk, w.blk_de));
@@ -2073,8 +2117,10 @@ static int pipeline_impl(vla_model* m, const vla_frame* frames, const float* noi
   auto actx = [&](int i) { return (i / k) % nctx; };      // context of item i
   HIP_TRY(hipDeviceSynchronize());
 
+  const bool alone = s.mode == VLA_MODE_SERIAL;
   auto den_key = [&](int li, int a0, int na) {
     std::vector<int> cs;
+    if (alone) li = -1;
     for (int f = 0; f < na; ++f) cs.push_back(actx(a0 + f));
     return std::make_pair(li, cs);
   };
@@ -2100,6 +2146,7 @@ static int pipeline_impl(vla_model* m, const vla_frame* frames, const float* noi
       if (m->den_graphs.count(key)) continue;
       ActWs* aw = m->aws[li].get();
       Run ra{m, st.a[li], acaps, &aw->scr, aw};
+      ra.alone = alone;
       const vla_ctx* cs[MAX_ACT_BATCH] = {};
       for (int f = 0; f < na; ++f) cs[f] = m->pctx[actx(a0 + f)];
       hipGraphExec_t ge = nullptr;
@@ -2158,6 +2205,7 @@ static int pipeline_impl(vla_model* m, const vla_frame* frames, const float* noi
         HIP_TRY(launch_copy(actions + a0 * chunk, aw->xg, na * chunk * 4, sa));
       } else {
         Run ra{m, sa, acaps, &aw->scr, aw};
+        ra.alone = alone;
         const vla_ctx* cs[MAX_ACT_BATCH] = {};
         for (int f = 0; f < na; ++f) cs[f] = m->pctx[actx(a0 + f)];
         VLA_TRY(run_denoise_n(ra, cs, na, noise + a0 * chunk, actions + a0 * chunk));
@@ -2385,6 +2433,7 @@ int vla_action_denoise(vla_model* m, const vla_ctx* ctx, const float* noise, flo
     hipError_t e = solo_begin(m, 1, (hipStream_t)stream, &cap);
     if (e != hipSuccess) return fail(VLA_EHIP, std::string("ordering standalone denoises: ") + hipGetErrorString(e));
     Run r{m, (hipStream_t)stream, LaunchCaps{}, &m->aws[0]->scr, m->aws[0].get()};
+    r.alone = true;
     const int rc = run_denoise(r, ctx, noise, actions);
     e = solo_end(m, 1, (hipStream_t)stream, cap);
     if (rc == VLA_OK && e != hipSuccess) return fail(VLA_EHIP, std::string("ordering standalone denoises: ") + hipGetErrorString(e));
