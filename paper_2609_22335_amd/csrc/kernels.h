@@ -309,6 +309,10 @@ struct AttnKvDesc {
   unsigned* cnt = nullptr;
   int cnt_n = 0;
   Prefetch pf;  // one frame
+  // The launch's sums need not equal those of a launch of more frames (a
+  // one-frame action phase): few query tiles may be split along the head dim
+  // in a way that changes the order of the key sums.
+  bool solo = false;
 };
 hipError_t launch_attention_kv(const AttnKvDesc& d, const LaunchCaps& caps, hipStream_t st);
 // Floats of partials (and, in *counters, the counters) a launch of these

@@ -1193,164 +1193,6 @@ __device__ __forceinline__ void prefetch_wg(const Prefetch& pf, int i) {
   }
 }
 
-// ---------------------------------------------------------------------------
-// Skinny GEMM for M <= 64 (the action expert's rows): C[M, N] = A[M, K] W^T
-// with W stored in MFMA fragment order (see frag_index): the 16 x SW fragment
-// of n-block nb and K-slab ks is 1 KB contiguous, lane l holding W[16 nb +
-// l % 16][SW ks + VEC (l / 16) ...], and A in the row-block operand layout
-// (afrag_index), so both operands load as contiguous 1 KB chunks (lda is
-// unused). A workgroup owns 32 columns (two
-// n-blocks, so the paired epilogues stay inside it) and a K-range of
-// 4 * SPW slabs; each wave takes SPW consecutive slabs and issues every load
-// of its range at once (one memory round trip), then the four waves' partial
-// sums are added in wave order through LDS. K-ranges beyond one workgroup
-// are split, with the split-K reduce kernel applying the epilogue.
-// ---------------------------------------------------------------------------
-
-// Frames (a batched action phase): `frames` row blocks of M rows, block f of
-// A at A + f a_blk elements. Every (column pair, K-range) tile is computed
-// once per frame by its own workgroup, exactly as in a one-frame call; the
-// frames of a tile are consecutive tile indices, and with the XCD-aware
-// order below they run on one XCD at the same time, so the weights come
-// from HBM once and from that XCD's L2 for the other frame.
-// One instantiation per epilogue kind (KIND): the action loop launches these
-// kernels back to back, and each carries only its own epilogue's code, which
-// keeps the code the loop runs small enough to stay in the instruction cache.
-template <typename T, int SPW, int KIND>
-__global__ __launch_bounds__(256) void k_skinny(const T* __restrict__ A, size_t a_blk, int frames,
-                                                const T* __restrict__ Wf, int KS, int ks0, int M,
-                                                int N, int K, int splits, Epi e,
-                                                float* __restrict__ part, int G, Prefetch pf) {
-  VLA_WAVE_BEGIN(KK_SKINNY);
-  if ((int)blockIdx.x >= G) {
-    prefetch_wg(pf, (int)blockIdx.x - G);
-    VLA_WAVE_END(KK_SKINNY);
-    return;
-  }
-  constexpr int VEC = 16 / sizeof(T);
-  constexpr int SW = 4 * VEC;
-  __shared__ float red[4][8][4][64];  // [wave][n-block * 4 + m-tile][r][lane]
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int npairs = (N + 31) / 32;
-  const int nslab = (K + SW - 1) / SW;
-  const int total = npairs * splits * frames;
-  const int Mt = M * frames;  // rows of all frames
-  const T dummy = T();
-  const Rsrc rw = rsrc(Wf, (size_t)npairs * 2 * KS * 64 * VEC * sizeof(T));
-  // row-block operand layout, one block per frame
-  const Rsrc ra = rsrc(A, ((size_t)(frames - 1) * a_blk + (size_t)nslab * 4 * 64 * VEC) * sizeof(T));
-  const int first = G % 8 == 0 ? (int)(blockIdx.x % 8) * (G / 8) + (int)(blockIdx.x / 8) : (int)blockIdx.x;
-  // Folded RMSNorm (see Epi::rowss): thread t holds the partial
-  // sums of squares of row t / 4 for the blocks congruent to t % 4 (mod 4),
-  // requested before the first tile's loads (waiting for those covers them)
-  // and turned into the rows' scales at the first epilogue.
-  __shared__ float sPart[64][4];
-  __shared__ float sInv[64];
-  constexpr int SSQ = 16;  // column blocks per thread: at most 64 blocks
-  const bool rowscale = e.rowss != nullptr;
-  const int srow = tid >> 2, squ = tid & 3;
-  float ssq[SSQ];
-  if (rowscale) {
-    const Rsrc rs = rsrc(e.rowss, (size_t)e.rowss_n * M * 4);
-#pragma unroll
-    for (int k = 0; k < SSQ; ++k) {
-      const int p = squ + 4 * k;
-      ssq[k] = bld1(rs, p < e.rowss_n && srow < M ? (uint32_t)(((size_t)p * M + srow) * 4) : OOB);
-    }
-  }
-  bool inv_ready = false;
-  for (int w = first; w < total; w += G) {
-    const int f = w % frames, wt = w / frames;
-    const int s = wt % splits, np = wt / splits;
-    const int sb = (s * 4 + wave) * SPW;
-    const uint32_t aoff = (uint32_t)((size_t)f * a_blk * sizeof(T));  // frame f's block
-    uint4 bf[SPW][2], af[SPW][4];
-#pragma unroll
-    for (int q = 0; q < SPW; ++q) {
-      const int ks = sb + q;
-      const bool ok = ks < nslab;
-#pragma unroll
-      for (int nb = 0; nb < 2; ++nb)
-        bf[q][nb] = bld16(rw, ok ? (uint32_t)((((size_t)(2 * np + nb) * KS + ks0 + ks) * 64 + lane) * VEC * sizeof(T))
-                                 : OOB);
-      const int k = ks * SW + (lane >> 4) * VEC;
-#pragma unroll
-      for (int mt = 0; mt < 4; ++mt) {
-        const int row = mt * 16 + (lane & 15);
-        const bool oka = ok && row < M && k < K;
-        af[q][mt] = bld16s(ra, oka ? (uint32_t)((((size_t)ks * 4 + mt) * 64 + lane) * VEC * sizeof(T)) : OOB, aoff);
-      }
-    }
-    f32x4 acc[2][4];
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-      for (int mt = 0; mt < 4; ++mt) acc[nb][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int q = 0; q < SPW; ++q)
-#pragma unroll
-      for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt) acc[nb][mt] = mfma_step(af[q][mt], bf[q][nb], acc[nb][mt], dummy);
-
-    __syncthreads();  // red is free (previous tile's epilogue done)
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-      for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) red[wave][nb * 4 + mt][r][lane] = acc[nb][mt][r];
-    __syncthreads();
-    // wave w finishes m-tile w: sum the four waves in order, then the epilogue
-    const int mt = wave;
-    const int n = np * 32 + (lane & 15);
-    int mg[4], nn[4];
-    float v0[4], v1[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      v0[r] = ((red[0][mt][r][lane] + red[1][mt][r][lane]) + red[2][mt][r][lane]) + red[3][mt][r][lane];
-      v1[r] = ((red[0][4 + mt][r][lane] + red[1][4 + mt][r][lane]) + red[2][4 + mt][r][lane]) +
-              red[3][4 + mt][r][lane];
-      const int m = mt * 16 + (lane >> 4) * 4 + r;
-      mg[r] = m < M ? f * M + m : Mt;  // row over all frames (Mt: skipped)
-      nn[r] = n;
-    }
-    if (rowscale) {
-      if (!inv_ready) {
-        float t = 0.f;
-#pragma unroll
-        for (int k = 0; k < SSQ; ++k) t += ssq[k];  // blocks in increasing order (absent ones read 0)
-        sPart[srow][squ] = t;
-        __syncthreads();
-        if (squ == 0)
-          sInv[srow] = 1.f / sqrtf((((sPart[srow][0] + sPart[srow][1]) + sPart[srow][2]) + sPart[srow][3]) /
-                                       e.rowss_d + 1e-6f);
-        __syncthreads();
-        inv_ready = true;
-      }
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int m = mt * 16 + (lane >> 4) * 4 + r;
-        const float sc = sInv[m];
-        v0[r] *= sc;
-        v1[r] *= sc;
-      }
-    }
-    if (splits == 1) {
-      epi_pairs<T, 4, KIND>(e, Mt, N, mg, nn, v0, v1);
-    } else {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        if (mg[r] >= Mt) continue;
-        float* P = part + (size_t)s * Mt * N + (size_t)mg[r] * N;
-        if (n < N) P[n] = v0[r];
-        if (n + 16 < N) P[n + 16] = v1[r];
-      }
-    }
-  }
-  VLA_WAVE_END(KK_SKINNY);
-}
-
 // Row-major copy of a fragment-ordered weight: one thread per 16-byte piece
 // (VEC consecutive k of one row n, which the fragment order keeps together).
 template <typename T>
@@ -1420,67 +1262,37 @@ static int prefetch_wgs(const Prefetch& p, int frames, const LaunchCaps& caps) {
   return caps.max_wgs > 0 || frames > 1 || p.wgs <= 0 || p.wgs % 8 || (!p.p[0] && !p.p[1]) ? 0 : p.wgs;
 }
 
-constexpr int SKINNY_SPW = 8;
-static int skinny_splits(const GemmDesc& g) {
-  const int per_wg = 4 * SKINNY_SPW * frag_slab(g.dtype);
-  return std::max(1, (g.K + per_wg - 1) / per_wg);
-}
-
-template <typename T, int SPW, int KIND>
-static hipError_t run_skinny_t(const GemmDesc& g, int splits, const Scratch& s,
-                               const LaunchCaps& caps, hipStream_t st) {
-  int grid = ((g.N + 31) / 32) * splits * g.frames;
-  if (caps.max_wgs > 0) grid = std::min(grid, caps.max_wgs);
-  const int pf = prefetch_wgs(g.pf, g.frames, caps);
-  hipExtLaunchKernelGGL((k_skinny<T, SPW, KIND>), dim3(grid + pf), dim3(256), 0, st, caps.ev_start,
-                        caps.ev_stop, 0, (const T*)g.A, g.a_blk, g.frames, (const T*)g.W, g.frag_ks,
-                        g.frag_ks0, g.M, g.N, g.K, splits, g.epi, s.ptr, grid, g.pf);
-  if (splits > 1) {
-    const int Mt = g.M * g.frames;
-    const long long total = (long long)Mt * ((g.N + 31) / 32) * 16;
-    int rgrid = (int)std::min<long long>((total + 255) / 256, 4096);
-    if (caps.max_wgs > 0) rgrid = std::min(rgrid, caps.max_wgs);
-    k_splitk_reduce<T><<<rgrid, 256, 0, st>>>(s.ptr, splits, Mt, g.N, g.epi);
-  }
-  return hipGetLastError();
-}
-
-template <typename T>
-static hipError_t run_skinny_kind(const GemmDesc& g, int splits, const Scratch& s, const LaunchCaps& caps,
-                                  hipStream_t st) {
-  switch (g.epi.kind) {
-    case EPI_F32: return run_skinny_t<T, SKINNY_SPW, EPI_F32>(g, splits, s, caps, st);
-    case EPI_T: return run_skinny_t<T, SKINNY_SPW, EPI_T>(g, splits, s, caps, st);
-    case EPI_GELU: return run_skinny_t<T, SKINNY_SPW, EPI_GELU>(g, splits, s, caps, st);
-    case EPI_SWISH: return run_skinny_t<T, SKINNY_SPW, EPI_SWISH>(g, splits, s, caps, st);
-    case EPI_GEGLU: return run_skinny_t<T, SKINNY_SPW, EPI_GEGLU>(g, splits, s, caps, st);
-    case EPI_QKV_ROPE: return run_skinny_t<T, SKINNY_SPW, EPI_QKV_ROPE>(g, splits, s, caps, st);
-    case EPI_QKV_PLAIN: return run_skinny_t<T, SKINNY_SPW, EPI_QKV_PLAIN>(g, splits, s, caps, st);
-    default: return hipErrorInvalidValue;
-  }
-}
-
 // ---------------------------------------------------------------------------
-// Slim GEMM: the skinny GEMM in 16-row tiles. A workgroup of NW waves owns
-// 16 rows x 16 NB columns of the result and the whole of K: wave w takes the
-// w-th part of the K-slabs with all its loads in flight at once, the waves'
-// sums are added in wave order through LDS, and 256 threads run the epilogue,
-// whose own operands were requested with the tile's. No split leaves the
-// workgroup, so a residual update needs neither partials nor a counter.
+// Slim GEMM for M <= 64 (the action head's rows): C[M, N] = A[M, K] W^T with
+// W stored in MFMA fragment order (see frag_index): the 16 x SW fragment of
+// n-block nb and K-slab ks is 1 KB contiguous, lane l holding W[16 nb + l % 16]
+// [SW ks + VEC (l / 16) ...], and A in the row-block operand layout
+// (afrag_index), so both operands load as contiguous 1 KB chunks (lda is
+// unused). Frames of a batched action phase: `frames` row blocks of M rows,
+// block f of A at A + f a_blk elements, each computed as in a one-frame call.
+//
+// A workgroup of NW waves owns 16 RT rows x 16 NB columns of the result and
+// the whole of K: wave w takes the w-th part of the K-slabs with all its
+// loads in flight at once, the waves' sums are added in wave order through
+// LDS, and the epilogue's own operands were requested with the tile's. No
+// split leaves the workgroup, so a residual update needs neither partials nor
+// a counter, and no launch is followed by a reduction.
 //
 // What bounds these launches is latency (a launch with nothing to do takes
 // 1.5 us in a graph, one that only streams 16.8 MB 4.2 us), then the bytes a
-// CU draws from L2: the 64-row tile of k_skinny reads all of A into each of
-// its few workgroups, this one a quarter of A (50 rows: 4 row tiles) and the
-// weights 4 times from L2 (the row tiles of a column block are neighbours on
-// one XCD, so HBM serves them once).
+// CU draws from L2: about 50 per clock. In 16-row tiles a workgroup reads a
+// quarter of A (50 rows: 4 row tiles) and the weights come 4 times from L2
+// (the row tiles of a column block are neighbours on one XCD, so HBM serves
+// them once).
+// One instantiation per epilogue kind: the action loop launches these back to
+// back, and the code it runs should stay in the instruction cache.
 // ---------------------------------------------------------------------------
 
 constexpr int SLIM_NW = 8, SLIM_LN_NW = 16;
 
 // LNR > 0: the operand is the LayerNorm of ln.x over K <= 256 LNR columns
 // (NW = 16).
-template <typename T, int NW, int SPW, int NB, int KIND, int LNR>
+template <typename T, int NW, int SPW, int NB, int RT, int KIND, int LNR>
 __global__ __launch_bounds__(64 * NW) void k_slim(const T* __restrict__ A, size_t a_blk, LnOperand ln, int frames,
                                                   const T* __restrict__ Wf, int KS, int ks0, int M, int N, int K,
                                                   Epi e, int G, Prefetch pf) {
@@ -1495,13 +1307,16 @@ __global__ __launch_bounds__(64 * NW) void k_slim(const T* __restrict__ A, size_
   constexpr int SW = 4 * VEC;
   constexpr bool PAIRED = KIND == EPI_GEGLU || KIND == EPI_QKV_ROPE;
   constexpr bool LN = LNR > 0;
+  constexpr int EG = NW / 4;                // row tiles the epilogue takes at once (256 threads each)
+  constexpr int EI = (RT + EG - 1) / EG;    // and in how many turns
   static_assert(!PAIRED || NB == 2, "paired epilogues need 32 columns");
-  static_assert(!LN || (NW == 16 && 256 * LNR <= NW * SPW * SW), "a wave per row, all of K in one request");
-  __shared__ float red[NW][NB][4][64];  // [wave][n-block][r][lane]
-  __shared__ float sInv[16];
+  static_assert(!LN || (NW == 16 && RT == 1 && 256 * LNR <= NW * SPW * SW), "a wave per row, all of K in one request");
+  static_assert(LN || NW == 8, "two rows of a tile per wave in the folded norm");
+  __shared__ float red[NW][RT][NB][4][64];  // [wave][row tile][n-block][r][lane]
+  __shared__ float sInv[RT][16];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g4 = lane >> 4;
-  const int mt = (M + 15) / 16, ncb = (N + 16 * NB - 1) / (16 * NB);
+  const int mt = (M + 16 * RT - 1) / (16 * RT), ncb = (N + 16 * NB - 1) / (16 * NB);
   const int nslab = (K + SW - 1) / SW, pw = (nslab + NW - 1) / NW;
   const int per_cb = mt * frames, total = ncb * per_cb;
   const T dummy = T();
@@ -1511,25 +1326,29 @@ __global__ __launch_bounds__(64 * NW) void k_slim(const T* __restrict__ A, size_
   const int first = G % 8 == 0 ? (int)(blockIdx.x % 8) * (G / 8) + (int)(blockIdx.x / 8) : (int)blockIdx.x;
   for (int w = first; w < total; w += G) {
     const int cb = w / per_cb, q = w - cb * per_cb;
-    const int f = q / mt, mi = q - f * mt;
-    const int arow = mi * 16 + (lane & 15);  // this lane's A row
-    // Folded RMSNorm: rows 2 wave, 2 wave + 1 of the tile (half a wave each),
-    // lane's blocks l, l + 32; requested before the operands, so waiting for
-    // them does not wait for those
-    float ssq[2] = {0.f, 0.f};
-    if (rowscale && NW == 8) {
+    const int f = q / mt, mi = (q - f * mt) * RT;  // first 16-row tile
+    // Folded RMSNorm: rows 2 wave, 2 wave + 1 of each row tile (half a wave
+    // each), lane's blocks l, l + 32; requested before the operands, so
+    // waiting for them does not wait for those
+    float ssq[RT][2];
+    if (rowscale) {
       const Rsrc rs = rsrc(e.rowss, (size_t)e.rowss_n * M * 4);
-      const int row = mi * 16 + 2 * wave + (lane >> 5);
 #pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        const int p = (lane & 31) + 32 * k;
-        ssq[k] = bld1(rs, p < e.rowss_n && row < M ? (uint32_t)(((size_t)p * M + row) * 4) : OOB);
+      for (int t = 0; t < RT; ++t) {
+        const int row = (mi + t) * 16 + 2 * wave + (lane >> 5);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          const int p = (lane & 31) + 32 * k;
+          ssq[t][k] = bld1(rs, p < e.rowss_n && row < M ? (uint32_t)(((size_t)p * M + row) * 4) : OOB);
+        }
       }
     }
     const int s0 = wave * pw, s1 = min(nslab, s0 + pw);
-    f32x4 acc[NB];
+    f32x4 acc[RT][NB];
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) acc[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) acc[t][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
     // The wave's part of a column block's weights (and, below, of a row tile's
     // operand) is a buffer of its own that ends at slab s1, so slabs past the
     // end read as zero and no load carries a condition.
@@ -1553,34 +1372,42 @@ __global__ __launch_bounds__(64 * NW) void k_slim(const T* __restrict__ A, size_
       }
     };
 
-    // the epilogue's operands: thread tid < 256 finishes row erow, columns
-    // n (and n + 16)
-    const int eloc = (lane >> 4) * 4 + (wave & 3), erow = mi * 16 + eloc;
+    // the epilogue's operands: in turn i, 256 threads finish row tile
+    // tid / 256 + EG i, a thread its row erow(i) and columns n (and n + 16)
     const int n = cb * 16 * NB + (lane & 15);
-    const bool eok = tid < 256 && erow < M;
-    const int m = f * M + erow;  // row over all frames
-    float b0 = 0.f, b1 = 0.f, o0 = 0.f, o1 = 0.f, g0 = 0.f, g1 = 0.f, c0 = 1.f, c1 = 1.f;
+    const int eloc = (lane >> 4) * 4 + (wave & 3);
+    auto etile = [&](int i) { return (tid >> 8) + EG * i; };
+    auto erow = [&](int i) { return (mi + etile(i)) * 16 + eloc; };
+    auto eok = [&](int i) { return etile(i) < RT && erow(i) < M; };
+    float b0 = 0.f, b1 = 0.f, g0 = 0.f, g1 = 0.f, c0 = 1.f, c1 = 1.f;  // by column
+    float o0[EI], o1[EI];                                              // by row and column
+#pragma unroll
+    for (int i = 0; i < EI; ++i) o0[i] = o1[i] = 0.f;
     auto load_epi = [&]() {
-      if (tid >= 256) return;
-      auto two = [&](Rsrc r, size_t base, float& x0, float& x1) {
-        x0 = bld1(r, eok && n < N ? (uint32_t)((base + n) * 4) : OOB);
-        if (NB == 2) x1 = bld1(r, eok && n + 16 < N ? (uint32_t)((base + n + 16) * 4) : OOB);
+      auto two = [&](Rsrc r, bool ok, size_t base, float& x0, float& x1) {
+        x0 = bld1(r, ok && n < N ? (uint32_t)((base + n) * 4) : OOB);
+        if (NB == 2) x1 = bld1(r, ok && n + 16 < N ? (uint32_t)((base + n + 16) * 4) : OOB);
       };
       if (KIND != EPI_GEGLU && KIND != EPI_QKV_ROPE && KIND != EPI_QKV_PLAIN && e.bias)
-        two(rsrc(e.bias, (size_t)N * 4), 0, b0, b1);
-      if (KIND == EPI_F32 && e.rowadd)
-        two(rsrc(e.rowadd, span(e.rowadd_period, e.ldra, N, 4)), (size_t)(m % e.rowadd_period) * e.ldra, o0, o1);
-      if (KIND == EPI_EULER) two(rsrc(e.x, span(M * frames, e.ldx, N, 4)), (size_t)m * e.ldx, o0, o1);
+        two(rsrc(e.bias, (size_t)N * 4), true, 0, b0, b1);
       if (KIND == EPI_RESID) {
-        two(rsrc(e.resid, span(M * frames, e.ldr, N, 4)), (size_t)m * e.ldr, o0, o1);
-        if (e.norm_g) two(rsrc(e.norm_g, (size_t)N * 4), 0, g0, g1);
-        if (e.colscale) two(rsrc(e.colscale, (size_t)N * 4), 0, c0, c1);
+        if (e.norm_g) two(rsrc(e.norm_g, (size_t)N * 4), true, 0, g0, g1);
+        if (e.colscale) two(rsrc(e.colscale, (size_t)N * 4), true, 0, c0, c1);
       }
-      if (KIND == EPI_QKV_ROPE && eok && n + 16 < N && n < (e.nq + e.nkv) * e.hd) {
-        const int pp = n % e.hd;
-        const size_t t = (size_t)(e.pos0 + epi_key(e, m)) * (e.hd / 2) + 16 * (pp >> 5) + (pp & 15);
-        o0 = e.rope_cos[t];
-        o1 = e.rope_sin[t];
+#pragma unroll
+      for (int i = 0; i < EI; ++i) {
+        const bool ok = eok(i);
+        const int m = f * M + erow(i);
+        if (KIND == EPI_F32 && e.rowadd)
+          two(rsrc(e.rowadd, span(e.rowadd_period, e.ldra, N, 4)), ok, (size_t)(m % e.rowadd_period) * e.ldra, o0[i], o1[i]);
+        if (KIND == EPI_EULER) two(rsrc(e.x, span(M * frames, e.ldx, N, 4)), ok, (size_t)m * e.ldx, o0[i], o1[i]);
+        if (KIND == EPI_RESID) two(rsrc(e.resid, span(M * frames, e.ldr, N, 4)), ok, (size_t)m * e.ldr, o0[i], o1[i]);
+        if (KIND == EPI_QKV_ROPE && ok && n + 16 < N && n < (e.nq + e.nkv) * e.hd) {
+          const int pp = n % e.hd;
+          const size_t t = (size_t)(e.pos0 + epi_key(e, m)) * (e.hd / 2) + 16 * (pp >> 5) + (pp & 15);
+          o0[i] = e.rope_cos[t];
+          o1[i] = e.rope_sin[t];
+        }
       }
     };
 
@@ -1589,23 +1416,33 @@ __global__ __launch_bounds__(64 * NW) void k_slim(const T* __restrict__ A, size_
       // the statistics stay inside the wave, and the operand goes through LDS
       // into fragment order (16-byte chunk c = k / VEC of row i at LNP c + 16 i
       // bytes; the padded stride spreads the chunks of one row over the banks).
+      // Gain and shift are read once for the workgroup, through LDS.
       constexpr int R = LNR, LNP = 16 * 16 + 16;
       __shared__ __attribute__((aligned(16))) unsigned char sA[256 * R / VEC * LNP];
+      __shared__ __attribute__((aligned(16))) float sG[256 * R], sB[256 * R];
+      constexpr int GB = (256 * R + 64 * NW - 1) / (64 * NW);  // columns per thread
       const int xrow = mi * 16 + wave;
       const Rsrc rx = rsrc(ln.x + (size_t)xrow * ln.ldx, xrow < M ? (size_t)K * 4 : 0);
       const Rsrc rg = rsrc(ln.g, (size_t)K * 4), rb = rsrc(ln.b ? ln.b : ln.g, ln.b ? (size_t)K * 4 : 0);
-      f32x4 xv[R], gv[R], bv[R];
+      f32x4 xv[R];
+      float gv[GB], bv[GB];
       uint4 bf[SPW][NB];
 #pragma unroll
       for (int j = 0; j < R; ++j) xv[j] = bld4f(rx, (uint32_t)(lane * 16 + j * 1024));
 #pragma unroll
-      for (int j = 0; j < R; ++j) {
-        gv[j] = bld4f(rg, (uint32_t)(lane * 16 + j * 1024));
-        bv[j] = bld4f(rb, (uint32_t)(lane * 16 + j * 1024));
+      for (int j = 0; j < GB; ++j) {
+        gv[j] = bld1(rg, (uint32_t)(tid + j * 64 * NW) * 4);
+        bv[j] = bld1(rb, (uint32_t)(tid + j * 64 * NW) * 4);
       }
       load_w(s0, bf);
       load_epi();
       __builtin_amdgcn_sched_barrier(0);  // every load is out before the first wait
+#pragma unroll
+      for (int j = 0; j < GB; ++j)
+        if (tid + j * 64 * NW < 256 * R) {
+          sG[tid + j * 64 * NW] = ln.g_plus_one ? 1.f + gv[j] : gv[j];
+          sB[tid + j * 64 * NW] = bv[j];
+        }
       float p1 = 0.f, p2 = 0.f;
 #pragma unroll
       for (int j = 0; j < R; ++j) p1 += (xv[j][0] + xv[j][1]) + (xv[j][2] + xv[j][3]);
@@ -1620,13 +1457,13 @@ __global__ __launch_bounds__(64 * NW) void k_slim(const T* __restrict__ A, size_
         }
       }
       const float inv = 1.f / sqrtf(wave_sum_x16_x32(row16_sum(p2)) / K + 1e-6f);
+      __syncthreads();
 #pragma unroll
       for (int j = 0; j < R; ++j) {
         const int k = lane * 4 + j * 256;
-        f32x4 y;
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-          y[c] = k < K ? (xv[j][c] - mean) * inv * (ln.g_plus_one ? 1.f + gv[j][c] : gv[j][c]) + bv[j][c] : 0.f;
+        const f32x4 gk = *(const f32x4*)&sG[k], bk = *(const f32x4*)&sB[k];
+        f32x4 y = (xv[j] - mean) * inv * gk + bk;
+        if (k >= K) y = f32x4{0.f, 0.f, 0.f, 0.f};
         unsigned char* d = sA + (size_t)(k / VEC) * LNP + wave * 16 + (k % VEC) * sizeof(T);
         if constexpr (sizeof(T) == 2)
           *(uint2*)d = make_uint2(f2bf2(y[0], y[1]), f2bf2(y[2], y[3]));
@@ -1640,22 +1477,31 @@ __global__ __launch_bounds__(64 * NW) void k_slim(const T* __restrict__ A, size_
         const int c = min(4 * (s0 + u) + g4, 256 * R / VEC - 1);
         const uint4 af = *(const uint4*)(sA + (size_t)c * LNP + (lane & 15) * 16);
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) acc[nb] = mfma_step(af, bf[u][nb], acc[nb], dummy);
+        for (int nb = 0; nb < NB; ++nb) acc[0][nb] = mfma_step(af, bf[u][nb], acc[0][nb], dummy);
       }
     } else {
       const Rsrc ra = rsrc(A + (size_t)f * a_blk, (size_t)max(s1, 0) * 4 * CH);  // frame f's block
-      const uint32_t aoff = arow < M ? (uint32_t)(mi * CH + lane * 16) : OOB;
       const bool tail = K % SW != 0 && s1 == nslab;  // K ends inside this wave's last slab
-      for (int sb = s0; sb < max(s1, s0 + 1); sb += SPW) {
-        uint4 bf[SPW][NB], af[SPW];
-        load_w(sb, bf);
-        uint32_t ao = aoff + (uint32_t)sb * 4 * CH;
+      uint32_t aoff[RT];
 #pragma unroll
-        for (int u = 0; u < SPW; ++u) {
-          af[u] = bld16(ra, ao);
-          ao += 4 * CH;
-          asm("" : "+v"(ao));
-        }
+      for (int t = 0; t < RT; ++t) {
+        const int tile = mi + t;
+        aoff[t] = tile * 16 + (lane & 15) < M ? (uint32_t)(tile * CH + lane * 16) : OOB;
+      }
+      for (int sb = s0; sb < max(s1, s0 + 1); sb += SPW) {
+        uint4 bf[SPW][NB], af[SPW][RT];
+        load_w(sb, bf);
+        uint32_t ao[RT];
+#pragma unroll
+        for (int t = 0; t < RT; ++t) ao[t] = aoff[t] + (uint32_t)sb * 4 * CH;
+#pragma unroll
+        for (int u = 0; u < SPW; ++u)
+#pragma unroll
+          for (int t = 0; t < RT; ++t) {
+            af[u][t] = bld16(ra, ao[t]);
+            ao[t] += 4 * CH;
+            asm("" : "+v"(ao[t]));
+          }
         if (sb == s0) load_epi();
         __builtin_amdgcn_sched_barrier(0);  // every load is out before the first wait
         if (tail) {
@@ -1663,44 +1509,56 @@ __global__ __launch_bounds__(64 * NW) void k_slim(const T* __restrict__ A, size_
           asm("" : "+v"(kl));
 #pragma unroll
           for (int u = 0; u < SPW; ++u)
-            if (u * SW >= kl) af[u] = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+            for (int t = 0; t < RT; ++t)
+              if (u * SW >= kl) af[u][t] = make_uint4(0u, 0u, 0u, 0u);
         }
 #pragma unroll
         for (int u = 0; u < SPW; ++u)
 #pragma unroll
-          for (int nb = 0; nb < NB; ++nb) acc[nb] = mfma_step(af[u], bf[u][nb], acc[nb], dummy);
+          for (int t = 0; t < RT; ++t)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) acc[t][nb] = mfma_step(af[u][t], bf[u][nb], acc[t][nb], dummy);
       }
       if (rowscale) {
-        float t = ssq[0] + ssq[1];
-        t = row16_sum(t);
-        t += __shfl_xor(t, 16);
-        if ((lane & 31) == 0) sInv[2 * wave + (lane >> 5)] = 1.f / sqrtf(t / e.rowss_d + 1e-6f);
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+          float v = row16_sum(ssq[t][0] + ssq[t][1]);
+          v += __shfl_xor(v, 16);
+          if ((lane & 31) == 0) sInv[t][2 * wave + (lane >> 5)] = 1.f / sqrtf(v / e.rowss_d + 1e-6f);
+        }
       }
     }
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
+    for (int t = 0; t < RT; ++t)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) red[wave][nb][r][lane] = acc[nb][r];
+      for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) red[wave][t][nb][r][lane] = acc[t][nb][r];
     __syncthreads();
-    if (tid < 256) {
-      // lane (g, i) of wave r holds row 4 g + r, column i of the tile
-      const int r = wave & 3;
+#pragma unroll
+    for (int i = 0; i < EI; ++i) {
+      const int et = etile(i);
+      if (et >= RT) continue;  // (whole waves)
+      // lane (g, c) of the r-th of four waves holds row 4 g + r, column c of the tile
+      const int r = wave & 3, row = erow(i), m = f * M + row;  // m: row over all frames
+      const bool ok = row < M;
       float v0 = 0.f, v1 = 0.f;
 #pragma unroll
       for (int u = 0; u < NW; ++u) {
-        v0 += red[u][0][r][lane];
-        if (NB == 2) v1 += red[u][NB - 1][r][lane];
+        v0 += red[u][et][0][r][lane];
+        if (NB == 2) v1 += red[u][et][NB - 1][r][lane];
       }
       if (rowscale) {
-        const float sc = sInv[eloc];
+        const float sc = sInv[et][eloc];
         v0 *= sc;
         v1 *= sc;
       }
       v0 += b0;
       v1 += b1;
       if constexpr (KIND == EPI_RESID) {
-        float x0 = __builtin_fmaf(c0, v0, o0), x1 = __builtin_fmaf(c1, v1, o1);
-        const bool k0 = eok && n < N, k1 = NB == 2 && eok && n + 16 < N;
+        float x0 = __builtin_fmaf(c0, v0, o0[i]), x1 = __builtin_fmaf(c1, v1, o1[i]);
+        const bool k0 = ok && n < N, k1 = NB == 2 && ok && n + 16 < N;
         float* xr = e.resid + (size_t)m * e.ldr + n;
         if (k0) xr[0] = x0;
         if (k1) xr[16] = x1;
@@ -1710,7 +1568,7 @@ __global__ __launch_bounds__(64 * NW) void k_slim(const T* __restrict__ A, size_
           if (k1) TT<T>::st(h + afrag_index(DT, m, n + 16), x1 * g1);
           float ss = (k0 ? x0 * x0 : 0.f) + (k1 ? x1 * x1 : 0.f);
           ss = row16_sum(ss);
-          if ((lane & 15) == 0 && eok) e.rowss[(size_t)cb * M + erow] = ss;
+          if ((lane & 15) == 0 && ok) e.rowss[(size_t)cb * M + row] = ss;
         }
       } else if constexpr (KIND == EPI_EULER) {
         auto put = [&](int col, float v, float x) {
@@ -1718,30 +1576,30 @@ __global__ __launch_bounds__(64 * NW) void k_slim(const T* __restrict__ A, size_
           e.x[(size_t)m * e.ldx + col] = xn;
           TT<T>::st((T*)e.xop + out_at<T>(e, m, col, e.ldxop, e.blk_xop), xn);
         };
-        if (eok && n < N) put(n, v0, o0);
-        if (NB == 2 && eok && n + 16 < N) put(n + 16, v1, o1);
+        if (ok && n < N) put(n, v0, o0[i]);
+        if (NB == 2 && ok && n + 16 < N) put(n + 16, v1, o1[i]);
       } else if constexpr (KIND == EPI_F32) {
         float* o = (float*)e.out + (size_t)m * e.ldo + n;
-        if (eok && n < N) o[0] = v0 + o0;
-        if (NB == 2 && eok && n + 16 < N) o[16] = v1 + o1;
+        if (ok && n < N) o[0] = v0 + o0[i];
+        if (NB == 2 && ok && n + 16 < N) o[16] = v1 + o1[i];
       } else if constexpr (KIND == EPI_QKV_ROPE) {
-        if (eok && n + 16 < N) {
+        if (ok && n + 16 < N) {
           const int hd = e.hd, qcols = e.nq * hd, kcols = e.nkv * hd;
           if (n < qcols + kcols) {
             const bool isq = n < qcols;
             const int rn = isq ? n : n - qcols;
             const int head = rn / hd, pp = rn - head * hd;
-            const int i = 16 * (pp >> 5) + (pp & 15);
-            const float x0 = v0 * o0 - v1 * o1, x1 = v1 * o0 + v0 * o1;
+            const int ri = 16 * (pp >> 5) + (pp & 15);
+            const float x0 = v0 * o0[i] - v1 * o1[i], x1 = v1 * o0[i] + v0 * o1[i];
             if (isq) {
               T* dst = (T*)e.q + (size_t)m * e.ldq + head * hd;
-              TT<T>::st(dst + i, x0);
-              TT<T>::st(dst + i + hd / 2, x1);
+              TT<T>::st(dst + ri, x0);
+              TT<T>::st(dst + ri + hd / 2, x1);
             } else {
               const int key = epi_key(e, m);
               T* dst = (T*)e.k + epi_kblk(e, m, e.blk_k);
-              TT<T>::st(dst + kv_kidx(DT, e.kv_nb, hd, head, key, i), x0);
-              TT<T>::st(dst + kv_kidx(DT, e.kv_nb, hd, head, key, i + hd / 2), x1);
+              TT<T>::st(dst + kv_kidx(DT, e.kv_nb, hd, head, key, ri), x0);
+              TT<T>::st(dst + kv_kidx(DT, e.kv_nb, hd, head, key, ri + hd / 2), x1);
             }
           } else {
             epi_pair<T, KIND>(e, M * frames, N, m, n, v0, v1);  // V columns: stores only
@@ -1750,7 +1608,7 @@ __global__ __launch_bounds__(64 * NW) void k_slim(const T* __restrict__ A, size_
       } else {
         Epi s = e;  // the rest only store, with the bias added
         s.bias = nullptr;
-        if (eok) {
+        if (ok) {
           if constexpr (NB == 2)
             epi_pair<T, KIND>(s, M * frames, N, m, n, v0, v1);
           else if (n < N)
@@ -1772,19 +1630,17 @@ static int slim_nb(const Epi& e, int N) {
   return e.kind == EPI_F32 || e.kind == EPI_T || e.kind == EPI_SWISH || e.kind == EPI_EULER ? 1 : 2;
 }
 int slim_blocks(int N) { return N > 1024 ? (N + 31) / 32 : (N + 15) / 16; }
-static int slim_tiles(const GemmDesc& g) {
+static int slim_tiles(const GemmDesc& g, int rt) {
   const int cols = 16 * slim_nb(g.epi, g.N);
-  return (g.N + cols - 1) / cols * ((g.M + 15) / 16);
+  return (g.N + cols - 1) / cols * ((g.M + 16 * rt - 1) / (16 * rt));
 }
-// The slim kernel where its tiles of one frame come in at most two rounds on
-// the chip (the expert's gate/up, 256 column blocks of four row tiles, would
-// draw 384 KB per CU from L2 against k_skinny's 164 KB). The frame count does
-// not enter: a frame's sums are the same in every group. A residual update
-// has no other kernel.
+// Row tiles per workgroup: one where the tiles of one frame come in at most
+// two rounds on the chip, else all four of a 64-row frame (the expert's
+// gate/up, 256 column blocks of four row tiles, would draw 384 KB per CU from
+// L2 in 16-row tiles, against 164 KB). The frame count does not enter: a
+// frame's sums are the same in every group.
 constexpr int SLIM_MAX_TILES = 512;
-static bool use_slim(const GemmDesc& g) {
-  return g.epi.kind == EPI_RESID || g.epi.kind == EPI_EULER || slim_tiles(g) <= SLIM_MAX_TILES;
-}
+static int slim_rt(const GemmDesc& g) { return slim_tiles(g, 1) <= SLIM_MAX_TILES || g.M <= 16 ? 1 : 4; }
 // The operand's LayerNorm inside the GEMM: K as wide as the registers of a
 // wave per row hold (x, gain, shift and the weights in flight).
 constexpr int slim_ln_max_k(int dtype) { return dtype == DT_BF16 ? 1536 : 1024; }
@@ -1794,29 +1650,34 @@ bool slim_ln_fits(int dtype, int M, int N, int K, int kind) {
   g.M = M;
   g.N = N;
   g.epi.kind = kind;
-  return K % 8 == 0 && K <= slim_ln_max_k(dtype) && M <= 64 && slim_tiles(g) <= SLIM_MAX_TILES;
+  return K % 8 == 0 && K <= slim_ln_max_k(dtype) && M <= 64 && slim_tiles(g, 1) <= SLIM_MAX_TILES;
 }
 
-template <typename T, int NW, int SPW, int NB, int KIND, int LNR>
+template <typename T, int NW, int SPW, int NB, int RT, int KIND, int LNR>
 static hipError_t run_slim_t(const GemmDesc& g, const LaunchCaps& caps, hipStream_t st) {
-  int grid = (g.N + 16 * NB - 1) / (16 * NB) * ((g.M + 15) / 16) * g.frames;
+  int grid = slim_tiles(g, RT) * g.frames;
   if (caps.max_wgs > 0) grid = std::min(grid, caps.max_wgs);
   const int pf = prefetch_wgs(g.pf, g.frames, caps);
-  hipExtLaunchKernelGGL((k_slim<T, NW, SPW, NB, KIND, LNR>), dim3(grid + pf), dim3(64 * NW), 0, st, caps.ev_start,
+  hipExtLaunchKernelGGL((k_slim<T, NW, SPW, NB, RT, KIND, LNR>), dim3(grid + pf), dim3(64 * NW), 0, st, caps.ev_start,
                         caps.ev_stop, 0, (const T*)g.A, g.a_blk, g.ln, g.frames, (const T*)g.W, g.frag_ks,
                         g.frag_ks0, g.M, g.N, g.K, g.epi, grid, g.pf);
   return hipGetLastError();
 }
 
 // K-slabs a wave requests at once: its whole share where the registers
-// allow (NB = 1: 24 slabs, NB = 2: 16), else in rounds
+// allow (one row tile: 24 slabs of one n-block, 16 of two; four: 8 and 4),
+// else in rounds
 template <typename T, int NB, int KIND>
 static hipError_t run_slim_spw(const GemmDesc& g, const LaunchCaps& caps, hipStream_t st) {
   const int nslab = (g.K + frag_slab(g.dtype) - 1) / frag_slab(g.dtype), pw = (nslab + SLIM_NW - 1) / SLIM_NW;
-  if (pw <= 4) return run_slim_t<T, SLIM_NW, 4, NB, KIND, 0>(g, caps, st);
-  if (pw <= 8) return run_slim_t<T, SLIM_NW, 8, NB, KIND, 0>(g, caps, st);
-  if (NB == 2 || pw <= 16) return run_slim_t<T, SLIM_NW, 16, NB, KIND, 0>(g, caps, st);
-  return run_slim_t<T, SLIM_NW, NB == 1 ? 24 : 16, NB, KIND, 0>(g, caps, st);
+  if (slim_rt(g) == 4) {
+    if (NB == 2 || pw <= 4) return run_slim_t<T, SLIM_NW, 4, NB, 4, KIND, 0>(g, caps, st);
+    return run_slim_t<T, SLIM_NW, NB == 1 ? 8 : 4, NB, 4, KIND, 0>(g, caps, st);
+  }
+  if (pw <= 4) return run_slim_t<T, SLIM_NW, 4, NB, 1, KIND, 0>(g, caps, st);
+  if (pw <= 8) return run_slim_t<T, SLIM_NW, 8, NB, 1, KIND, 0>(g, caps, st);
+  if (NB == 2 || pw <= 16) return run_slim_t<T, SLIM_NW, 16, NB, 1, KIND, 0>(g, caps, st);
+  return run_slim_t<T, SLIM_NW, NB == 1 ? 24 : 16, NB, 1, KIND, 0>(g, caps, st);
 }
 
 template <typename T>
@@ -1840,9 +1701,9 @@ static hipError_t run_slim_kind(const GemmDesc& g, const LaunchCaps& caps, hipSt
 template <typename T, int NB, int KIND>
 static hipError_t run_slim_ln_k(const GemmDesc& g, const LaunchCaps& caps, hipStream_t st) {
   constexpr int S = sizeof(T) == 2 ? 1 : 2;  // slabs of a wave per 512 columns of K
-  if (g.K <= 512) return run_slim_t<T, SLIM_LN_NW, S, NB, KIND, 2>(g, caps, st);
-  if (g.K <= 1024) return run_slim_t<T, SLIM_LN_NW, 2 * S, NB, KIND, 4>(g, caps, st);
-  if constexpr (sizeof(T) == 2) return run_slim_t<T, SLIM_LN_NW, 3, NB, KIND, 6>(g, caps, st);
+  if (g.K <= 512) return run_slim_t<T, SLIM_LN_NW, S, NB, 1, KIND, 2>(g, caps, st);
+  if (g.K <= 1024) return run_slim_t<T, SLIM_LN_NW, 2 * S, NB, 1, KIND, 4>(g, caps, st);
+  if constexpr (sizeof(T) == 2) return run_slim_t<T, SLIM_LN_NW, 3, NB, 1, KIND, 6>(g, caps, st);
   return hipErrorInvalidValue;
 }
 template <typename T>
@@ -1857,8 +1718,7 @@ static hipError_t run_slim_ln(const GemmDesc& g, const LaunchCaps& caps, hipStre
 }
 
 
-static hipError_t launch_skinny(const GemmDesc& g, const Scratch& s, const LaunchCaps& caps,
-                                hipStream_t st) {
+static hipError_t launch_slim(const GemmDesc& g, const LaunchCaps& caps, hipStream_t st) {
   if (g.M > 64 || g.frames < 1 || g.frames > MAX_FRAMES ||
       (g.frames > 1 && (g.epi.blk_rows != g.M || g.a_blk < afrag_elems(g.dtype, g.K))))
     return hipErrorInvalidValue;
@@ -1876,11 +1736,7 @@ static hipError_t launch_skinny(const GemmDesc& g, const Scratch& s, const Launc
       return hipErrorInvalidValue;
     return g.dtype == DT_BF16 ? run_slim_ln<uint16_t>(g, caps, st) : run_slim_ln<float>(g, caps, st);
   }
-  if (use_slim(g)) return g.dtype == DT_BF16 ? run_slim_kind<uint16_t>(g, caps, st) : run_slim_kind<float>(g, caps, st);
-  const int splits = skinny_splits(g);
-  if (splits > 1 && (e.rowss || (size_t)splits * g.M * g.frames * g.N > s.floats)) return hipErrorInvalidValue;
-  if (g.dtype == DT_BF16) return run_skinny_kind<uint16_t>(g, splits, s, caps, st);
-  return run_skinny_kind<float>(g, splits, s, caps, st);
+  return g.dtype == DT_BF16 ? run_slim_kind<uint16_t>(g, caps, st) : run_slim_kind<float>(g, caps, st);
 }
 
 struct TileCfg {
@@ -1894,16 +1750,10 @@ static const TileCfg kF32Cfg[] = {{64, 64, 32}, {32, 64, 32}};
 
 GemmPlan plan_gemm(const GemmDesc& g) {
   GemmPlan p{};
-  if (g.frag_ks > 0) {  // fragment-ordered weights: the skinny kernels
+  if (g.frag_ks > 0) {  // fragment-ordered weights: the slim kernel, never split
     p.cfg = -1;
-    if (g.ln.x || use_slim(g)) {
-      p.splits = 1;
-      p.tiles = slim_tiles(g) * g.frames;
-      return p;
-    }
-    p.splits = skinny_splits(g);
-    p.tiles = ((g.N + 31) / 32) * p.splits * g.frames;
-    p.scratch_floats = p.splits > 1 ? (size_t)p.splits * g.M * g.frames * g.N : 0;
+    p.splits = 1;
+    p.tiles = slim_tiles(g, g.ln.x ? 1 : slim_rt(g)) * g.frames;
     return p;
   }
   const TileCfg* cfgs = g.dtype == DT_BF16 ? kBf16Cfg : kF32Cfg;
@@ -2051,7 +1901,7 @@ static hipError_t run_gemm_kind(const GemmDesc& g, const GemmPlan& p, const Scra
 
 hipError_t launch_gemm(const GemmDesc& g, const Scratch& s, const LaunchCaps& caps,
                        hipStream_t st) {
-  if (g.frag_ks > 0) return launch_skinny(g, s, caps, st);
+  if (g.frag_ks > 0) return launch_slim(g, caps, st);
   const GemmPlan p = plan_gemm(g);
   if (g.epi.kind == EPI_PART) {
     if (!g.epi.out || (size_t)p.splits * g.M * g.N > (size_t)g.epi.ldo) return hipErrorInvalidValue;
@@ -2873,7 +2723,7 @@ __global__ __launch_bounds__(64 * NW) void k_attn2(Attn2Args a) {
 // 355 keys take it 13 us.
 // ---------------------------------------------------------------------------
 
-template <int HDP, int VB>
+template <int HDP, int VB, int DS>
 __global__ __launch_bounds__(512) void k_attn3(Attn2Args a) {
   VLA_WAVE_BEGIN(KK_ATTN2);
   if ((int)blockIdx.x >= a.grid) {
@@ -2883,27 +2733,36 @@ __global__ __launch_bounds__(512) void k_attn3(Attn2Args a) {
   }
   typedef uint16_t T;
   constexpr int NW = 8, CB = (VB + NW - 1) / NW;  // waves; score blocks per wave and chunk
-  constexpr int NQF = HDP / 32, NOT = HDP / 16, DT = NOT / NW;
+  constexpr int NQF = HDP / 32, NOT = HDP / 16;
+  constexpr int WT = NOT / DS;                // head-dim tiles of a workgroup
+  constexpr int DT = WT >= NW ? WT / NW : 1;  // of a wave
+  constexpr int KH = NW * DT / WT;            // waves that share a tile, each its part of the blocks
+  constexpr int VW = VB / KH;                 // a wave's blocks
+  static_assert(WT * KH == NW * DT && VB % KH == 0, "waves cover the tiles");
   constexpr int QS = HDP + 8;
   constexpr uint32_t CH = 1024;  // bytes of a fragment chunk
   __shared__ __attribute__((aligned(16))) T sQ[16 * QS];
   __shared__ uint4 sP[NW * CB][2][64];
   __shared__ float sM[NW][16], sL[NW][16];
+  __shared__ f32x4 sO[KH > 1 ? KH - 1 : 1][KH > 1 ? WT : 1][64];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g4 = lane >> 4;
   const int group = a.nq / a.nkv;
   const int R = a.Sq * group;
   const int nblk = a.nb0 + a.nb1;
-  const int total = a.rtiles * a.nkv, all = total * a.frames;
+  const int total = a.rtiles * a.nkv, all = total * a.frames * DS;
+  const int wd = wave % (WT / DT), wk = wave / (WT / DT);  // head-dim tiles DT wd .., blocks VW wk ..
   const T dummy = T();
   const Rsrc rq = rsrc(a.q, span(a.Sq * a.frames, a.ldq, a.nq * HDP, sizeof(T)));
   // each XCD takes a contiguous range of tiles, so the tiles of a frame (and
   // of a KV head) share their K and V in one L2
   const int first = a.grid % 8 == 0 ? (int)(blockIdx.x % 8) * (a.grid / 8) + (int)(blockIdx.x / 8) : (int)blockIdx.x;
   for (int w = first; w < all; w += a.grid) {
-    const int f = __builtin_amdgcn_readfirstlane(w / total), wl = w % total;
+    const int ds = w % DS, wq = w / DS;
+    const int f = __builtin_amdgcn_readfirstlane(wq / total), wl = wq % total;
     const int rt = wl % a.rtiles, j = wl / a.rtiles;
+    const int dt0 = ds * WT + wd * DT;  // this wave's first head-dim tile
     // KV head j of both segments (nb 32-key blocks of HDP / 16 K chunks and as many V chunks)
     const size_t h0 = (size_t)a.nb0 * NOT * CH, h1 = (size_t)a.nb1 * NOT * CH;
     const Rsrc rk0 = rsrc((const char*)a.k0[f] + j * h0, h0), rv0 = rsrc((const char*)a.v0[f] + j * h0, h0);
@@ -2929,7 +2788,13 @@ __global__ __launch_bounds__(512) void k_attn3(Attn2Args a) {
         const Rsrc r = seg1 ? rk1 : rk0;
         uint32_t off = (uint32_t)(seg1 ? b - a.nb0 : b) * (NOT * CH) + lane * 16;
 #pragma unroll
-        for (int c = 0; c < 2 * NQF; ++c) kf[t][c / NQF][c % NQF] = bld16(r, off + c * CH);
+        for (int c = 0; c < 2 * NQF; ++c) {
+          if (c > 0 && c % 4 == 0) {  // (see load_w of k_slim)
+            off += 4 * CH;
+            asm("" : "+v"(off));
+          }
+          kf[t][c / NQF][c % NQF] = bld16(r, off + (c % 4) * CH);
+        }
       }
     };
     load_k(0);
@@ -2956,16 +2821,17 @@ __global__ __launch_bounds__(512) void k_attn3(Attn2Args a) {
         for (int ks = 0; ks < NQF; ++ks)
 #pragma unroll
           for (int nt = 0; nt < 2; ++nt) s[t][nt] = mfma_step(kf[t][nt][ks], qf[ks], s[t][nt], dummy);
-      // this wave's V: head-dim tiles DT wave .. + DT - 1 of every block, into
-      // the registers that K held
+      // this wave's V: its head-dim tiles of its blocks, into the registers
+      // that K held
       __builtin_amdgcn_sched_barrier(0);
-      uint4 vf[VB][DT];
+      uint4 vf[VW][DT];
 #pragma unroll
-      for (int u = 0; u < VB; ++u) {
-        const int b = base + u;
+      for (int u = 0; u < VW; ++u) {
+        const int b = base + wk * VW + u;
         const bool seg1 = b >= a.nb0;
         const Rsrc r = seg1 ? rv1 : rv0;
-        const uint32_t off = (uint32_t)(seg1 ? b - a.nb0 : b) * (NOT * CH) + wave * (DT * CH) + lane * 16;
+        uint32_t off = (uint32_t)(seg1 ? b - a.nb0 : b) * (NOT * CH) + dt0 * CH + lane * 16;
+        asm("" : "+v"(off));
 #pragma unroll
         for (int d = 0; d < DT; ++d) vf[u][d] = bld16(r, off + d * CH);
       }
@@ -3023,8 +2889,8 @@ __global__ __launch_bounds__(512) void k_attn3(Attn2Args a) {
 #pragma unroll
       for (int d = 0; d < DT; ++d) o2[d] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int u = 0; u < VB; ++u) {
-        const uint4 hi = sP[u][0][lane], lo = sP[u][1][lane];
+      for (int u = 0; u < VW; ++u) {
+        const uint4 hi = sP[wk * VW + u][0][lane], lo = sP[wk * VW + u][1][lane];
 #pragma unroll
         for (int d = 0; d < DT; ++d) {
           o[d] = mfma_step(vf[u][d], hi, o[d], dummy);
@@ -3040,14 +2906,17 @@ __global__ __launch_bounds__(512) void k_attn3(Attn2Args a) {
     }
     lpart = wave_sum_x16_x32(lpart);
     if (lane < 16) sL[wave][lane] = lpart;
+    if (KH > 1 && wk > 0) sO[wk - 1][wd][lane] = o[0];  // (KH > 1: one tile per wave)
     __syncthreads();
     float den = 0.f;
 #pragma unroll
     for (int u = 0; u < NW; ++u) den += sL[u][lane & 15];
+#pragma unroll
+    for (int u = 0; u < KH - 1; ++u) o[0] += sO[u][wd][lane];
     const float inv = 1.f / den;
     const int prow = rt * 16 + (lane & 15);
-    if (prow < R) {
-      const int sq = prow / group, col = (j * group + prow % group) * HDP + wave * (16 * DT) + 4 * g4;
+    if (prow < R && wk == 0) {
+      const int sq = prow / group, col = (j * group + prow % group) * HDP + dt0 * 16 + 4 * g4;
       T* ob = (T*)a.out + f * a.out_blk;
 #pragma unroll
       for (int d = 0; d < DT; ++d) {
@@ -3096,9 +2965,19 @@ static void attn2_split(Attn2Args& a, float* part, size_t part_floats, unsigned*
 // k_attn3: bf16, head dim exactly 128 or 256 (no unused head-dim positions to
 // mask). The chunk is the smallest that holds the call's key blocks.
 static bool use_attn3(int dtype, int hd) { return dtype == DT_BF16 && (hd == 128 || hd == 256); }
-static hipError_t run_attn3(Attn2Args& a, const LaunchCaps& caps, hipStream_t st) {
+static hipError_t run_attn3(Attn2Args& a, bool solo, const LaunchCaps& caps, hipStream_t st) {
   a.nsplit = 1;
-  a.grid = a.rtiles * a.nkv * a.frames;
+  // One tile's K and V come through one CU at about 50 bytes per clock (384 KB
+  // for the expert's 355 keys: 3 us), so few tiles are split along the head
+  // dim, each part computing the scores again and a part of the output: the
+  // expert's 25 tiles as 100 workgroups of K and a quarter of V (one call
+  // after another, 9.1 us unsplit, 7.8 us in four). Where a wave's part falls
+  // below one 16-row tile, waves share it by keys, which changes the order of
+  // the sums: only for launches that are never batched (solo). Two parts of
+  // head dim 256 keep the order.
+  const int tiles = a.rtiles * a.nkv * a.frames;
+  const int ds = solo ? (tiles <= 64 ? 4 : tiles <= 128 ? 2 : 1) : (a.hd == 256 && tiles <= 128 ? 2 : 1);
+  a.grid = tiles * ds;
   if (caps.max_wgs > 0) a.grid = std::min(a.grid, caps.max_wgs);
   const int grid = a.grid + prefetch_wgs(a.pf, a.frames, caps);
   const int nblk = a.nb0 + a.nb1;
@@ -3106,8 +2985,14 @@ static hipError_t run_attn3(Attn2Args& a, const LaunchCaps& caps, hipStream_t st
     hipExtLaunchKernelGGL(k, dim3(grid), dim3(512), 0, st, caps.ev_start, caps.ev_stop, 0, a);
     return hipGetLastError();
   };
-  if (a.hd == 256) return nblk <= 8 ? go(k_attn3<256, 8>) : nblk <= 12 ? go(k_attn3<256, 12>) : go(k_attn3<256, 16>);
-  return nblk <= 8 ? go(k_attn3<128, 8>) : go(k_attn3<128, 16>);
+  auto pick = [&](auto ic) {
+    constexpr int DS = ic;
+    if (a.hd == 256)
+      return nblk <= 8 ? go(k_attn3<256, 8, DS>) : nblk <= 12 ? go(k_attn3<256, 12, DS>) : go(k_attn3<256, 16, DS>);
+    return nblk <= 8 ? go(k_attn3<128, 8, DS>) : go(k_attn3<128, 16, DS>);
+  };
+  return ds == 4 ? pick(std::integral_constant<int, 4>{}) : ds == 2 ? pick(std::integral_constant<int, 2>{})
+                                                                    : pick(std::integral_constant<int, 1>{});
 }
 
 template <typename T>
@@ -3182,7 +3067,7 @@ hipError_t launch_attention_kv(const AttnKvDesc& d, const LaunchCaps& caps, hipS
   a.nb1 = (d.S1 + 31) / 32;
   a.rtiles = (d.Sq * (d.nq / d.nkv) + 15) / 16;
   a.scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)d.hd));
-  if (use_attn3(d.dtype, d.hd)) return run_attn3(a, caps, st);
+  if (use_attn3(d.dtype, d.hd)) return run_attn3(a, d.solo && d.frames == 1, caps, st);
   if (d.dtype == DT_BF16) return run_attn2_t<uint16_t>(a, hdp, caps, st, d.part, d.part_floats, d.cnt, d.cnt_n);
   return run_attn2_t<float>(a, hdp, caps, st, d.part, d.part_floats, d.cnt, d.cnt_n);
 }

@@ -905,8 +905,15 @@ static Epi epi_kind(int kind, void* out = nullptr, int ldo = 0, const float* bia
   return e;
 }
 
-// workgroups that read weights ahead, per launch of a one-frame layer
-constexpr int PF_ATTN = 192, PF_O = 128, PF_GU = 64, PF_KV = 64, PF_MLP = 64;
+// Workgroups that read ahead, per launch of a one-frame layer. The pi0 loop
+// (10 steps of 18 layers) takes 6.67 ms without and 6.11 ms with the QKV
+// launch reading the layer's prefix K and V (64 workgroups; 6.36 ms without
+// that) and the attention reading the O and gate/up weights (96; 128 and 192:
+// 6.15 ms). More is slower: the O launch reading the down weights 6.15 ms,
+// the gate/up launch, whose workgroups fill the CUs, reading the next QKV
+// weights 6.41 ms. The cognition-token head (one frame 12.93 ms without)
+// gains from all of its four: 12.55 ms.
+constexpr int PF_KV = 64, PF_ATTN = 96, PF_COG = 128, PF_DIT = 64;
 
 // One Gemma-style decoder layer: RMSNorm (after adding the pending residual
 // partials) -> QKV (+RoPE, K/V stored) -> attention over [past; own] -> O ->
@@ -934,7 +941,7 @@ static int decoder_layer(const Run& r, bool lm, const DecLayer& L, float* x, int
                          void* h, void* q, void* kout, void* vout, int pos0, const void* const* kpast,
                          const void* const* vpast, int npast, void* att, void* mlpbuf, bool kv_only,
                          int* pend, int frames = 1, size_t kstride = 0, size_t vstride = 0,
-                         const vla_model::WideLayer* wl = nullptr, int next_g = -1, int next_w = -1) {
+                         const vla_model::WideLayer* wl = nullptr, int next_g = -1) {
   vla_model* m = r.m;
   const vla_config& c = m->c;
   const Dims& d = m->d;
@@ -1033,13 +1040,15 @@ static int decoder_layer(const Run& r, bool lm, const DecLayer& L, float* x, int
     a.v1_blk = aw->blk_v;
     a.out_blk = (size_t)rows * d.qd;
   }
-  if (fold) a.pf = ahead(r, PF_ATTN, L.o, L.gu);
+  if (fold) {
+    a.solo = true;
+    a.pf = ahead(r, PF_ATTN, L.o, L.gu);
+  }
   VLA_TRY(attn_kv(r, lm ? "lm.attn" : "ex.attn", a));
   int so = 0;
   const char* to = lm ? "lm.o" : "ex.o";
   if (fold) {
-    VLA_TRY(gemm_resid(r, to, att, d.qd, L.o, gm, dim, d.qd, x, nullptr, L.rms2, h,
-                       ahead(r, PF_O, L.down)));
+    VLA_TRY(gemm_resid(r, to, att, d.qd, L.o, gm, dim, d.qd, x, nullptr, L.rms2, h));
   } else {
     if (wide)
       VLA_TRY(gemm_part_rm(r, to, att, d.qd, wl->o, d.qd, gm, dim, d.qd, &so, frm));
@@ -1054,7 +1063,7 @@ static int decoder_layer(const Run& r, bool lm, const DecLayer& L, float* x, int
   if (wide)
     VLA_TRY(gemm_rm(r, tg, h, dim, wl->gu, dim, gm, 2 * mlp, dim, eg, frm));
   else
-    VLA_TRY(gemm(r, tg, h, dim, L.gu, gm, 2 * mlp, dim, eg, 0, frm, fold ? ahead(r, PF_GU, next_w) : Prefetch()));
+    VLA_TRY(gemm(r, tg, h, dim, L.gu, gm, 2 * mlp, dim, eg, 0, frm));
   const char* td = lm ? "lm.down" : "ex.down";
   if (fold) {
     VLA_TRY(gemm_resid(r, td, mlpbuf, mlp, L.down, gm, dim, mlp, x, nullptr, next_g, h));
@@ -1274,15 +1283,16 @@ static int run_denoise_dit(const Run& r, const vla_ctx* ctx, const float* noise,
         a.v0 = w.vown;
         a.S0 = H;
       }
+      a.solo = true;
       a.pf = ahead(r, PF_ATTN, D.o, D.fc1);
       VLA_TRY(attn_kv(r, "ex.attn", a));
       VLA_TRY(gemm_resid(r, "ex.o", w.att, de, D.o, H, de, de, w.u, ad + 2 * de));
       Epi e1 = epi_kind(EPI_GELU, w.mlp, c.ex_mlp);
       e1.afrag = 1;
       VLA_TRY(gemm_ln(r, "ex.fc1", adanorm(ad + 3 * de, ad + 4 * de), w.h, D.fc1, H, c.ex_mlp, de, e1,
-                      ahead(r, PF_MLP, D.fc2)));
+                      ahead(r, PF_DIT, D.fc2)));
       VLA_TRY(gemm_resid(r, "ex.fc2", w.mlp, c.ex_mlp, D.fc2, H, de, c.ex_mlp, w.u, ad + 5 * de, -1, nullptr,
-                         ahead(r, PF_MLP, l + 1 < L ? (l % 2 ? m->dit[l + 1].q : m->dit[l + 1].qkv) : m->dit[0].q)));
+                         ahead(r, PF_DIT, l + 1 < L ? (l % 2 ? m->dit[l + 1].q : m->dit[l + 1].qkv) : m->dit[0].q)));
     }
     const float* fa = m->fada + (size_t)k * 2 * de;
     Epi e;
@@ -1351,14 +1361,15 @@ static int run_denoise_cog(const Run& r, const vla_ctx* ctx, const float* noise,
       a.Sq = S;
       a.out = w.att;
       a.out_afrag = 1;
+      a.solo = true;
       a.pf = ahead(r, PF_ATTN, L.o, L.fc1);
       VLA_TRY(attn_kv(r, "ex.attn", a));
-      VLA_TRY(gemm_resid(r, "ex.o", w.att, de, L.o, S, de, de, w.u, nullptr, -1, nullptr, ahead(r, PF_O, L.fc2)));
+      VLA_TRY(gemm_resid(r, "ex.o", w.att, de, L.o, S, de, de, w.u, nullptr, -1, nullptr, ahead(r, PF_COG, L.fc2)));
       Epi e1 = epi_kind(EPI_GELU, w.mlp, c.ex_mlp);
       e1.afrag = 1;
       VLA_TRY(gemm_ln(r, "ex.fc1", ln(L.ln2_g, L.ln2_b), w.h, L.fc1, S, c.ex_mlp, de, e1));
       VLA_TRY(gemm_resid(r, "ex.fc2", w.mlp, c.ex_mlp, L.fc2, S, de, c.ex_mlp, w.u, nullptr, -1, nullptr,
-                         ahead(r, PF_O, m->cogl[(l + 1) % c.ex_layers].qkv)));
+                         ahead(r, PF_COG, m->cogl[(l + 1) % c.ex_layers].qkv)));
     }
     Epi e;
     e.kind = EPI_EULER;
@@ -1464,8 +1475,7 @@ static int run_denoise_n(const Run& r, const vla_ctx* const* ctxs, int frames, c
       }
       VLA_TRY(decoder_layer(r, false, m->ex[l], w.u, H, de, c.ex_mlp, w.h, w.q, w.kown, w.vown, d.prefix,
                             K, V, d.prefix, w.att, w.mlp, false, &pend, frames, 0, 0,
-                            fb ? &m->exw[l] : nullptr, l + 1 < c.ex_layers ? m->ex[l + 1].rms1 : m->fin_g,
-                            l + 1 < c.ex_layers ? m->ex[l + 1].qkv : m->ex[0].qkv));
+                            fb ? &m->exw[l] : nullptr, l + 1 < c.ex_layers ? m->ex[l + 1].rms1 : m->fin_g));
     }
     // (pend < 0: the last down projection left h = x * fin_g and its row sums)
     if (pend >= 0) VLA_TRY(norm(r, w.u, frames * H, de, pend, nullptr, m->fin_g, -1, true, w.h, true, blk, w.blk_de));
@@ -3004,6 +3014,7 @@ int vla_debug_attention_cache(int32_t dtype, int32_t Sq, int32_t nq, int32_t nkv
     a.nq = nq;
     a.nkv = nkv;
     a.hd = hd;
+    a.solo = true;
     // room for key splits, as the action phases give it (zeroed counters)
     int nc = 0;
     const size_t nf = attn_kv_split_floats(a.dtype, 1, Sq, nq, nkv, hd, S0, S1, &nc);

@@ -1,0 +1,114 @@
+"""GPU tests of the action head's GEMM and of the short-key cache attention at
+the sizes where their tiles, rounds and splits change."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+from oracle import vla_oracle as O  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def V():
+    assert torch.cuda.is_available()
+    import paper_2609_22335_amd as mod
+    return mod
+
+
+# (dtype, M, N, K): row tiles 1, 1 + 1 row, 3 + 2 rows, 4; a last column block
+# of 8; one and two blocks of row sums (N <= and > 1024); K of one piece, of a
+# slab and a piece, at and past a wave's 4, 8, 16 and 24 slabs, and in rounds
+@pytest.mark.parametrize("dtype,M,N,K", [
+    (1, 1, 8, 8), (1, 16, 40, 40), (1, 17, 1024, 1032), (1, 50, 1024, 2056), (1, 64, 1032, 4104), (1, 18, 2048, 6152),
+    (0, 1, 8, 8), (0, 17, 72, 264), (0, 50, 1032, 1544), (0, 64, 128, 3080),
+])
+@pytest.mark.parametrize("kind", ["bias", "t", "gelu", "resid_norm"])
+def test_action_gemm_edges(V, kind, dtype, M, N, K):
+    import gpu_util as g
+    g.say(f"slim gemm {kind} {dtype} {M}x{N}x{K}")
+    rng = np.random.default_rng(M * 7919 + N * 31 + K)
+    a = rng.standard_normal((M, K)).astype(np.float32)
+    w = (0.05 * rng.standard_normal((N, K))).astype(np.float32)
+    b = rng.standard_normal(N).astype(np.float32)
+    opt = torch.bfloat16 if dtype else torch.float32
+    A, W = torch.from_numpy(a).cuda().to(opt), torch.from_numpy(w).cuda().to(opt)
+    a, w = A.double().cpu().numpy(), W.double().cpu().numpy()
+    v = a @ w.T
+    delta = 2 * K * 2.0 ** -24 * (np.abs(a) @ np.abs(w).T) + 2.0 ** -22 * (np.abs(v) + np.abs(b))
+    ulp = 2.0 ** -8 if dtype else 2.0 ** -22
+    bd = torch.from_numpy(b).cuda()
+    if kind == "resid_norm":
+        x0 = rng.standard_normal((M, N)).astype(np.float32)
+        gain = (1 + 0.02 * rng.standard_normal(N)).astype(np.float32)
+        x, out = torch.from_numpy(x0).cuda(), torch.full((M, N), float("nan"), dtype=opt, device="cuda")
+        V.vla_debug_gemm_epi(dtype, M, N, K, A, W, kind, skinny=True, out=out, resid=x,
+                             gain=torch.from_numpy(gain).cuda())
+        ref = x0 + v
+        assert (np.abs(x.double().cpu().numpy() - ref) <= delta + 2.0 ** -23 * np.abs(ref)).all()
+        rms = np.sqrt((ref * ref).mean(1, keepdims=True) + 1e-6)
+        ref = ref / rms * gain
+        # the norm carries each row's largest error through 1 / rms
+        bound = 4 * (np.abs(gain) + np.abs(ref)) * delta.max(1, keepdims=True) / rms + (ulp + 2.0 ** -20) * np.abs(ref)
+    else:
+        out = torch.full((M, N), float("nan"), dtype=torch.float32 if kind == "bias" else opt, device="cuda")
+        V.vla_debug_gemm_epi(dtype, M, N, K, A, W, kind, skinny=True, bias=bd, out=out)
+        ref = v + b
+        if kind == "gelu":  # slope at most 1.13; the kernel's exp2 and reciprocal are good to about 1 ulp
+            ref, delta = O.gelu_tanh(ref), 1.13 * delta + 2.0 ** -20 * np.abs(ref)
+        bound = delta + (0 if kind == "bias" else ulp) * np.abs(ref) + 1e-30
+    err = np.abs(out.double().cpu().numpy() - ref)
+    assert (err <= bound).all(), (err.max(), (err / bound).max())
+
+
+# (Sq, nq, nkv, hd, S0, S1): tiles split four ways, in two and unsplit along
+# the head dim; key blocks at 8, 12 and 16 and one past, two and three chunks;
+# ragged segments; a last query tile of one row
+@pytest.mark.parametrize("Sq,nq,nkv,hd,S0,S1", [
+    (50, 8, 1, 256, 305, 50), (50, 8, 1, 256, 256, 0), (50, 8, 1, 256, 257, 0), (33, 8, 1, 256, 384, 0),
+    (51, 8, 1, 256, 352, 33), (50, 8, 1, 256, 833, 50), (130, 8, 1, 256, 512, 1), (305, 8, 1, 256, 305, 0),
+    (833, 8, 1, 256, 833, 0), (1, 1, 1, 256, 1, 0), (16, 4, 4, 128, 96, 0), (96, 16, 16, 128, 96, 0),
+    (17, 3, 1, 128, 300, 17), (40, 16, 2, 128, 1100, 31), (200, 8, 8, 128, 513, 0),
+])
+def test_cache_attention_chunks(V, Sq, nq, nkv, hd, S0, S1):
+    import gpu_util as g
+    g.say(f"cache attention {Sq} {nq}/{nkv} hd {hd} keys {S0}+{S1}")
+    rng = np.random.default_rng(Sq * 1009 + S0)
+    rnd = lambda s, n: torch.from_numpy(rng.standard_normal((s, n, hd)).astype(np.float32)).to(torch.bfloat16)
+    q, k, v = 2 * rnd(Sq, nq), rnd(S0 + S1, nkv), rnd(S0 + S1, nkv)
+    dk, dv = [], []
+    for x, y in ((k[:S0], v[:S0]), (k[S0:], v[S0:])):
+        if not x.shape[0]:
+            dk.append(None)
+            dv.append(None)
+            continue
+        kc, vc = cache_layout(x, y)
+        dk.append(kc.cuda())
+        dv.append(vc.cuda())
+    out = torch.full((Sq, nq, hd), float("nan"), dtype=torch.bfloat16, device="cuda")
+    V.vla_debug_attention_cache(1, Sq, nq, nkv, hd, q.cuda(), dk[0], dv[0], S0, dk[1], dv[1], S1, out)
+    torch.cuda.synchronize()
+    ref = O.attention(*(t.double().numpy() for t in (q, k, v)))
+    err = np.abs(out.double().cpu().numpy() - ref)
+    # one bf16 rounding; scores and P (two bf16 parts) to well under 1e-4 of values of order 1
+    assert (err <= 2.0 ** -8 * np.abs(ref) + 2e-4).all(), err.max()
+
+
+def cache_layout(k, v):
+    """bf16 K / V rows [S, nkv, hd] in the KV-cache layout (include/vla.h);
+    unused K positions hold NaN, unused V positions zero."""
+    S, nkv, hd = k.shape
+    nb, ns, ndt = (S + 31) // 32, (hd + 31) // 32, (hd + 15) // 16
+    p = torch.arange(S).view(S, 1, 1)
+    j = torch.arange(nkv).view(1, nkv, 1)
+    d = torch.arange(hd).view(1, 1, hd)
+    b, kin = p // 32, p % 32
+    ki = ((((j * nb + b) * 2 + (kin // 4) % 2) * ns + d // 32) * 64 + 16 * ((d % 32) // 8) + 4 * (kin // 8) + kin % 4) * 8 + d % 8
+    vi = (((j * nb + b) * ndt + d // 16) * 64 + 16 * (kin // 8) + d % 16) * 8 + kin % 8
+    K = torch.full((nkv * nb * 32 * ns * 32,), float("nan"), dtype=torch.bfloat16)
+    W = torch.zeros(nkv * nb * 32 * ndt * 16, dtype=torch.bfloat16)
+    K[ki.reshape(-1)] = k.reshape(-1)
+    W[vi.reshape(-1)] = v.reshape(-1)
+    return K, W
