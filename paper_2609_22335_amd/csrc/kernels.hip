@@ -22,6 +22,7 @@ namespace vla {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int NUM_CU_PLAN = 256;  // planner constant; never the live CU count
 
@@ -144,6 +145,15 @@ __device__ __forceinline__ f32x4 mfma_step(uint4 a, uint4 b, f32x4 c, float) {
   c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.z), __uint_as_float(b.z), c, 0, 0, 0);
   c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.w), __uint_as_float(b.w), c, 0, 0, 0);
   return c;
+}
+
+// The 32 x 32 x 16 step of the 4-wave direct-load GEMM tiles. Two of them over
+// the same 32 K columns give bit for bit what one 16 x 16 x 32 step gives (both
+// add the products in the same order), so tiles of either shape compute the
+// same results.
+__device__ __forceinline__ f32x16 mfma32_step(uint4 a, uint4 b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0,
+                                                 0, 0);
 }
 
 // Masked loads go through buffer resources: a byte offset at or past the
@@ -452,6 +462,12 @@ __device__ __forceinline__ void epi_pairs(const Epi& e, int M, int N, const int 
 #define VLA_GEMM_LDS_PAD 2  // LDS row padding of the GEMM tiles, in 16-byte units (32 B: fewest bank conflicts measured)
 #endif
 
+// v, as a value the compiler knows nothing about
+__device__ __forceinline__ int opaque(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
 // Compile-time loop: f(integral_constant<int, I>) for I = B .. E-1, so that
 // register arrays are indexed by constants even where the loop body is too
 // large for the unroller.
@@ -480,43 +496,69 @@ struct GemmSmem {
 // epilogue slice; stage 1 is a separate __shared__ array, so the compiler can
 // tell the two stages apart and lets the LDS reads of one stage run while
 // loads into the other are in flight.
-template <typename T, int BM, int BN, int BK, int WGM>
+template <typename T, int BM, int BN, int BK, int WGM, int NS>
 struct GemmSmemDL {
   static constexpr int CLD = BN + 4;
+  static constexpr int SZ = (NS == 3 ? BM : BM + BN) * BK;  // elements of a stage
   union {
-    T d[(BM + BN) * BK];
+    T d[SZ];
     float c[WGM * 16 * CLD];
   };
 };
 
 // Waves per SIMD each tile is built for, so that its registers leave room
-// for the workgroups its LDS allows on a CU (160 KB): the 4-wave 128 x 128
-// bf16 tile (80 KB) two per CU, the smaller 4-wave bf16 tiles (40 and 30 KB)
-// four (the fp32 tiles, which only the small test models run, three); the
-// 8-wave 256 x 256 tile runs alone. Without it the compiler may take a few
-// registers more than that leaves (the 128 x 128 GeGLU tile took 260 of
-// 256) and a CU then holds one workgroup fewer.
-constexpr int gemm_waves_per_eu(int bm, int waves, bool dl, int esize) {
-  return dl || waves != 4 ? 2 : esize == 4 ? 3 : bm >= 128 ? 2 : 4;
+// for the workgroups its LDS allows on a CU (160 KB). Direct-load tiles of 4
+// waves: 64 x 64 in two stages (32 KB) four per CU, in the ring of four
+// (64 KB) two; 128 x 128 (64 KB) two; the 320 x 128 (128 KB) and 256 x 256
+// (128 KB) ones alone, with the whole register file. The 8-wave 256 x 256
+// tile runs alone too, two waves per SIMD. Register-staged tiles: bf16 four
+// (40 and 30 KB), fp32, which only the small test models run, three. Without
+// it the compiler may take a few registers more than that leaves (the
+// 128 x 128 GeGLU tile took 260 of 256) and a CU then holds one workgroup
+// fewer.
+constexpr int gemm_waves_per_eu(int bm, int waves, bool dl, int esize, int ns) {
+  if (!dl) return esize == 4 ? 3 : 4;
+  if (waves != 4) return 2;
+  return bm <= 64 ? (ns == 2 ? 4 : 2) : bm <= 128 ? 2 : 1;
 }
+
+// What bounds these tiles. A register-staged K-step is a chain of read,
+// multiply, store and barrier, 850 cycles for 64 x 64 x 64 with one workgroup
+// on the CU whatever its prefetch depth; loads straight into LDS take the
+// store out of it and 32 x 32 x 16 MFMAs half of the fragment reads. From
+// there a large launch is bound by the matrix pipe (a wave's MFMAs come in one
+// stream, with a fragment read or a load between every few), a small one by
+// the ~450-cycle step of its ring. Alone, weights from HBM, before (64 x 64
+// through registers; 128 and 256 tiles of 16 x 16 x 32 MFMAs) and now:
+//   400 x 1024 x 1024    64 ring    10.4 us   8.9 us
+//   400 x 2560 x 1024    64 ring    13.5 us  11.4 us
+//   256 x 3456 x 1152    64         11.5 us   9.9 us
+//   2048 x 3456 x 1152   128        36.8 us  27.3 us
+//   2440 x 2560 x 2048   128        50.4 us  40.8 us
+//   305 x 16384 x 2048   128        50.8 us  43.4 us
+//   305 x 32768 x 2048   320 x 128  84 us    65 us
 
 // KIND >= 0: the epilogue kind fixed at compile time (the tiles of the
 // batched action loops, short launches whose code should stay in the
 // instruction cache); KIND = -1: chosen at run time from e.kind.
 template <typename T, int BM, int BN, int BK, int WGM = 2, int WGN = 2, int PD = 1, int PAD = VLA_GEMM_LDS_PAD,
-          bool DL = false, int KIND = -1>
+          bool DL = false, int KIND = -1, int NS = 2>
 __global__ __launch_bounds__(64 * WGM * WGN)
-__attribute__((amdgpu_waves_per_eu(gemm_waves_per_eu(BM, WGM * WGN, DL, (int)sizeof(T))))) void k_gemm(const T* __restrict__ A, int lda,
+__attribute__((amdgpu_waves_per_eu(gemm_waves_per_eu(BM, WGM * WGN, DL, (int)sizeof(T), NS)))) void k_gemm(const T* __restrict__ A, int lda,
                                               const T* __restrict__ W, int ldw, int M, int N,
                                               int K, int kchunk, int splits, int tiles_m,
                                               int tiles_n, int group_m, Epi e, float* __restrict__ part) {
   VLA_WAVE_BEGIN(KK_GEMM);
-  using SM = std::conditional_t<DL, GemmSmemDL<T, BM, BN, BK, WGM>, GemmSmem<T, BM, BN, BK, WGM, PAD>>;
+  using SM = std::conditional_t<DL, GemmSmemDL<T, BM, BN, BK, WGM, NS>, GemmSmem<T, BM, BN, BK, WGM, PAD>>;
   constexpr int VEC = 16 / sizeof(T);
   constexpr int SW = 4 * VEC;  // K covered by one MFMA step across the 4 lane groups
   constexpr int LDS = BK + VEC * PAD;
   constexpr int CLD = SM::CLD;
   constexpr int NT = 64 * WGM * WGN;  // threads: a WGM x WGN grid of waves
+  // direct loads in 4 waves: 32 x 32 x 16 MFMAs (one wave per SIMD keeps the
+  // matrix pipe full with them, not with the 16 x 16 x 32 ones: 2.05 against
+  // 1.33 PFLOP/s measured with 16 accumulators)
+  constexpr bool M32 = DL && WGM * WGN == 4;
   constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 16, TN = WN / 16;
   constexpr int KV = BK / VEC;
   constexpr int AV = BM * KV / NT, BV = BN * KV / NT;
@@ -559,16 +601,26 @@ __attribute__((amdgpu_waves_per_eu(gemm_waves_per_eu(BM, WGM * WGN, DL, (int)siz
     const int kbeg = s * kchunk, kend = min(K, kbeg + kchunk);
     const int nk = (kend - kbeg + BK - 1) / BK;
 
-    f32x4 acc[TM][TN];
+    f32x4 acc[M32 ? 1 : TM][M32 ? 1 : TN];
+    f32x16 acc32[M32 ? TM / 2 : 1][M32 ? TN / 2 : 1];
+    if constexpr (M32) {
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+      for (int i = 0; i < TM / 2; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < TN / 2; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc32[i][j][r] = 0.f;
+    } else {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
 
     if constexpr (DL) {
       // Operands go from global memory straight into LDS (buffer loads with
       // the LDS as destination: each wave instruction writes 1 KB, lane l at
-      // byte 16 l), two stages. A K-tile row is BK elements = 8 chunks of 16
+      // byte 16 l). A K-tile row is BK elements = 8 chunks of 16
       // bytes with no padding; chunk c of tile row r sits at chunk position
       // c ^ (r % 8), so the 16-byte fragment reads of 8 consecutive rows hit
       // distinct banks. Lane l of an instruction covering rows 8g .. 8g + 7
@@ -577,30 +629,232 @@ __attribute__((amdgpu_waves_per_eu(gemm_waves_per_eu(BM, WGM * WGN, DL, (int)siz
       // zero through the buffer range check.
       static_assert(sizeof(T) == 2 && BK / VEC == 8, "direct loads: 8 chunks per tile row");
       static_assert((BM / 8) % (NT / 64) == 0 && (BN / 8) % (NT / 64) == 0, "direct loads per wave");
-      __shared__ __attribute__((aligned(16))) T d1[(BM + BN) * BK];
+      // stage 0 is sm.d; every stage is an object of its own
+      __shared__ __attribute__((aligned(16))) T d1[SM::SZ];
+      __shared__ __attribute__((aligned(16))) T d2[NS == 4 ? SM::SZ : 8];
+      __shared__ __attribute__((aligned(16))) T d3[NS == 4 ? SM::SZ : 8];
+      // NS 2: a K-tile in two stages. NS 4: in a ring of four. NS 3: the A
+      // operand in two stages (sm.d, d1), the weights in four of their own
+      constexpr int BSZ = NS == 3 ? BN * BK : 8;
+      __shared__ __attribute__((aligned(16))) T w0[BSZ];
+      __shared__ __attribute__((aligned(16))) T w1[BSZ];
+      __shared__ __attribute__((aligned(16))) T w2[BSZ];
+      __shared__ __attribute__((aligned(16))) T w3[BSZ];
+      static_assert(NS == 2 || (M32 && (NS == 3 || NS == 4)), "stages");
       constexpr int LA = BM / 8 / (NT / 64), LB = BN / 8 / (NT / 64);  // instructions per wave
       const int lr = lane >> 3, lcol = ((lane & 7) ^ lr) * VEC;
-      uint32_t aoff[LA], boff[LB];
+      // byte offset of this lane's row and chunk; the instructions go on 8 rows
+      // at a time (in a running register, opaque to the compiler, which would
+      // keep every offset in a register of its own); rows past M or N lie past
+      // the buffers' ranges
+      const uint32_t abase = (uint32_t)(((size_t)(m0 + wave * LA * 8 + lr) * lda + lcol) * sizeof(T));
+      const uint32_t bbase = (uint32_t)(((size_t)(n0 + wave * LB * 8 + lr) * ldw + lcol) * sizeof(T));
+      const uint32_t astep = (uint32_t)(8 * lda * sizeof(T)), bstep = (uint32_t)(8 * ldw * sizeof(T));
+      auto issue_a = [&](T* d, int k0) {
+        uint32_t ao = lcol < kend - k0 ? abase + (uint32_t)k0 * sizeof(T) : OOB;
 #pragma unroll
-      for (int i = 0; i < LA; ++i) {
-        const int gm = m0 + (wave * LA + i) * 8 + lr;
-        aoff[i] = gm < M ? (uint32_t)(((size_t)gm * lda + lcol) * sizeof(T)) : OOB;
-      }
-#pragma unroll
-      for (int i = 0; i < LB; ++i) {
-        const int gn = n0 + (wave * LB + i) * 8 + lr;
-        boff[i] = gn < N ? (uint32_t)(((size_t)gn * ldw + lcol) * sizeof(T)) : OOB;
-      }
-      auto issue = [&](T* d, int k0) {
-        const bool kok = lcol < kend - k0;
-        const uint32_t soff = (uint32_t)k0 * sizeof(T);
-#pragma unroll
-        for (int i = 0; i < LA; ++i)
-          bld16_lds(ra_r, d + (wave * LA + i) * 8 * BK, kok ? aoff[i] : OOB, soff);
-#pragma unroll
-        for (int i = 0; i < LB; ++i)
-          bld16_lds(rb_r, d + (BM + (wave * LB + i) * 8) * BK, kok ? boff[i] : OOB, soff);
+        for (int i = 0; i < LA; ++i) {
+          bld16_lds(ra_r, d + (wave * LA + i) * 8 * BK, ao, 0);
+          ao += astep;
+          asm("" : "+v"(ao));
+        }
       };
+      auto issue_b = [&](T* d, int k0) {
+        uint32_t bo = lcol < kend - k0 ? bbase + (uint32_t)k0 * sizeof(T) : OOB;
+#pragma unroll
+        for (int i = 0; i < LB; ++i) {
+          bld16_lds(rb_r, d + (wave * LB + i) * 8 * BK, bo, 0);
+          bo += bstep;
+          asm("" : "+v"(bo));
+        }
+      };
+      auto issue = [&](T* d, int k0) {
+        issue_a(d, k0);
+        issue_b(d + BM * BK, k0);
+      };
+      if constexpr (M32) {
+        // Fragments of a 16-column slab s: tile row (lane % 32) + 32 i, chunk
+        // 2 s + lane / 32, at chunk position chunk ^ (lane % 8). Two sets of
+        // fragments: each slab's MFMAs run while the next slab's are read.
+        constexpr int TM2 = TM / 2, TN2 = TN / 2;
+        const int fr = lane & 31, fp = ((lane >> 5) ^ (lane & 7)) * VEC;
+        if constexpr (NS == 4) {
+          // Ring of four stages, three K-tiles in flight. A step waits for its
+          // own loads of K-tile `it` (the two behind it stay in flight) and for
+          // its fragment reads of the tile before, then one barrier: the tile
+          // is whole and the slot of the one before is free for the loads of
+          // tile it + 3. All fragments of the tile are read at once, into the
+          // other set, while the MFMAs of the tile before run. (A step of the
+          // register-staged tiles is a chain of read, multiply, store and
+          // barrier: 850 cycles for 64 x 64 x 64 with one workgroup on the CU,
+          // whatever its prefetch depth.) Loads past the end read zeros.
+          constexpr int FS = BK / 16;  // 16-column slabs
+          constexpr int NLD = LA + LB;
+          constexpr int WAITV = 2 * NLD;
+          constexpr int WAIT = (WAITV & 15) | ((WAITV >> 4) << 14) | 0x70;  // vmcnt WAITV, lgkmcnt 0
+          uint4 fa[2][FS][TM2], fb[2][FS][TN2];
+          auto rd = [&](const T* d, int set) {
+            const T* sa = d + (wm * WM + fr) * BK;
+            const T* sb = d + (BM + wn * WN + fr) * BK;
+#pragma unroll
+            for (int sl = 0; sl < FS; ++sl) {
+              const int cp = fp ^ (sl * 2 * VEC);
+#pragma unroll
+              for (int j = 0; j < TN2; ++j) fb[set][sl][j] = *(const uint4*)(sb + j * 32 * BK + cp);
+#pragma unroll
+              for (int i = 0; i < TM2; ++i) fa[set][sl][i] = *(const uint4*)(sa + i * 32 * BK + cp);
+            }
+          };
+          auto mm = [&](int set) {
+#pragma unroll
+            for (int sl = 0; sl < FS; ++sl)
+#pragma unroll
+              for (int i = 0; i < TM2; ++i)
+#pragma unroll
+                for (int j = 0; j < TN2; ++j) acc32[i][j] = mfma32_step(fa[set][sl][i], fb[set][sl][j], acc32[i][j]);
+          };
+          auto step = [&](const T* cur, T* nxt, int it, int set) {
+            __builtin_amdgcn_s_waitcnt(WAIT);
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            issue(nxt, kbeg + (it + 3) * BK);
+            rd(cur, set);
+            mm(1 - set);
+          };
+          __syncthreads();  // the previous tile's epilogue is done with the LDS
+          issue(sm.d, kbeg);
+          issue(d1, kbeg + BK);
+          issue(d2, kbeg + 2 * BK);
+#pragma unroll
+          for (int sl = 0; sl < FS; ++sl) {
+#pragma unroll
+            for (int i = 0; i < TM2; ++i) fa[1][sl][i] = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+            for (int j = 0; j < TN2; ++j) fb[1][sl][j] = make_uint4(0u, 0u, 0u, 0u);
+          }
+          // (whole rounds of four: the steps past nk multiply zeros)
+          for (int it = 0; it < nk; it += 4) {
+            step(sm.d, d3, it, 0);
+            step(d1, sm.d, it + 1, 1);
+            step(d2, d1, it + 2, 0);
+            step(d3, d2, it + 3, 1);
+          }
+          mm(1);
+          // the loads past the end have landed in every wave before the
+          // epilogue takes the LDS
+          __builtin_amdgcn_s_waitcnt(VMCNT0);
+          __syncthreads();
+        } else {
+        uint4 fa[2][TM2], fb[2][TN2];
+        auto rd = [&](const T* da, const T* db, int sl, int set) {
+          const T* sa = da + (wm * WM + fr) * BK + (fp ^ (sl * 2 * VEC));
+          const T* sb = db + (wn * WN + fr) * BK + (fp ^ (sl * 2 * VEC));
+#pragma unroll
+          for (int j = 0; j < TN2; ++j) fb[set][j] = *(const uint4*)(sb + j * 32 * BK);
+#pragma unroll
+          for (int i = 0; i < TM2; ++i) fa[set][i] = *(const uint4*)(sa + i * 32 * BK);
+        };
+        auto mm = [&](int set) {
+#pragma unroll
+          for (int i = 0; i < TM2; ++i)
+#pragma unroll
+            for (int j = 0; j < TN2; ++j) acc32[i][j] = mfma32_step(fa[set][i], fb[set][j], acc32[i][j]);
+        };
+        // The four slabs of a K-tile in LDS (da, db), each slab's fragments read
+        // while the slab before is multiplied (the first slab: the last of the
+        // K-tile before, in set 1), as one straight block in which the
+        // scheduler is told to put one fragment read and (at first) one load
+        // per few MFMAs.
+        auto slabs = [&](const T* da, const T* db) {
+          rd(da, db, 0, 0);
+          mm(1);
+          rd(da, db, 1, 1);
+          mm(0);
+          rd(da, db, 2, 0);
+          mm(1);
+          rd(da, db, 3, 1);
+          mm(0);
+          constexpr int RDS = TM2 + TN2, MMS = TM2 * TN2, LDS_N = LA + LB;
+          constexpr int PER = MMS / RDS > 0 ? MMS / RDS : 1;  // MFMAs per fragment read
+#pragma unroll
+          for (int ph = 0; ph < 4; ++ph) {
+#pragma unroll
+            for (int q = 0; q < RDS; ++q) {
+              __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                     // fragment read
+              if (ph * RDS + q < LDS_N) __builtin_amdgcn_sched_group_barrier(0x20, 1, 0);  // load
+              __builtin_amdgcn_sched_group_barrier(0x8, PER, 0);                     // MFMAs
+            }
+            if (MMS > PER * RDS) __builtin_amdgcn_sched_group_barrier(0x8, MMS - PER * RDS, 0);
+          }
+        };
+        if constexpr (NS == 3) {
+          // Activations (in L2) one K-tile ahead, weights (from HBM) two: a
+          // step waits for everything but the weights it requested itself
+          // (loads return in order, so those two steps old have to be there).
+          // Loads past the end read zeros, and are issued all the same.
+          constexpr int WAIT = (LB & 15) | ((LB >> 4) << 14) | 0x70;  // vmcnt LB, lgkmcnt 0
+          auto step = [&](const T* da, const T* db, T* na, T* nb, int it) {
+            issue_a(na, kbeg + (it + 1) * BK);
+            issue_b(nb, kbeg + (it + 2) * BK);
+            slabs(da, db);
+            __builtin_amdgcn_s_waitcnt(WAIT);
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+          };
+          __syncthreads();  // the previous tile's epilogue is done with the LDS
+          issue_a(sm.d, kbeg);
+          issue_b(w0, kbeg);
+          issue_b(w1, kbeg + BK);
+#pragma unroll
+          for (int i = 0; i < TM2; ++i) fa[1][i] = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+          for (int j = 0; j < TN2; ++j) fb[1][j] = make_uint4(0u, 0u, 0u, 0u);
+          __builtin_amdgcn_s_waitcnt(VMCNT0);
+          __syncthreads();
+          // (whole rounds of four: the steps past nk multiply zeros)
+          for (int it = 0; it < nk; it += 4) {
+            step(sm.d, w0, d1, w2, it);
+            step(d1, w1, sm.d, w3, it + 1);
+            step(sm.d, w2, d1, w0, it + 2);
+            step(d1, w3, sm.d, w1, it + 3);
+          }
+          mm(1);
+          // the loads past the end have landed in every wave before the
+          // epilogue takes the LDS
+          __builtin_amdgcn_s_waitcnt(VMCNT0);
+          __syncthreads();
+        } else {
+        // A step begins when K-tile `it` is in LDS (cur) and every wave has
+        // read the last slab of the one before (into set 1): its stage (nxt)
+        // is free, so the next K-tile's loads go out first and have the whole
+        // step to arrive.
+        auto step = [&](const T* cur, T* nxt, int it) {
+          issue(nxt, kbeg + (it + 1) * BK);
+          slabs(cur, cur + BM * BK);
+          __builtin_amdgcn_s_waitcnt(VMCNT0);
+          __syncthreads();
+        };
+        T* d0 = sm.d;
+        __syncthreads();  // the previous tile's epilogue is done with the LDS
+        issue(d0, kbeg);
+#pragma unroll
+        for (int i = 0; i < TM2; ++i) fa[1][i] = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+        for (int j = 0; j < TN2; ++j) fb[1][j] = make_uint4(0u, 0u, 0u, 0u);
+        __builtin_amdgcn_s_waitcnt(VMCNT0);
+        __syncthreads();  // tile 0 is in LDS
+        int it = 0;
+        for (; it + 1 < nk; it += 2) {
+          step(d0, d1, it);
+          step(d1, d0, it + 1);
+        }
+        if (it < nk) step(d0, d1, it);
+        mm(1);
+        }
+        }
+      } else {
       // fragment reads: tile row (lane % 16) + 16 i of the wave's rows, chunk
       // 4 ks + lane / 16, at chunk position chunk ^ (lane % 8)
       const int fr = lane & 15, fp = ((lane >> 4) ^ (lane & 7)) * VEC;
@@ -642,6 +896,7 @@ __attribute__((amdgpu_waves_per_eu(gemm_waves_per_eu(BM, WGM * WGN, DL, (int)siz
           __syncthreads();
         }
       }
+      }
       // GeGLU straight from the accumulators: gate column n (n % 32 < 16)
       // and its up column n + 16 sit in tiles j = 2g and 2g + 1 of the same
       // lane, so each lane forms its outputs in registers. The bf16 tile
@@ -652,9 +907,33 @@ __attribute__((amdgpu_waves_per_eu(gemm_waves_per_eu(BM, WGM * WGN, DL, (int)siz
       // no stage is read any more.
       if (reg_geglu) {
         constexpr int OLD = BN / 2 + 8;
-        static_assert(WGM == 2 && BM / 2 * OLD <= (BM + BN) * BK, "staging fits a stage");
+        static_assert(WGM == 2 && BM / 2 * OLD <= SM::SZ, "staging fits a stage");
         static_assert(TN % 2 == 0, "gate / up tiles in one wave");
+        T* d0 = sm.d;
+        const int tid = opaque(threadIdx.x), lane = tid & 63;  // (see the general epilogue)
         uint16_t* ob = (uint16_t*)(wm == 0 ? d0 : d1);
+        if constexpr (M32) {
+          // a 32 x 32 tile's lanes 0 .. 15 (and 32 .. 47) hold gate columns,
+          // the next 16 the up columns of the same rows; swapping lane rows
+          // between two registers (rows rr and rr + 1 of the tile) leaves the
+          // gates of both in one and their ups in the other
+#pragma unroll
+          for (int i = 0; i < TM / 2; ++i)
+#pragma unroll
+            for (int g = 0; g < TN / 2; ++g) {
+              // (one tile at a time: all of them at once do not fit the registers)
+              __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+              for (int r = 0; r < 16; r += 2) {
+                auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc32[i][g][r]),
+                                                           __float_as_uint(acc32[i][g][r + 1]), false, false);
+                const float ga = __uint_as_float(sw[0]), up = __uint_as_float(sw[1]);
+                const int lrow = i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3) + ((lane >> 4) & 1);
+                const int ocol = wn * (WN / 2) + 16 * g + (lane & 15);
+                ob[lrow * OLD + ocol] = f2bf(gelu_tanh(ga) * up);
+              }
+            }
+        } else {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -665,6 +944,7 @@ __attribute__((amdgpu_waves_per_eu(gemm_waves_per_eu(BM, WGM * WGN, DL, (int)siz
               const int ocol = wn * (WN / 2) + 16 * g + (lane & 15);
               ob[lrow * OLD + ocol] = f2bf(gelu_tanh(acc[i][2 * g][r]) * acc[i][2 * g + 1][r]);
             }
+        }
         __syncthreads();
         constexpr int CPR = BN / 16;  // 16-byte chunks per output row
         const int ncols = N / 2, c00 = n0 / 2;
@@ -778,6 +1058,10 @@ __attribute__((amdgpu_waves_per_eu(gemm_waves_per_eu(BM, WGM * WGN, DL, (int)siz
     }
 
     if (reg_geglu) continue;  // stored above
+    // The epilogue's addresses come from a thread index that the compiler
+    // cannot see through: it would form them once before the tile loop and
+    // keep them through the K loop in registers that there are none of.
+    const int tid = DL ? opaque(threadIdx.x) : (int)threadIdx.x, lane = tid & 63;
     // epilogue in 16-row slices: slice i of every wave row goes through LDS,
     // then all threads apply the epilogue with row-contiguous stores
     float* P = (ekind == EPI_PART ? (float*)e.out : part) + (size_t)s * M * N;
@@ -827,13 +1111,22 @@ __attribute__((amdgpu_waves_per_eu(gemm_waves_per_eu(BM, WGM * WGN, DL, (int)siz
         if (n0 + c8 * 8 + k < N) bv[k] = e.bias[n0 + c8 * 8 + k];
     }
     auto slice = [&](auto ic) {
-      const int i = ic;
+      constexpr int i = ic;
       __syncthreads();
+      if constexpr (M32) {
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
+        for (int j = 0; j < TN / 2; ++j)
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-          sm.c[(wm * 16 + (lane >> 4) * 4 + r) * CLD + wn * WN + j * 16 + (lane & 15)] = acc[i][j][r];
+          for (int r = 0; r < 8; ++r)
+            sm.c[(wm * 16 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3)) * CLD + wn * WN + j * 32 + (lane & 31)] =
+                acc32[i / 2][j][(i & 1) * 8 + r];
+      } else {
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            sm.c[(wm * 16 + (lane >> 4) * 4 + r) * CLD + wn * WN + j * 16 + (lane & 15)] = acc[i][j][r];
+      }
       __syncthreads();
       if (vec8) {
         const int chunks = WGM * 16 * oc8;
@@ -1861,19 +2154,19 @@ void plan_tile(const GemmDesc& g, const GemmPlan& p, int* bm, int* bn) {
 }
 
 template <typename T, int BM, int BN, int BK, int WGM = 2, int WGN = 2, int PD = 1, int PAD = VLA_GEMM_LDS_PAD,
-          bool DL = false, int KIND = -1>
+          bool DL = false, int KIND = -1, int NS = 2>
 static hipError_t run_gemm_t(const GemmDesc& g, const GemmPlan& p, const Scratch& s,
                              const LaunchCaps& caps, hipStream_t st) {
   const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
   const int kblocks = (g.K + BK - 1) / BK;
   const int kchunk = ((kblocks + p.splits - 1) / p.splits) * BK;
-  int grid = p.tiles;
+  int grid = tiles_m * tiles_n * p.splits;
   if (caps.max_wgs > 0) grid = std::min(grid, caps.max_wgs);
   // row-tile bands sized so a band's A K-range takes about half of an XCD's
   // 4 MB L2
   const size_t band_bytes = (size_t)BM * kchunk * sizeof(T);
   const int group_m = std::max(1, std::min(tiles_m, (int)((2u << 20) / std::max<size_t>(band_bytes, 1))));
-  hipExtLaunchKernelGGL((k_gemm<T, BM, BN, BK, WGM, WGN, PD, PAD, DL, KIND>), dim3(grid), dim3(64 * WGM * WGN), 0, st,
+  hipExtLaunchKernelGGL((k_gemm<T, BM, BN, BK, WGM, WGN, PD, PAD, DL, KIND, NS>), dim3(grid), dim3(64 * WGM * WGN), 0, st,
                         caps.ev_start,
                         caps.ev_stop, 0, (const T*)g.A, g.lda, (const T*)g.W, g.ldw, g.M, g.N,
                         g.K, kchunk, p.splits, tiles_m, tiles_n, group_m, g.epi, s.ptr);
@@ -1888,15 +2181,40 @@ static hipError_t run_gemm_t(const GemmDesc& g, const GemmPlan& p, const Scratch
 
 // the 4-wave tiles: the decoder layers' epilogues (QKV-RoPE, GeGLU, split-K
 // partials) get their own instantiations, the rest share the run-time one
-template <typename T, int BM, int BN, int BK, int PD, int PAD = VLA_GEMM_LDS_PAD, bool DL = false>
+template <typename T, int BM, int BN, int BK, int PD, int PAD = VLA_GEMM_LDS_PAD, bool DL = false, int NS = 2>
 static hipError_t run_gemm_kind(const GemmDesc& g, const GemmPlan& p, const Scratch& s, const LaunchCaps& caps,
                                 hipStream_t st) {
   switch (g.epi.kind) {
-    case EPI_QKV_ROPE: return run_gemm_t<T, BM, BN, BK, 2, 2, PD, PAD, DL, EPI_QKV_ROPE>(g, p, s, caps, st);
-    case EPI_GEGLU: return run_gemm_t<T, BM, BN, BK, 2, 2, PD, PAD, DL, EPI_GEGLU>(g, p, s, caps, st);
-    case EPI_PART: return run_gemm_t<T, BM, BN, BK, 2, 2, PD, PAD, DL, EPI_PART>(g, p, s, caps, st);
-    default: return run_gemm_t<T, BM, BN, BK, 2, 2, PD, PAD, DL>(g, p, s, caps, st);
+    case EPI_QKV_ROPE: return run_gemm_t<T, BM, BN, BK, 2, 2, PD, PAD, DL, EPI_QKV_ROPE, NS>(g, p, s, caps, st);
+    case EPI_GEGLU: return run_gemm_t<T, BM, BN, BK, 2, 2, PD, PAD, DL, EPI_GEGLU, NS>(g, p, s, caps, st);
+    case EPI_PART: return run_gemm_t<T, BM, BN, BK, 2, 2, PD, PAD, DL, EPI_PART, NS>(g, p, s, caps, st);
+    default: return run_gemm_t<T, BM, BN, BK, 2, 2, PD, PAD, DL, -1, NS>(g, p, s, caps, st);
   }
+}
+
+// A plan fixes the tile that is reported and the K-splits; the launch may run
+// the same sums in workgroups of another size (same BK, same splits, same
+// order along K: bit for bit the same result).
+//
+// One tile of 320 rows where the 128 tile would take three of 128 and leave
+// most of the third empty (257 .. 320 rows), if the columns make at least 3/4
+// of a round: 305 x 32768 x 2048 with GeGLU 65 us against 84 us; at 16384
+// columns (128 workgroups, half the chip) the 128 tile's 43 us stand against
+// 50 us.
+static bool tall(const GemmDesc& g, const GemmPlan& p) {
+  return p.splits == 1 && g.M > 256 && g.M <= 320 && g.N >= NUM_CU_PLAN * 3 / 4 * 128;
+}
+
+// Whether a plan of 256 x 256 tiles runs in 128 x 128 ones: a round of 256
+// workgroups of the former takes as long as 1.7 rounds of 512 of the latter,
+// which fill the last round better (6664 x 2560 x 2048, 270 tiles, 103 us
+// against 120 us; 2440 x 8192 x 2048, 320 tiles, 109 us against 120 us; where
+// both fill their rounds alike, 6144 x 4304 x 1152, 97.4 us against 96.8 us).
+static bool finer(const GemmDesc& g, const GemmPlan& p) {
+  const long long t128 = (long long)((g.M + 127) / 128) * ((g.N + 127) / 128) * p.splits;
+  const long long r256 = (p.tiles + NUM_CU_PLAN - 1) / NUM_CU_PLAN;
+  const long long r128 = (t128 + 2 * NUM_CU_PLAN - 1) / (2 * NUM_CU_PLAN);
+  return 17 * r256 >= 10 * r128;
 }
 
 hipError_t launch_gemm(const GemmDesc& g, const Scratch& s, const LaunchCaps& caps,
@@ -1909,10 +2227,28 @@ hipError_t launch_gemm(const GemmDesc& g, const Scratch& s, const LaunchCaps& ca
     return hipErrorInvalidValue;
   }
   if (g.dtype == DT_BF16) {
-    switch (p.cfg) {
-      case 0: return run_gemm_kind<uint16_t, 128, 128, 64, 3>(g, p, s, caps, st);
-      case 1: return run_gemm_kind<uint16_t, 64, 64, 64, 2>(g, p, s, caps, st);
-      case 3: return run_gemm_t<uint16_t, 256, 256, 64, 2, 4, 1, 0, true>(g, p, s, caps, st);
+    // The direct loads to LDS move whole 16-byte pieces, and step through the
+    // rows past a K-range in 32-bit offsets: operands that do not start on
+    // 16 bytes, or with rows of more than 2 MB, go through registers.
+    if (p.cfg != 2 && ((((uintptr_t)g.A | (uintptr_t)g.W) & 15) || std::max(g.lda, g.ldw) > 1 << 20))
+      return run_gemm_t<uint16_t, 64, 64, 64, 2, 2, 2>(g, p, s, caps, st);
+    switch (p.cfg == 3 && finer(g, p) ? 0 : p.cfg) {
+      case 0:
+        if (tall(g, p)) return run_gemm_kind<uint16_t, 320, 128, 64, 1, 0, true, 3>(g, p, s, caps, st);
+        return run_gemm_kind<uint16_t, 128, 128, 64, 1, 0, true, 2>(g, p, s, caps, st);
+      case 1:
+        // up to two workgroups per CU the ring of four stages, whose loads are
+        // three K-tiles ahead (400 x 1024 x 1024 8.9 us, in two stages 10.4 us);
+        // beyond, two stages leave room for the further workgroups
+        if (p.tiles <= 2 * NUM_CU_PLAN) return run_gemm_kind<uint16_t, 64, 64, 64, 1, 0, true, 4>(g, p, s, caps, st);
+        return run_gemm_kind<uint16_t, 64, 64, 64, 1, 0, true, 2>(g, p, s, caps, st);
+      case 3:
+        switch (g.epi.kind) {
+          case EPI_PART: return run_gemm_t<uint16_t, 256, 256, 64, 2, 2, 1, 0, true, EPI_PART>(g, p, s, caps, st);
+          case EPI_GELU: return run_gemm_t<uint16_t, 256, 256, 64, 2, 2, 1, 0, true, EPI_GELU>(g, p, s, caps, st);
+          case EPI_GEGLU: return run_gemm_t<uint16_t, 256, 256, 64, 2, 4, 1, 0, true, EPI_GEGLU>(g, p, s, caps, st);
+          default: return run_gemm_t<uint16_t, 256, 256, 64, 2, 4, 1, 0, true>(g, p, s, caps, st);
+        }
       default: return run_gemm_kind<uint16_t, 32, 64, 64, 2>(g, p, s, caps, st);
     }
   }

@@ -112,3 +112,66 @@ def cache_layout(k, v):
     K[ki.reshape(-1)] = k.reshape(-1)
     W[vi.reshape(-1)] = v.reshape(-1)
     return K, W
+
+
+# (kind, M, N, K, row padding): each launch of the tiled GEMM, at its edges.
+# 64 x 64 in the ring of four (one K-tile and a piece, three, four, five; one
+# row and one column past a tile; split K) and, past 512 tiles, in two stages;
+# 128 x 128 with whole and ragged last tiles; the 320-row tile from 257 to 320
+# rows; 256 x 256 plans that run in 128 x 128 tiles or stay; 4-wave GELU
+@pytest.mark.parametrize("kind,M,N,K,pad", [
+    ("f32", 33, 8, 8, 0), ("f32", 64, 64, 72, 8), ("f32", 65, 72, 192, 0), ("f32", 129, 200, 256, 8),
+    ("f32", 100, 1032, 328, 0), ("f32", 40, 64, 4104, 0), ("f32", 400, 1024, 1024, 64), ("f32", 520, 4168, 136, 0),
+    ("f32", 256, 16384, 64, 0), ("f32", 385, 10248, 200, 8), ("f32", 257, 24576, 136, 0), ("f32", 320, 24584, 264, 8),
+    ("f32", 321, 24576, 72, 0), ("f32", 1025, 12936, 72, 0), ("f32", 2440, 8192, 328, 0), ("f32", 4096, 4096, 136, 8),
+    ("geglu", 400, 8192, 200, 0), ("geglu", 305, 32768, 136, 0), ("geglu", 2440, 32768, 136, 0),
+    ("geglu", 100, 1056, 328, 0), ("gelu", 2048, 4304, 136, 0), ("gelu", 4100, 4304, 200, 0), ("t", 256, 3456, 1152, 0),
+])
+def test_gemm_tiles(V, kind, M, N, K, pad):
+    import gpu_util as g
+    g.say(f"gemm {kind} {M}x{N}x{K} +{pad}")
+    gen = torch.Generator(device="cuda").manual_seed(M * 7919 + N * 31 + K)
+    bias = torch.randn(N, generator=gen, device="cuda") if kind != "geglu" else None
+    # rows of K + pad elements, the padding infinite: nothing of it may be read into a sum
+    ops = []
+    for rows, scale in ((M, 1.0), (N, 0.05)):
+        buf = torch.full((rows * (K + pad) + 8,), float("inf"), dtype=torch.bfloat16, device="cuda")
+        val = (scale * torch.randn(rows, K, generator=gen, device="cuda")).bfloat16()
+        ops.append((buf, val))
+
+    def run(off):
+        """The operands start `off` elements past 16 bytes."""
+        for buf, val in ops:
+            buf[off:off + val.shape[0] * (K + pad)].view(val.shape[0], K + pad)[:, :K] = val
+        A, W = (buf[off:] for buf, _ in ops)
+        out = torch.full((M, N // 2 if kind == "geglu" else N), float("nan"), device="cuda",
+                         dtype=torch.float32 if kind == "f32" else torch.bfloat16)
+        if kind == "f32":
+            V.vla_debug_gemm(1, M, N, K, A, K + pad, W, K + pad, bias, out)
+        else:
+            V.vla_debug_gemm_epi(1, M, N, K, A, W, kind, bias=bias, out=out)
+        torch.cuda.synchronize()
+        return out
+
+    out = run(0)
+    a, w = (val.double() for _, val in ops)
+    v, mag = a @ w.T, a.abs() @ w.abs().T
+    delta = 2 * K * 2.0 ** -24 * mag
+    if kind == "geglu":
+        (gt, up), (dg, du) = v.chunk(2, 1), delta.chunk(2, 1)  # W holds the gate rows, then the up rows
+        act = 0.5 * gt * (1 + torch.tanh((2 / np.pi) ** 0.5 * (gt + 0.044715 * gt ** 3)))
+        ref = act * up
+        delta = up.abs() * 1.13 * dg + act.abs() * du + 1.13 * dg * du + 2.0 ** -20 * ref.abs()
+    else:
+        ref = v + bias.double()
+        delta = delta + 2.0 ** -22 * (v.abs() + bias.abs())
+        if kind == "gelu":
+            ref = 0.5 * ref * (1 + torch.tanh((2 / np.pi) ** 0.5 * (ref + 0.044715 * ref ** 3)))
+            delta = 1.13 * delta + 2.0 ** -20 * ref.abs()
+    # (1e-6: gelu's tail, where 1 + tanh loses what tanh rounds away)
+    bound = delta + (0 if kind == "f32" else 2.0 ** -8) * (ref.abs() + delta) + 1e-6
+    err = (out.double() - ref).abs()
+    assert bool((err <= bound).all()), (float(err.max()), float((err / bound).max()))
+    # operands 8 bytes past a 16-byte boundary go through the register-staged
+    # tile: the same sums, bit for bit
+    assert torch.equal(run(4), out)
