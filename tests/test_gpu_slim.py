@@ -175,3 +175,37 @@ def test_gemm_tiles(V, kind, M, N, K, pad):
     # operands 8 bytes past a 16-byte boundary go through the register-staged
     # tile: the same sums, bit for bit
     assert torch.equal(run(4), out)
+
+
+# Vectors that are there but neutral (zero bias and shift, a column scale of
+# one) and splits that are there but zero take other variants of the norms:
+# the same sums, bit for bit. Rows of one wave (d <= 1024) and of a workgroup.
+@pytest.mark.parametrize("dtype,rows,d,rms", [(1, 1, 8, 1), (1, 400, 1024, 1), (1, 17, 1028, 0), (1, 5000, 2048, 1),
+                                              (0, 3, 256, 0), (0, 70, 2048, 0)])
+def test_norm_variants(V, dtype, rows, d, rms):
+    import gpu_util as g
+    g.say(f"norm variants {dtype} {rows}x{d} rms {rms}")
+    gen = torch.Generator(device="cuda").manual_seed(rows + d)
+    r = lambda *s: torch.randn(*s, generator=gen, device="cuda")
+    x0, gain, zero, one = r(rows, d), 1 + 0.1 * r(d), torch.zeros(d, device="cuda"), torch.ones(d, device="cuda")
+    part = torch.zeros(9, rows, d, device="cuda")
+    part[:4] = 0.25 * r(4, rows, d)
+
+    def run(splits, vecs):
+        x = x0.clone()
+        out = torch.full((rows, d), float("nan"), dtype=torch.bfloat16 if dtype else torch.float32, device="cuda")
+        V.vla_debug_norm(dtype, rows, d, x, d, part if splits else None, splits, zero if vecs else None,
+                         one if vecs and splits else None, gain, 0, zero if vecs else None, rms, out, d, 0)
+        torch.cuda.synchronize()
+        return x, out
+
+    for counts in ((0,), (4, 5, 8, 9)):
+        got = [run(sp, v) for sp in counts for v in (False, True)]
+        x = x0.double() + (part[:4].double().sum(0) if counts[0] else 0)
+        c = x if rms else x - x.mean(1, keepdim=True)
+        ref = c / torch.sqrt((c * c).mean(1, keepdim=True) + 1e-6) * gain.double()
+        # sums of at most 2048 values of a row of standard deviation ~1, and one rounding
+        bound = (2.0 ** -8 if dtype else 2.0 ** -23) * ref.abs() + 64 * 2.0 ** -23 * (1 + ref.abs())
+        assert bool(((got[0][1].double() - ref).abs() <= bound).all())
+        for y in got[1:]:
+            assert torch.equal(y[0], got[0][0]) and torch.equal(y[1], got[0][1])
