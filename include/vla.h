@@ -297,7 +297,8 @@ int vla_debug_attention(int32_t dtype, int32_t Sq, int32_t nq, int32_t nkv, int3
  * head's kernel (M <= 64): W is converted to MFMA fragment order and A to
  * the row-block operand layout, and operand-type outputs are written in that
  * layout and returned row-major. skinny = 0 runs the tiled kernel with the
- * tile the planner picks for M and N. plan_out (host, may be NULL) receives
+ * tile the planner picks for M and N (the launch may deal its sums out in
+ * workgroups of another size: the results are the same). plan_out (host, may be NULL) receives
  * the tile's rows and columns (0 and 32 for the skinny kernel) and the
  * split-K factor. Blocking; allocates temporaries. */
 #define VLA_DEBUG_EPI_BIAS 0

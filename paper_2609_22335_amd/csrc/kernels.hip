@@ -2050,9 +2050,10 @@ GemmPlan plan_gemm(const GemmDesc& g) {
     return p;
   }
   const TileCfg* cfgs = g.dtype == DT_BF16 ? kBf16Cfg : kF32Cfg;
-  // The 256 x 256 tile does about twice the work per CU-cycle of the
-  // 128 x 128 tile (one workgroup per CU at ~3,600 cycles per K-step against
-  // two at ~3,900), so where it leaves CUs idle it can still win: with the
+  // The plan prices the tiles in cycles per K-step (256 x 256, one workgroup
+  // per CU: ~3,600; two of 128 x 128: ~3,900, measured with loads through
+  // registers; what the launch makes of a 256 plan now is finer()). Where the
+  // 256 tile leaves CUs idle it can still win: with the
   // epilogues that take its short paths (GeGLU, store, GELU, swish) it is
   // also chosen when its rounds of tiles take fewer cycles than the 128
   // tile's, counting ~18K cycles of epilogue per 256 tile. The tile does not
