@@ -188,6 +188,11 @@ __device__ __forceinline__ void bld16_lds(Rsrc r, void* dst, uint32_t off, uint3
 // s_waitcnt operand that waits for every outstanding vector memory load
 // (vmcnt 0; expcnt and lgkmcnt left at their maxima)
 constexpr int VMCNT0 = 0x0F70;
+// sched_barrier mask: vector memory operations stay on their side, the rest
+// may cross. It stands between two groups of loads into LDS of which a counted
+// vmcnt waits for the first only: they write different objects through
+// independent addresses, so nothing else keeps the compiler from mixing them.
+constexpr int LDS_ORDER = 0x78F;
 __device__ __forceinline__ float bld1(Rsrc r, uint32_t off) {
   return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
 }
@@ -724,7 +729,9 @@ __attribute__((amdgpu_waves_per_eu(gemm_waves_per_eu(BM, WGM * WGN, DL, (int)siz
           };
           __syncthreads();  // the previous tile's epilogue is done with the LDS
           issue(sm.d, kbeg);
+          __builtin_amdgcn_sched_barrier(LDS_ORDER);
           issue(d1, kbeg + BK);
+          __builtin_amdgcn_sched_barrier(LDS_ORDER);
           issue(d2, kbeg + 2 * BK);
 #pragma unroll
           for (int sl = 0; sl < FS; ++sl) {
@@ -796,6 +803,7 @@ __attribute__((amdgpu_waves_per_eu(gemm_waves_per_eu(BM, WGM * WGN, DL, (int)siz
           constexpr int WAIT = (LB & 15) | ((LB >> 4) << 14) | 0x70;  // vmcnt LB, lgkmcnt 0
           auto step = [&](const T* da, const T* db, T* na, T* nb, int it) {
             issue_a(na, kbeg + (it + 1) * BK);
+            __builtin_amdgcn_sched_barrier(LDS_ORDER);
             issue_b(nb, kbeg + (it + 2) * BK);
             slabs(da, db);
             __builtin_amdgcn_s_waitcnt(WAIT);
