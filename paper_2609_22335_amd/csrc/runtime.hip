@@ -1160,7 +1160,7 @@ static int run_prefill_n(const Run& r, const vla_frame* f, int n, vla_ctx* const
     VLA_TRY(run_norm(r, nd));
   }
   // prefix of frame i at rows i * P: [projected image tokens; text * sqrt(d);
-  // state projection]
+  // state projection; the cognition-token head's learned token]
   for (int i = 0; i < n; ++i) {
     float* xl = w.xl + (size_t)i * P * dl;
     VLA_TRY(gemm(r, "proj", (char*)w.h + (size_t)i * d.nimg * d.kproj * m->esz, d.kproj, m->proj_w, d.nimg,
@@ -1173,7 +1173,7 @@ static int run_prefill_n(const Run& r, const vla_frame* f, int n, vla_ctx* const
       void* sb = (char*)w.sbuf + (size_t)i * d.s_pad * m->esz;
       HIP_TRY(launch_cvt_pad(m->dt, f[i].state, 1, c.state_dim, sb, d.s_pad, false, nullptr, r.st));
       VLA_TRY(gemm(r, "state", sb, d.s_pad, m->state_w, 1, dl, d.s_pad,
-                   epi_kind(EPI_F32, xl + (size_t)(P - 1) * dl, dl, m->f32(m->state_b))));
+                   epi_kind(EPI_F32, xl + (size_t)(d.nimg + c.n_text) * dl, dl, m->f32(m->state_b))));
     }
   }
   // LM prefill writing the caches

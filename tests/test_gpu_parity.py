@@ -528,6 +528,26 @@ def test_cog_phases_vs_oracle(V, name, cfg):
     assert err <= chunk_bound(cfg, want)
 
 
+@pytest.mark.parametrize("dtype", [synth.F32, synth.BF16], ids=["f32", "bf16"])
+def test_cog_with_robot_state(V, dtype):
+    """Cognition-token head with a robot state: the prefix ends in the state's
+    row and then the cognition token. One frame against the oracle; two frames
+    in one prefill equal to it bit for bit."""
+    cfg = dict(synth.micro_cog(dtype), state_dim=5)
+    test_cog_phases_vs_oracle(V, f"micro-cog-state-{dtype}", cfg)
+    g = G()
+    frames = [g.DevFrame(synth.make_frame(cfg, r, 0)) for r in range(2)]
+    out = torch.empty(2, cfg["chunk_len"], cfg["action_dim"], device="cuda")
+    with g.model(cfg, 0) as m:
+        V.vla_pipeline_run(m, [f.c for f in frames], torch.stack([f.noise for f in frames]), 2, mode="serial",
+                           actions=out, vlm_batch=2)
+        torch.cuda.synchronize()
+        for r in range(2):
+            one, _ = g.run_frame(m, cfg, synth.make_frame(cfg, r, 0))
+            assert np.array_equal(out[r].cpu().numpy().astype(np.float64).ravel(), one.ravel()), r
+
+
+
 @pytest.mark.timeout(900)
 def test_cogact_full_size_vs_oracle(V):
     """The CogACT-shaped VLA at its real sizes (PaliGemma-shaped VLM with the
