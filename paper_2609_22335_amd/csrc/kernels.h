@@ -315,8 +315,9 @@ struct AttnKvDesc {
   bool solo = false;
 };
 hipError_t launch_attention_kv(const AttnKvDesc& d, const LaunchCaps& caps, hipStream_t st);
-// Floats of partials (and, in *counters, the counters) a launch of these
-// shapes needs for its key splits; 0 when it runs unsplit.
+// Floats of partials (and, in *counters, the counters) that launches of these
+// shapes and of up to `frames` frames need for their key splits; 0 when they
+// run unsplit. (bf16 at head dims 128 and 256: only solo launches are split.)
 size_t attn_kv_split_floats(int dtype, int frames, int Sq, int nq, int nkv, int hd, int S0, int S1, int* counters);
 hipError_t launch_attention(const AttnDesc& a, const Scratch& s, const LaunchCaps& caps, hipStream_t st);
 

@@ -3308,8 +3308,30 @@ static void attn2_split(Attn2Args& a, float* part, size_t part_floats, unsigned*
 }
 
 // k_attn3: bf16, head dim exactly 128 or 256 (no unused head-dim positions to
-// mask). The chunk is the smallest that holds the call's key blocks.
-static bool use_attn3(int dtype, int hd) { return dtype == DT_BF16 && (hd == 128 || hd == 256); }
+// mask).
+static bool attn3_hd(int dtype, int hd) { return dtype == DT_BF16 && (hd == 128 || hd == 256); }
+// It works in chunks of 16 key blocks, a last one that is nearly empty
+// costing as much as a full one, and its parts of a tile each go through all
+// keys; k_attn2 pays by the block and, in a solo launch (which brings room for
+// the partials), deals the blocks of a tile out to workgroups. So k_attn3
+// takes up to one chunk, and beyond it (us, k_attn2 / k_attn3):
+// * head dim 128: 50 queries of 8 heads, solo, 640 keys 8.2 / 9.0, 883 keys 9.5
+//   / 9.7, 1024 keys 10.2 / 9.7, 1536 keys 11.0 / 12.9; 513 queries of 513
+//   keys 14.4 / 19.3, 1024 of 1024 20.1 / 20.9: only two full chunks, solo;
+// * head dim 256, solo: 1024 keys 16.2 / 12.1; 1536 keys 17.2 / 16.6, one query
+//   14.5 / 16.9; 2048 keys 17.5 / 21.1: two chunks, or three with 8 tiles;
+// * head dim 256, not solo: few tiles (50 queries of 8 heads) 833 keys 17.4 /
+//   13.3, 3000 keys 43 / 34; many tiles 513 of 513 26.3 / 30.6, 833 of 833
+//   33.9 / 31.7, 1200 of 1200 61.6 / 63.4: where the chunks are filled to 5/6.
+// Whether a launch is solo, and the sizes of one frame: the frame count does
+// not enter, so a frame's sums are the same in every group.
+static bool use_attn3(int dtype, int hd, int nblk, int tiles1, bool solo) {
+  if (!attn3_hd(dtype, hd)) return false;
+  if (nblk <= 16) return true;
+  if (hd == 128) return solo && nblk > 28 && nblk <= 32;
+  if (solo) return nblk <= 32 || (nblk <= 48 && tiles1 >= 8);
+  return tiles1 <= 64 || 6 * nblk >= 5 * ((nblk + 15) / 16 * 16);
+}
 static hipError_t run_attn3(Attn2Args& a, bool solo, const LaunchCaps& caps, hipStream_t st) {
   a.nsplit = 1;
   // One tile's K and V come through one CU at about 50 bytes per clock (384 KB
@@ -3412,18 +3434,26 @@ hipError_t launch_attention_kv(const AttnKvDesc& d, const LaunchCaps& caps, hipS
   a.nb1 = (d.S1 + 31) / 32;
   a.rtiles = (d.Sq * (d.nq / d.nkv) + 15) / 16;
   a.scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)d.hd));
-  if (use_attn3(d.dtype, d.hd)) return run_attn3(a, d.solo && d.frames == 1, caps, st);
-  if (d.dtype == DT_BF16) return run_attn2_t<uint16_t>(a, hdp, caps, st, d.part, d.part_floats, d.cnt, d.cnt_n);
+  const bool solo = d.solo && d.frames == 1;
+  if (use_attn3(d.dtype, d.hd, a.nb0 + a.nb1, a.rtiles * a.nkv, solo)) return run_attn3(a, solo, caps, st);
+  // Past k_attn3's range a launch that may be batched stays unsplit: the split
+  // count depends on the frames.
+  const bool split = solo || !attn3_hd(d.dtype, d.hd);
+  if (d.dtype == DT_BF16)
+    return run_attn2_t<uint16_t>(a, hdp, caps, st, split ? d.part : nullptr, d.part_floats, d.cnt, d.cnt_n);
   return run_attn2_t<float>(a, hdp, caps, st, d.part, d.part_floats, d.cnt, d.cnt_n);
 }
 
 size_t attn_kv_split_floats(int dtype, int frames, int Sq, int nq, int nkv, int hd, int S0, int S1, int* counters) {
   const int hdp = attn_hdp(hd, dtype);
   *counters = 0;
-  if (hdp < 0 || nkv <= 0 || nq % nkv || use_attn3(dtype, hd)) return 0;
+  if (hdp < 0 || nkv <= 0 || nq % nkv) return 0;
   const int nw = dtype == DT_BF16 ? (hdp * 2 >= 512 ? 4 : 8) : (hdp * 4 >= 512 ? 4 : 8);
   const int nblk = (S0 + 31) / 32 + (S1 + 31) / 32;
-  const int tiles = (Sq * (nq / nkv) + 15) / 16 * nkv * frames;
+  const int tiles1 = (Sq * (nq / nkv) + 15) / 16 * nkv;
+  // at k_attn3's head dims only a solo launch past its range is split
+  if (attn3_hd(dtype, hd) && use_attn3(dtype, hd, nblk, tiles1, true)) return 0;
+  const int tiles = attn3_hd(dtype, hd) ? tiles1 : tiles1 * frames;
   int bps;
   const int ns = attn2_plan(nblk, nw, tiles, &bps);
   *counters = ns > 1 ? tiles : 0;

@@ -96,6 +96,44 @@ def test_cache_attention_chunks(V, Sq, nq, nkv, hd, S0, S1):
     assert (err <= 2.0 ** -8 * np.abs(ref) + 2e-4).all(), err.max()
 
 
+# The same on both sides of each line between the two cache-attention kernels:
+# one chunk of 16 key blocks and one block more, two full chunks, the second
+# nearly full or not, three chunks with 8 query tiles and with fewer, and the
+# long keys that k_attn2 splits over workgroups
+@pytest.mark.parametrize("Sq,nq,nkv,hd,S0,S1", [
+    (50, 8, 1, 128, 512, 0), (50, 8, 1, 128, 513, 0), (17, 8, 2, 128, 896, 0), (17, 8, 2, 128, 870, 27),
+    (3, 16, 16, 128, 1024, 0), (50, 8, 1, 128, 1000, 25), (1, 8, 1, 128, 3000, 0), (50, 8, 1, 256, 1024, 0),
+    (50, 8, 1, 256, 1025, 0), (16, 8, 1, 256, 1480, 50), (15, 8, 1, 256, 1480, 50), (50, 4, 4, 256, 1537, 0),
+    (1, 1, 1, 256, 3000, 17),
+])
+def test_cache_attention_kernel_choice(V, Sq, nq, nkv, hd, S0, S1):
+    test_cache_attention_chunks(V, Sq, nq, nkv, hd, S0, S1)
+
+
+def test_long_prefix_bf16_heads(V):
+    """A model whose key blocks lie past the first chunk: one frame against
+    the oracle; action groups of four, three and two bit for bit alike
+    (launches that may be batched take one kernel, unsplit, whatever the group)."""
+    import gpu_util as g
+    import synth
+    import test_gpu_parity as P
+    cfg = dict(synth.micro(synth.BF16), head_dim=128, n_text=560)
+    P.test_phases_vs_oracle(V, "micro-bf16-hd128-long", cfg)
+    frames = [g.DevFrame(synth.make_frame(cfg, 0, r)) for r in range(5)]
+    noise = torch.stack([f.noise for f in frames])
+    got = []
+    with g.model(cfg, 0) as m:
+        for batch in (4, 3, 2):  # (five frames: 4 + 1, 3 + 2, 2 + 2 + 1)
+            out = torch.full_like(noise, float("nan"))
+            V.vla_pipeline_run(m, [f.c for f in frames], noise, 5, mode="serial", actions=out, act_batch=batch,
+                               vlm_batch=2)
+            torch.cuda.synchronize()
+            got.append(out)
+    # (a group of one frame takes the one-frame action phase)
+    assert bool(torch.isfinite(got[0]).all())
+    assert torch.equal(got[0][:4], got[1][:4]) and torch.equal(got[0][:4], got[2][:4])
+
+
 def cache_layout(k, v):
     """bf16 K / V rows [S, nkv, hd] in the KV-cache layout (include/vla.h);
     unused K positions hold NaN, unused V positions zero."""
