@@ -2209,9 +2209,11 @@ static hipError_t run_gemm_kind(const GemmDesc& g, const GemmPlan& p, const Scra
 // most of the third empty (257 .. 320 rows), if the columns make at least 3/4
 // of a round: 305 x 32768 x 2048 with GeGLU 65 us against 84 us; at 16384
 // columns (128 workgroups, half the chip) the 128 tile's 43 us stand against
-// 50 us.
+// 50 us. Its rounds of four K-tiles need as many: 300 x 32768 with GeGLU 13.6 us
+// against 11.0 us at K 64, 14.7 against 14.0 us at K 192, and 16.9 against
+// 17.4 us at 260 x 24576, K 320.
 static bool tall(const GemmDesc& g, const GemmPlan& p) {
-  return p.splits == 1 && g.M > 256 && g.M <= 320 && g.N >= NUM_CU_PLAN * 3 / 4 * 128;
+  return p.splits == 1 && g.K >= 256 && g.M > 256 && g.M <= 320 && g.N >= NUM_CU_PLAN * 3 / 4 * 128;
 }
 
 // Whether a plan of 256 x 256 tiles runs in 128 x 128 ones: a round of 256
@@ -2246,10 +2248,23 @@ hipError_t launch_gemm(const GemmDesc& g, const Scratch& s, const LaunchCaps& ca
         if (tall(g, p)) return run_gemm_kind<uint16_t, 320, 128, 64, 1, 0, true, 3>(g, p, s, caps, st);
         return run_gemm_kind<uint16_t, 128, 128, 64, 1, 0, true, 2>(g, p, s, caps, st);
       case 1:
-        // up to two workgroups per CU the ring of four stages, whose loads are
+        // Up to two workgroups per CU the ring of four stages, whose loads are
         // three K-tiles ahead (400 x 1024 x 1024 8.9 us, in two stages 10.4 us);
-        // beyond, two stages leave room for the further workgroups
-        if (p.tiles <= 2 * NUM_CU_PLAN) return run_gemm_kind<uint16_t, 64, 64, 64, 1, 0, true, 4>(g, p, s, caps, st);
+        // beyond, two stages leave room for the further workgroups. Its prologue
+        // and its rounds of four K-tiles are too much for a short K: 150 x 1024 of
+        // partials, K 64, 4.2 us, in two stages 3.75 us (equal at K 192 and 256;
+        // five K-tiles, which the ring runs as eight, with two workgroups per CU,
+        // 400 x 1024 x 1152 in four splits, 7.4 / 6.6 us, with one, 150 rows, 5.1 /
+        // 5.9 us); and the tile with the epilogue chosen at run time, whose code is
+        // long, 256 x 1024, K 64, 6.65 us, through registers 5.7 us (K 320 7.3 /
+        // 6.95, K 512 7.4 / 8.0).
+        if (p.tiles <= 2 * NUM_CU_PLAN) {
+          const int kc = ((g.K + 63) / 64 + p.splits - 1) / p.splits;
+          const bool own = g.epi.kind == EPI_QKV_ROPE || g.epi.kind == EPI_GEGLU || g.epi.kind == EPI_PART;
+          if (!own && kc <= 5) return run_gemm_t<uint16_t, 64, 64, 64, 2, 2, 2>(g, p, s, caps, st);
+          if (kc > 2 && (kc != 5 || p.tiles <= NUM_CU_PLAN))
+            return run_gemm_kind<uint16_t, 64, 64, 64, 1, 0, true, 4>(g, p, s, caps, st);
+        }
         return run_gemm_kind<uint16_t, 64, 64, 64, 1, 0, true, 2>(g, p, s, caps, st);
       case 3:
         switch (g.epi.kind) {

@@ -215,6 +215,18 @@ def test_gemm_tiles(V, kind, M, N, K, pad):
     assert torch.equal(run(4), out)
 
 
+# K on both sides of the lines between the 64 x 64 tile's ring, its two stages
+# and its register-staged form (two K-tiles and three, five and six), and
+# between the 320-row tile and the 128 one (K 256)
+@pytest.mark.parametrize("kind,M,N,K", [
+    ("geglu", 150, 1024, 8), ("geglu", 150, 1056, 128), ("geglu", 150, 1024, 136), ("t", 150, 1032, 64),
+    ("t", 129, 1024, 320), ("t", 129, 1024, 328), ("gelu", 65, 72, 320), ("f32", 400, 4096, 128),
+    ("geglu", 300, 32768, 192), ("geglu", 300, 32768, 256), ("f32", 257, 24584, 248),
+])
+def test_gemm_short_k(V, kind, M, N, K):
+    test_gemm_tiles(V, kind, M, N, K, 0)
+
+
 # Vectors that are there but neutral (zero bias and shift, a column scale of
 # one) and splits that are there but zero take other variants of the norms:
 # the same sums, bit for bit. Rows of one wave (d <= 1024) and of a workgroup.
