@@ -2217,15 +2217,15 @@ static bool tall(const GemmDesc& g, const GemmPlan& p) {
 }
 
 // Whether a plan of 256 x 256 tiles runs in 128 x 128 ones: a round of 256
-// workgroups of the former takes as long as 1.7 rounds of 512 of the latter,
+// workgroups of the former takes as long as 1.6 rounds of 512 of the latter,
 // which fill the last round better (6664 x 2560 x 2048, 270 tiles, 103 us
-// against 120 us; 2440 x 8192 x 2048, 320 tiles, 109 us against 120 us; where
-// both fill their rounds alike, 6144 x 4304 x 1152, 97.4 us against 96.8 us).
+// against 120 us; 2440 x 8192 x 2048, 320 tiles, 109 us against 120 us; three
+// rounds against five, 1220 x 32768 x 2048 with GeGLU, 176 us against 166 us).
 static bool finer(const GemmDesc& g, const GemmPlan& p) {
   const long long t128 = (long long)((g.M + 127) / 128) * ((g.N + 127) / 128) * p.splits;
   const long long r256 = (p.tiles + NUM_CU_PLAN - 1) / NUM_CU_PLAN;
   const long long r128 = (t128 + 2 * NUM_CU_PLAN - 1) / (2 * NUM_CU_PLAN);
-  return 17 * r256 >= 10 * r128;
+  return 16 * r256 >= 10 * r128;
 }
 
 hipError_t launch_gemm(const GemmDesc& g, const Scratch& s, const LaunchCaps& caps,
@@ -2267,9 +2267,11 @@ hipError_t launch_gemm(const GemmDesc& g, const Scratch& s, const LaunchCaps& ca
         }
         return run_gemm_kind<uint16_t, 64, 64, 64, 1, 0, true, 2>(g, p, s, caps, st);
       case 3:
+        // Partials take four waves (2440 x 2048 x 16384 in three splits 133 us, in
+        // eight 141 us), the rest eight, whose epilogues are shorter (6144 x 4304
+        // x 1152 with GELU 85 us, in four 90 us).
         switch (g.epi.kind) {
           case EPI_PART: return run_gemm_t<uint16_t, 256, 256, 64, 2, 2, 1, 0, true, EPI_PART>(g, p, s, caps, st);
-          case EPI_GELU: return run_gemm_t<uint16_t, 256, 256, 64, 2, 2, 1, 0, true, EPI_GELU>(g, p, s, caps, st);
           case EPI_GEGLU: return run_gemm_t<uint16_t, 256, 256, 64, 2, 4, 1, 0, true, EPI_GEGLU>(g, p, s, caps, st);
           default: return run_gemm_t<uint16_t, 256, 256, 64, 2, 4, 1, 0, true>(g, p, s, caps, st);
         }
