@@ -517,12 +517,12 @@ struct GemmSmemDL {
 // (64 KB) two; 128 x 128 (64 KB) two; the 320 x 128 (128 KB) and 256 x 256
 // (128 KB) ones alone, with the whole register file. The 8-wave 256 x 256
 // tile runs alone too, two waves per SIMD. Register-staged tiles: bf16 four
-// (40 and 30 KB), fp32, which only the small test models run, three. Without
+// (40 and 30 KB; 128 x 128, 80 KB, two), fp32, which only the small test models run, three. Without
 // it the compiler may take a few registers more than that leaves (the
 // 128 x 128 GeGLU tile took 260 of 256) and a CU then holds one workgroup
 // fewer.
 constexpr int gemm_waves_per_eu(int bm, int waves, bool dl, int esize, int ns) {
-  if (!dl) return esize == 4 ? 3 : 4;
+  if (!dl) return esize == 4 ? 3 : bm >= 128 ? 2 : 4;
   if (waves != 4) return 2;
   return bm <= 64 ? (ns == 2 ? 4 : 2) : bm <= 128 ? 2 : 1;
 }
@@ -2238,11 +2238,17 @@ hipError_t launch_gemm(const GemmDesc& g, const Scratch& s, const LaunchCaps& ca
     return hipErrorInvalidValue;
   }
   if (g.dtype == DT_BF16) {
-    // The direct loads to LDS move whole 16-byte pieces, and step through the
-    // rows past a K-range in 32-bit offsets: operands that do not start on
-    // 16 bytes, or with rows of more than 2 MB, go through registers.
-    if (p.cfg != 2 && ((((uintptr_t)g.A | (uintptr_t)g.W) & 15) || std::max(g.lda, g.ldw) > 1 << 20))
+    // The four-wave direct-load tiles want operands that start on 16 bytes, and
+    // step through the rows past a K-range in 32-bit offsets. Other operands,
+    // and those with rows of more than 2 MB, take the register-staged tiles, or
+    // the eight-wave 256 x 256 one (2048 x 4096 x 1024 on the 128 tile 37 us, on
+    // the 64 one 42.5 us; 2440 x 8192 x 2048 on the 256 tile 145 us, on the 64
+    // one 191 us).
+    if (p.cfg != 2 && ((((uintptr_t)g.A | (uintptr_t)g.W) & 15) || std::max(g.lda, g.ldw) > 1 << 20)) {
+      if (p.cfg == 3) return run_gemm_t<uint16_t, 256, 256, 64, 2, 4, 1, 0, true>(g, p, s, caps, st);
+      if (p.cfg == 0) return run_gemm_t<uint16_t, 128, 128, 64, 2, 2, 3>(g, p, s, caps, st);
       return run_gemm_t<uint16_t, 64, 64, 64, 2, 2, 2>(g, p, s, caps, st);
+    }
     switch (p.cfg == 3 && finer(g, p) ? 0 : p.cfg) {
       case 0:
         if (tall(g, p)) return run_gemm_kind<uint16_t, 320, 128, 64, 1, 0, true, 3>(g, p, s, caps, st);

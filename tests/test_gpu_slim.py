@@ -227,6 +227,34 @@ def test_gemm_short_k(V, kind, M, N, K):
     test_gemm_tiles(V, kind, M, N, K, 0)
 
 
+# Operands off 16 bytes by one, two and four elements, and with rows of more
+# than 2 MB, on every tile they take: the sums of aligned, packed operands
+@pytest.mark.parametrize("M,N,K,ld", [(2440, 8192, 328, 0), (1025, 16384, 72, 0), (305, 16384, 200, 0), (400, 1024, 136, 0),
+                                      (129, 4104, 72, (1 << 20) + 8), (257, 16392, 72, (1 << 20) + 8)])
+def test_gemm_unaligned(V, M, N, K, ld):
+    import gpu_util as g
+    g.say(f"gemm unaligned {M}x{N}x{K} ld {ld}")
+    gen = torch.Generator(device="cuda").manual_seed(M + N + K)
+    a = torch.randn(M, K, generator=gen, device="cuda").bfloat16()
+    w = (0.05 * torch.randn(N, K, generator=gen, device="cuda")).bfloat16()
+
+    def run(off, lda):
+        A = torch.full((M * lda + 8,), float("inf"), dtype=torch.bfloat16, device="cuda")
+        W = torch.full((N * K + 8,), float("inf"), dtype=torch.bfloat16, device="cuda")
+        A[off:off + M * lda].view(M, lda)[:, :K] = a
+        W[off:off + N * K] = w.flatten()
+        out = torch.full((M, N), float("nan"), device="cuda")
+        V.vla_debug_gemm(1, M, N, K, A[off:], lda, W[off:], K, None, out)
+        torch.cuda.synchronize()
+        return out
+
+    ref = run(0, K)
+    bound = 2 * K * 2.0 ** -24 * (a.double().abs() @ w.double().abs().T)
+    assert bool(((ref.double() - a.double() @ w.double().T).abs() <= bound).all())
+    for off, lda in ((0, ld),) if ld else ((1, K), (2, K), (4, K)):
+        assert torch.equal(run(off, lda), ref), (off, lda)
+
+
 # Vectors that are there but neutral (zero bias and shift, a column scale of
 # one) and splits that are there but zero take other variants of the norms:
 # the same sums, bit for bit. Rows of one wave (d <= 1024) and of a workgroup.
