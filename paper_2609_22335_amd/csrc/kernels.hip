@@ -1965,16 +1965,15 @@ static hipError_t run_slim_t(const GemmDesc& g, const LaunchCaps& caps, hipStrea
   return hipGetLastError();
 }
 
-// K-slabs a wave requests at once: its whole share where the registers
-// allow (one row tile: 24 slabs of one n-block, 16 of two; four: 8 and 4),
-// else in rounds
+// K-slabs a wave requests at once. One row tile: its whole share where the
+// registers allow (24 slabs of one n-block, 16 of two), else in rounds. Four
+// row tiles: two, which leave registers for two workgroups on a CU (17 rows of
+// 9216 x 1536, fp32 out, 10.9 us, with eight 15.7 us; 50 rows of 8192 x 1024,
+// GeGLU, 6.85 us, with four 7.1 us).
 template <typename T, int NB, int KIND>
 static hipError_t run_slim_spw(const GemmDesc& g, const LaunchCaps& caps, hipStream_t st) {
   const int nslab = (g.K + frag_slab(g.dtype) - 1) / frag_slab(g.dtype), pw = (nslab + SLIM_NW - 1) / SLIM_NW;
-  if (slim_rt(g) == 4) {
-    if (NB == 2 || pw <= 4) return run_slim_t<T, SLIM_NW, 4, NB, 4, KIND, 0>(g, caps, st);
-    return run_slim_t<T, SLIM_NW, NB == 1 ? 8 : 4, NB, 4, KIND, 0>(g, caps, st);
-  }
+  if (slim_rt(g) == 4) return run_slim_t<T, SLIM_NW, 2, NB, 4, KIND, 0>(g, caps, st);
   if (pw <= 4) return run_slim_t<T, SLIM_NW, 4, NB, 1, KIND, 0>(g, caps, st);
   if (pw <= 8) return run_slim_t<T, SLIM_NW, 8, NB, 1, KIND, 0>(g, caps, st);
   if (NB == 2 || pw <= 16) return run_slim_t<T, SLIM_NW, 16, NB, 1, KIND, 0>(g, caps, st);
