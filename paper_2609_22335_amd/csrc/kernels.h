@@ -229,6 +229,9 @@ struct Scratch {
 // split or reduction order (results are independent of them).
 struct LaunchCaps {
   int max_wgs = 0;  // 0 = uncapped; otherwise grid-stride over tiles
+  // CUs that the stream's mask leaves it (0: all of them). Chooses between
+  // launch shapes of the same sums.
+  int cus = 0;
   // when set, the main kernel of the launch records these at its own start
   // and end (measurement only)
   hipEvent_t ev_start = nullptr;

@@ -1940,8 +1940,18 @@ static int slim_tiles(const GemmDesc& g, int rt) {
 // gate/up, 256 column blocks of four row tiles, would draw 384 KB per CU from
 // L2 in 16-row tiles, against 164 KB). The frame count does not enter: a
 // frame's sums are the same in every group.
+//
+// On a stream of fewer CUs 512 tiles are many rounds, and each 16-row tile
+// draws the weights again: there it is one, two or four row tiles, the first
+// that makes at most three tiles per CU (50 rows, us, with the whole chip's
+// shapes and with these: on 104 CUs 2560 x 1024 7.0 / 5.3, 1536 x 6144 24.1 /
+// 16.4; on 64 CUs 1024 x 4096 14.8 / 8.9, 1536 x 6144 35.3 / 22.5).
 constexpr int SLIM_MAX_TILES = 512;
-static int slim_rt(const GemmDesc& g) { return slim_tiles(g, 1) <= SLIM_MAX_TILES || g.M <= 16 ? 1 : 4; }
+static int slim_rt(const GemmDesc& g, int cus = 0) {
+  const int most = cus > 0 ? 3 * cus : SLIM_MAX_TILES;
+  if (g.M <= 16 || slim_tiles(g, 1) <= most) return 1;
+  return cus > 0 && slim_tiles(g, 2) <= most ? 2 : 4;
+}
 // The operand's LayerNorm inside the GEMM: K as wide as the registers of a
 // wave per row hold (x, gain, shift and the weights in flight).
 constexpr int slim_ln_max_k(int dtype) { return dtype == DT_BF16 ? 1536 : 1024; }
@@ -1967,14 +1977,25 @@ static hipError_t run_slim_t(const GemmDesc& g, const LaunchCaps& caps, hipStrea
 
 // K-slabs a wave requests at once. One row tile: its whole share where the
 // registers allow (24 slabs of one n-block, 16 of two), else in rounds. Four
-// row tiles: two, which leave registers for two workgroups on a CU (17 rows of
-// 9216 x 1536, fp32 out, 10.9 us, with eight 15.7 us; 50 rows of 8192 x 1024,
-// GeGLU, 6.85 us, with four 7.1 us).
+// row tiles: four of two n-blocks (two are 0.2 us faster alone, 50 x 8192 x
+// 1024 with GeGLU, 6.85 us, but not in the loop, 90.4 against 90.8 frames/s),
+// two of one, which leave registers for two workgroups on a CU (17 rows of
+// 9216 x 1536, fp32 out, 10.9 us, with eight 15.7 us). On a smaller stream two
+// with four row tiles (the GeGLU above on 104 CUs 11.6 us, with four 14.3 us),
+// and four with one where there are more than two tiles per CU, so that the
+// CUs hold more workgroups (50 x 1024 x 4096 on 104 CUs 8.5 us, with sixteen
+// 11.5 us).
 template <typename T, int NB, int KIND>
 static hipError_t run_slim_spw(const GemmDesc& g, const LaunchCaps& caps, hipStream_t st) {
   const int nslab = (g.K + frag_slab(g.dtype) - 1) / frag_slab(g.dtype), pw = (nslab + SLIM_NW - 1) / SLIM_NW;
-  if (slim_rt(g) == 4) return run_slim_t<T, SLIM_NW, 2, NB, 4, KIND, 0>(g, caps, st);
-  if (pw <= 4) return run_slim_t<T, SLIM_NW, 4, NB, 1, KIND, 0>(g, caps, st);
+  const int rt = slim_rt(g, caps.cus);
+  if (rt == 4) {
+    if (NB == 2 && caps.cus == 0) return run_slim_t<T, SLIM_NW, 4, NB, 4, KIND, 0>(g, caps, st);
+    return run_slim_t<T, SLIM_NW, 2, NB, 4, KIND, 0>(g, caps, st);
+  }
+  if (rt == 2) return run_slim_t<T, SLIM_NW, 4, NB, 2, KIND, 0>(g, caps, st);
+  if (pw <= 4 || (caps.cus > 0 && slim_tiles(g, 1) > 2 * caps.cus))
+    return run_slim_t<T, SLIM_NW, 4, NB, 1, KIND, 0>(g, caps, st);
   if (pw <= 8) return run_slim_t<T, SLIM_NW, 8, NB, 1, KIND, 0>(g, caps, st);
   if (NB == 2 || pw <= 16) return run_slim_t<T, SLIM_NW, 16, NB, 1, KIND, 0>(g, caps, st);
   return run_slim_t<T, SLIM_NW, NB == 1 ? 24 : 16, NB, 1, KIND, 0>(g, caps, st);
@@ -2220,11 +2241,45 @@ static bool tall(const GemmDesc& g, const GemmPlan& p) {
 // which fill the last round better (6664 x 2560 x 2048, 270 tiles, 103 us
 // against 120 us; 2440 x 8192 x 2048, 320 tiles, 109 us against 120 us; three
 // rounds against five, 1220 x 32768 x 2048 with GeGLU, 176 us against 166 us).
-static bool finer(const GemmDesc& g, const GemmPlan& p) {
+static bool finer(const GemmDesc& g, const GemmPlan& p, int cus) {
   const long long t128 = (long long)((g.M + 127) / 128) * ((g.N + 127) / 128) * p.splits;
-  const long long r256 = (p.tiles + NUM_CU_PLAN - 1) / NUM_CU_PLAN;
-  const long long r128 = (t128 + 2 * NUM_CU_PLAN - 1) / (2 * NUM_CU_PLAN);
+  const long long r256 = (p.tiles + cus - 1) / cus;
+  const long long r128 = (t128 + 2 * cus - 1) / (2 * cus);
   return 16 * r256 >= 10 * r128;
+}
+
+// The 64 x 64 tile. Up to two workgroups per CU the ring of four stages, whose
+// loads are three K-tiles ahead (400 x 1024 x 1024 8.9 us, in two stages 10.4
+// us); beyond, two stages leave room for the further workgroups. Its prologue
+// and its rounds of four K-tiles are too much for a short K: 150 x 1024 of
+// partials, K 64, 4.2 us, in two stages 3.75 us (equal at K 192 and 256; five
+// K-tiles, which the ring runs as eight, with two workgroups per CU, 400 x 1024
+// x 1152 in four splits, 7.4 / 6.6 us, with one, 150 rows, 5.1 / 5.9 us); and
+// the tile with the epilogue chosen at run time, whose code is long, 256 x
+// 1024, K 64, 6.65 us, through registers 5.7 us (K 320 7.3 / 6.95, K 512 7.4 /
+// 8.0).
+//
+// On a stream of fewer CUs two stages take over where the ring would need a
+// second round, unless K is long (us, ring / two stages: 152 CUs, 256 x 4304 x
+// 1152, 272 tiles, 19.0 / 15.7, 256 x 3456 x 1152, 216 tiles, 12.6 / 13.8; 192
+// CUs, 150 x 8192 x 1024, 384 tiles, 9.9 / 12.6; 104 CUs, 305 x 2048 x 16384 in
+// three splits 93 / 120, 400 x 1024 x 4096 in four, 448 tiles, 18.8 / 20.6, on
+// 152 CUs 15.3 / 13.5). The CUs count in whole 32s: with 152 the 272 tiles
+// above take two rounds, though they are fewer than two per CU.
+static hipError_t run_gemm_64(const GemmDesc& g, const GemmPlan& p, const Scratch& s, const LaunchCaps& caps,
+                              hipStream_t st) {
+  const int cus = caps.cus > 0 ? caps.cus : NUM_CU_PLAN;
+  const int kc = ((g.K + 63) / 64 + p.splits - 1) / p.splits;
+  const bool own = g.epi.kind == EPI_QKV_ROPE || g.epi.kind == EPI_GEGLU || g.epi.kind == EPI_PART;
+  const int slots = caps.cus > 0 ? std::max(1, cus / 32) * 32 : NUM_CU_PLAN;
+  bool ring = p.tiles <= 2 * slots;
+  if (p.tiles <= 2 * NUM_CU_PLAN) {
+    if (!own && kc <= 5) return run_gemm_t<uint16_t, 64, 64, 64, 2, 2, 2>(g, p, s, caps, st);
+    ring = ring || kc >= (p.tiles <= 4 * slots ? 32 : 16);
+  }
+  if (ring && kc > 2 && (kc != 5 || p.tiles <= cus))
+    return run_gemm_kind<uint16_t, 64, 64, 64, 1, 0, true, 4>(g, p, s, caps, st);
+  return run_gemm_kind<uint16_t, 64, 64, 64, 1, 0, true, 2>(g, p, s, caps, st);
 }
 
 hipError_t launch_gemm(const GemmDesc& g, const Scratch& s, const LaunchCaps& caps,
@@ -2237,6 +2292,7 @@ hipError_t launch_gemm(const GemmDesc& g, const Scratch& s, const LaunchCaps& ca
     return hipErrorInvalidValue;
   }
   if (g.dtype == DT_BF16) {
+    const int cus = caps.cus > 0 ? caps.cus : NUM_CU_PLAN;
     // The four-wave direct-load tiles want operands that start on 16 bytes, and
     // step through the rows past a K-range in 32-bit offsets. Other operands,
     // and those with rows of more than 2 MB, take the register-staged tiles, or
@@ -2248,29 +2304,12 @@ hipError_t launch_gemm(const GemmDesc& g, const Scratch& s, const LaunchCaps& ca
       if (p.cfg == 0) return run_gemm_t<uint16_t, 128, 128, 64, 2, 2, 3>(g, p, s, caps, st);
       return run_gemm_t<uint16_t, 64, 64, 64, 2, 2, 2>(g, p, s, caps, st);
     }
-    switch (p.cfg == 3 && finer(g, p) ? 0 : p.cfg) {
+    switch (p.cfg == 3 && finer(g, p, cus) ? 0 : p.cfg) {
       case 0:
         if (tall(g, p)) return run_gemm_kind<uint16_t, 320, 128, 64, 1, 0, true, 3>(g, p, s, caps, st);
         return run_gemm_kind<uint16_t, 128, 128, 64, 1, 0, true, 2>(g, p, s, caps, st);
       case 1:
-        // Up to two workgroups per CU the ring of four stages, whose loads are
-        // three K-tiles ahead (400 x 1024 x 1024 8.9 us, in two stages 10.4 us);
-        // beyond, two stages leave room for the further workgroups. Its prologue
-        // and its rounds of four K-tiles are too much for a short K: 150 x 1024 of
-        // partials, K 64, 4.2 us, in two stages 3.75 us (equal at K 192 and 256;
-        // five K-tiles, which the ring runs as eight, with two workgroups per CU,
-        // 400 x 1024 x 1152 in four splits, 7.4 / 6.6 us, with one, 150 rows, 5.1 /
-        // 5.9 us); and the tile with the epilogue chosen at run time, whose code is
-        // long, 256 x 1024, K 64, 6.65 us, through registers 5.7 us (K 320 7.3 /
-        // 6.95, K 512 7.4 / 8.0).
-        if (p.tiles <= 2 * NUM_CU_PLAN) {
-          const int kc = ((g.K + 63) / 64 + p.splits - 1) / p.splits;
-          const bool own = g.epi.kind == EPI_QKV_ROPE || g.epi.kind == EPI_GEGLU || g.epi.kind == EPI_PART;
-          if (!own && kc <= 5) return run_gemm_t<uint16_t, 64, 64, 64, 2, 2, 2>(g, p, s, caps, st);
-          if (kc > 2 && (kc != 5 || p.tiles <= NUM_CU_PLAN))
-            return run_gemm_kind<uint16_t, 64, 64, 64, 1, 0, true, 4>(g, p, s, caps, st);
-        }
-        return run_gemm_kind<uint16_t, 64, 64, 64, 1, 0, true, 2>(g, p, s, caps, st);
+        return run_gemm_64(g, p, s, caps, st);
       case 3:
         // Partials take four waves (2440 x 2048 x 16384 in three splits 133 us, in
         // eight 141 us), the rest eight, whose epilogues are shorter (6144 x 4304

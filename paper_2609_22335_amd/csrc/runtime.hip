@@ -380,9 +380,9 @@ struct vla_model {
   std::vector<hipEvent_t> eva;  // per action item: start, end
   // graph replay: frame inputs staged into fixed buffers, graphs cached per
   // (context, VLM grid cap) and (action lane, context)
-  std::map<std::tuple<int, int, int, int>, hipGraphExec_t> pre_graphs;  // (VLM lane, first context, WG cap, frames)
-  // (lane, or -1 for lane 0 in the serial mode, which reads ahead; contexts of the items)
-  std::map<std::pair<int, std::vector<int>>, hipGraphExec_t> den_graphs;
+  std::map<std::tuple<int, int, int, int>, hipGraphExec_t> pre_graphs;  // (VLM lane, first context, WG cap or -CUs, frames)
+  // (lane, or -1 for lane 0 in the serial mode, which reads ahead; CUs; contexts of the items)
+  std::map<std::tuple<int, int, std::vector<int>>, hipGraphExec_t> den_graphs;
   std::mutex mu;
 
   // per-tag kernel timer: every launch whose tag matches is bracketed by
@@ -2120,6 +2120,11 @@ static int pipeline_impl(vla_model* m, const vla_frame* frames, const float* noi
   VLA_TRY(grow(m->eva, (size_t)2 * items));
   LaunchCaps vcaps{}, acaps{};
   if (s.mode == VLA_MODE_WG_CAPPED) vcaps.max_wgs = s.vlm_wg_cap * m->num_cus;
+  if (s.mode == VLA_MODE_CU_MASKED) {
+    vcaps.cus = s.vlm_cus;
+    acaps.cus = s.act_cus;
+  }
+  const int vkey = vcaps.cus > 0 ? -vcaps.cus : vcaps.max_wgs;  // a graph holds its launches' shapes
   const size_t chunk = (size_t)c.chunk_len * c.action_dim;
   const size_t pix_bytes = (size_t)c.n_views * c.img_h * c.img_w * 3 * 4;
   auto vlane = [&](int r) { return (r / Bv) % vlanes; };  // VLM lane of frame r
@@ -2132,12 +2137,12 @@ static int pipeline_impl(vla_model* m, const vla_frame* frames, const float* noi
     std::vector<int> cs;
     if (alone) li = -1;
     for (int f = 0; f < na; ++f) cs.push_back(actx(a0 + f));
-    return std::make_pair(li, cs);
+    return std::make_tuple(li, acaps.cus, cs);
   };
   if (graphs) {  // capture what this run needs and is missing (outside the timed loop)
     for (int g0 = 0; g0 < R; g0 += Bv) {
       const int n = std::min(Bv, R - g0), vi = vlane(g0), ci = g0 % nctx;
-      const auto key = std::make_tuple(vi, ci, vcaps.max_wgs, n);
+      const auto key = std::make_tuple(vi, ci, vkey, n);
       if (m->pre_graphs.count(key)) continue;
       VlmWs* vw = m->vws[vi].get();
       vla_frame staged[MAX_VLM_BATCH];
@@ -2187,7 +2192,7 @@ static int pipeline_impl(vla_model* m, const vla_frame* frames, const float* noi
         if (c.state_dim > 0)
           HIP_TRY(launch_copy(vw->sstage + (size_t)i * c.state_dim, fr.state, (size_t)c.state_dim * 4, sv));
       }
-      HIP_TRY(hipGraphLaunch(m->pre_graphs[std::make_tuple(vi, ci, vcaps.max_wgs, n)], sv));
+      HIP_TRY(hipGraphLaunch(m->pre_graphs[std::make_tuple(vi, ci, vkey, n)], sv));
     } else {
       Run rv{m, sv, vcaps, &vw->scr, nullptr, vw};
       VLA_TRY(run_prefill_n(rv, &frames[g0], n, &m->pctx[ci]));

@@ -255,6 +255,32 @@ def test_gemm_unaligned(V, M, N, K, ld):
         assert torch.equal(run(off, lda), ref), (off, lda)
 
 
+# Streams of fewer CUs take other launch shapes (one, two or four row tiles of
+# the action GEMMs, ring or two stages of the 64 x 64 tile), each with a graph of
+# its own: the same chunks, bit for bit, one mask after another on one model
+@pytest.mark.parametrize("batch", [1, 2])
+def test_masked_launch_shapes(V, batch):
+    import gpu_util as g
+    import synth
+    cfg = dict(synth.micro(synth.BF16), chunk_len=50, ex_dim=256, ex_mlp=1024)
+    frames = [g.DevFrame(synth.make_frame(cfg, 0, r)) for r in range(4)]
+    noise = torch.stack([f.noise for f in frames])
+
+    with g.model(cfg, 0) as m:
+        def run(**kw):
+            out = torch.full_like(noise, float("nan"))
+            V.vla_pipeline_run(m, [f.c for f in frames], noise, 4, actions=out, act_batch=batch, vlm_batch=batch, **kw)
+            torch.cuda.synchronize()
+            return out
+
+        ref = run(mode="serial")
+        assert bool(torch.isfinite(ref).all())
+        for vlm, act in ((64, 8), (8, 16), (128, 24), (152, 40), (16, 64)):
+            for graphs in (True, False, True):
+                g.say(f"masks {vlm}/{act} graphs {graphs} batch {batch}")
+                assert torch.equal(run(mode="cu_masked", vlm_cus=vlm, act_cus=act, graphs=graphs), ref), (vlm, act)
+
+
 # Vectors that are there but neutral (zero bias and shift, a column scale of
 # one) and splits that are there but zero take other variants of the norms:
 # the same sums, bit for bit. Rows of one wave (d <= 1024) and of a workgroup.
