@@ -2311,11 +2311,12 @@ hipError_t launch_gemm(const GemmDesc& g, const Scratch& s, const LaunchCaps& ca
       case 1:
         return run_gemm_64(g, p, s, caps, st);
       case 3:
-        // Partials take four waves (2440 x 2048 x 16384 in three splits 133 us, in
-        // eight 141 us), the rest eight, whose epilogues are shorter (6144 x 4304
-        // x 1152 with GELU 85 us, in four 90 us).
+        // Partials and GELU take four waves (2440 x 2048 x 16384 in three splits
+        // 133 us, in eight 141 us; GELU inside a prefill, 2048 x 4304 x 1152 46 us,
+        // in eight 49 us, 6144 x 4304 x 1152 96 us, in eight 100 us), the rest eight.
         switch (g.epi.kind) {
           case EPI_PART: return run_gemm_t<uint16_t, 256, 256, 64, 2, 2, 1, 0, true, EPI_PART>(g, p, s, caps, st);
+          case EPI_GELU: return run_gemm_t<uint16_t, 256, 256, 64, 2, 2, 1, 0, true, EPI_GELU>(g, p, s, caps, st);
           case EPI_GEGLU: return run_gemm_t<uint16_t, 256, 256, 64, 2, 4, 1, 0, true, EPI_GEGLU>(g, p, s, caps, st);
           default: return run_gemm_t<uint16_t, 256, 256, 64, 2, 4, 1, 0, true>(g, p, s, caps, st);
         }
