@@ -328,6 +328,26 @@ typedef struct vla_debug_epi {
 int vla_debug_gemm_epi(int32_t dtype, int32_t M, int32_t N, int32_t K, const void* A, const void* W,
                        const vla_debug_epi* e, void* stream);
 
+/* Two of the action head's GEMMs with the RMSNorm between them folded into
+ * both, as one-frame expert layers run them. Row-major device arrays, A, W, W2
+ * and norm_out of the operand type, M <= 64, N <= 2048:
+ *   x fp32 [M][N] += colscale (A [M][K] W [N][K]^T)   (colscale [N] NULL: 1)
+ *   norm_out [M][N] = T(x * gain)
+ *   out fp32 [M][N2] = (norm_out W2 [N2][N]^T) / sqrt(mean(x^2) + 1e-6)
+ * Blocking; allocates temporaries. */
+int vla_debug_gemm_fold(int32_t dtype, int32_t M, int32_t N, int32_t K, const void* A, const void* W,
+                        const float* colscale, const float* gain, float* x, void* norm_out, int32_t N2,
+                        const void* W2, float* out, void* stream);
+
+/* The action head's GEMM over the LayerNorm of its fp32 rows, applied as they
+ * are loaded: out [M][N] = T(act(LN(x [M][K]) W [N][K]^T + bias)), LN with
+ * epsilon 1e-6, gain (or 1 + gain) and shift (NULL: none), act GELU with gelu
+ * set. M <= 64; shapes that take the norm as a launch of its own return
+ * VLA_EUNSUPPORTED. Blocking; allocates temporaries. */
+int vla_debug_gemm_ln(int32_t dtype, int32_t M, int32_t N, int32_t K, const float* x, const float* gain,
+                      int32_t gain_plus_one, const float* shift, const void* W, const float* bias, int32_t gelu,
+                      void* out, void* stream);
+
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, serving loops and harnesses that forbid hipMalloc): the GEMM of
  * vla_debug_gemm, same arguments, layouts, kernels, plan and result bits,

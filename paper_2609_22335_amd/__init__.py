@@ -120,6 +120,8 @@ def _load():
         "vla_debug_gemm": [I32, I32, I32, I32, P, I32, P, I32, P, P, P],
         "vla_gemm_noalloc": [I32, I32, I32, I32, P, I32, P, I32, P, P, P],
         "vla_debug_gemm_epi": [I32, I32, I32, I32, P, P, ctypes.POINTER(vla_debug_epi), P],
+        "vla_debug_gemm_fold": [I32, I32, I32, I32, P, P, P, P, P, P, I32, P, P, P],
+        "vla_debug_gemm_ln": [I32, I32, I32, I32, P, P, I32, P, P, P, I32, P, P],
         "vla_debug_attention": [I32, I32, I32, I32, I32, P, P, P, I32, P, P, I32, P, P],
         "vla_debug_generate": [U64, ctypes.c_char_p, I64, D, D, P],
         "vla_debug_gemm_plan": [I32, I32, I32, I32, I32, I32, I32, I32, P, ctypes.POINTER(I64)],
@@ -353,6 +355,18 @@ def vla_debug_gemm_epi(dtype: int, M: int, N: int, K: int, A, W, kind: str, skin
     return int(plan[0]), int(plan[1]), int(plan[2])
 
 
+def vla_debug_gemm_fold(dtype: int, M: int, N: int, K: int, A, W, colscale, gain, x, norm_out, N2: int, W2, out,
+                        stream: int = 0) -> None:
+    _check(_lib.vla_debug_gemm_fold(dtype, M, N, K, _ptr(A), _ptr(W), _ptr(colscale), _ptr(gain), _ptr(x),
+                                    _ptr(norm_out), N2, _ptr(W2), _ptr(out), stream or None))
+
+
+def vla_debug_gemm_ln(dtype: int, M: int, N: int, K: int, x, gain, gain_plus_one: int, shift, W, bias, gelu: bool, out,
+                      stream: int = 0) -> None:
+    _check(_lib.vla_debug_gemm_ln(dtype, M, N, K, _ptr(x), _ptr(gain), gain_plus_one, _ptr(shift), _ptr(W),
+                                  _ptr(bias), 1 if gelu else 0, _ptr(out), stream or None))
+
+
 def vla_gemm_noalloc(dtype: int, M: int, N: int, K: int, A, lda: int, W, ldw: int, bias, C,
                      stream: int = 0) -> None:
     _check(_lib.vla_gemm_noalloc(dtype, M, N, K, _ptr(A), lda, _ptr(W), ldw, _ptr(bias), _ptr(C),
@@ -411,7 +425,7 @@ def exported_symbols() -> Iterable[str]:
     return ["vla_preset", "vla_validate", "vla_model_config", "vla_create", "vla_destroy", "vla_ctx_create",
             "vla_ctx_destroy", "vla_vlm_prefill", "vla_action_denoise", "vla_pipeline_run",
             "vla_param_count", "vla_param_info", "vla_export_param", "vla_ctx_export_kv", "vla_ctx_export_cross", "vla_ctx_export_cog", "vla_wavelog_enable", "vla_wavelog_read",
-            "vla_debug_gemm", "vla_debug_gemm_epi", "vla_gemm_noalloc", "vla_debug_attention", "vla_debug_attention_cache", "vla_debug_norm", "vla_debug_generate",
+            "vla_debug_gemm", "vla_debug_gemm_epi", "vla_debug_gemm_fold", "vla_debug_gemm_ln", "vla_gemm_noalloc", "vla_debug_attention", "vla_debug_attention_cache", "vla_debug_norm", "vla_debug_generate",
             "vla_debug_gemm_plan",
             "vla_kernel_timer",
             "vla_kernel_timer_read", "vla_last_error"]

@@ -712,8 +712,8 @@ static GemmDesc gemm_desc(vla_model* m, const void* A, int lda, int W, int M, in
 // standalone calls (pi0, prefill and denoise on one stream 10.9 ms a frame; the
 // calls on two streams, the next prefill beside the denoise, 9.2 ms, without
 // reading ahead 9.5 ms). Not in concurrent schedules, where the launches of
-// several frames are in flight and the CUs and L2s in use (one action lane
-// beside prefills, four frames, 39.3 ms, reading ahead 40.6 ms).
+// several frames are in flight and the CUs and L2s in use (GR00T-shaped
+// serving in four action lanes 39.3 ms, reading ahead 40.6 ms).
 static Prefetch ahead(const Run& r, int wgs, int t0, int t1 = -1) {
   Prefetch p;
   if (!r.alone) return p;
@@ -2917,6 +2917,138 @@ int vla_debug_gemm_epi(int32_t dtype, int32_t M, int32_t N, int32_t K, const voi
       HIP_TRY(hipMemcpy(e.v_out, vr.data(), vr.size(), hipMemcpyHostToDevice));
     }
     return VLA_OK;
+  })
+}
+
+}  // extern "C"
+
+// Temporaries of a debug call: device buffers freed with the object, and the
+// action head's operand layouts of row-major device arrays.
+namespace {
+struct DebugTmp {
+  std::vector<void*> v;
+  ~DebugTmp() {
+    for (void* p : v) hipFree(p);
+  }
+  int alloc(size_t bytes, void** p) {
+    bytes = std::max<size_t>(bytes, 256);
+    HIP_TRY(hipMalloc(p, bytes));
+    v.push_back(*p);
+    HIP_TRY(hipMemset(*p, 0, bytes));
+    return VLA_OK;
+  }
+  // `rows` x `cols` values through index map `at` into a buffer of `elems`
+  template <typename F>
+  int layout(const void* src, int rows, int cols, size_t esz, size_t elems, F at, void** dst) {
+    std::vector<uint8_t> h((size_t)rows * cols * esz), o(elems * esz, 0);
+    HIP_TRY(hipMemcpy(h.data(), src, h.size(), hipMemcpyDeviceToHost));
+    for (int r = 0; r < rows; ++r)
+      for (int c = 0; c < cols; ++c) std::memcpy(&o[at(r, c) * esz], &h[((size_t)r * cols + c) * esz], esz);
+    VLA_TRY(alloc(o.size(), dst));
+    HIP_TRY(hipMemcpy(*dst, o.data(), o.size(), hipMemcpyHostToDevice));
+    return VLA_OK;
+  }
+  int weight(const void* W, int N, int K, int dt, void** dst) {
+    const int fks = (K + frag_slab(dt) - 1) / frag_slab(dt);
+    return layout(W, N, K, dsz(dt), (size_t)((N + 31) / 32 * 32) * fks * frag_slab(dt),
+                  [&](int n, int k) { return frag_index(n, k, fks, dt); }, dst);
+  }
+  int operand(const void* A, int M, int K, int dt, void** dst) {
+    return layout(A, M, K, dsz(dt), afrag_elems(dt, K), [&](int m, int k) { return afrag_index(dt, m, k); }, dst);
+  }
+  // an operand-layout buffer back to row-major
+  int rows(const void* src, int M, int N, int dt, void* dst) {
+    const size_t esz = dsz(dt);
+    std::vector<uint8_t> h(afrag_elems(dt, N) * esz), o((size_t)M * N * esz);
+    HIP_TRY(hipMemcpy(h.data(), src, h.size(), hipMemcpyDeviceToHost));
+    for (int m = 0; m < M; ++m)
+      for (int n = 0; n < N; ++n) std::memcpy(&o[((size_t)m * N + n) * esz], &h[afrag_index(dt, m, n) * esz], esz);
+    HIP_TRY(hipMemcpy(dst, o.data(), o.size(), hipMemcpyHostToDevice));
+    return VLA_OK;
+  }
+};
+
+GemmDesc debug_slim(int dt, const void* A, const void* W, int M, int N, int K, const Epi& e) {
+  GemmDesc g{dt, A, K, W, K, M, N, K, e};
+  g.frag_ks = (K + frag_slab(dt) - 1) / frag_slab(dt);
+  return g;
+}
+}  // namespace
+
+extern "C" {
+
+int vla_debug_gemm_fold(int32_t dtype, int32_t M, int32_t N, int32_t K, const void* A, const void* W,
+                        const float* colscale, const float* gain, float* x, void* norm_out, int32_t N2, const void* W2,
+                        float* out, void* stream) {
+  ABI_GUARD({
+    if (dtype != VLA_F32 && dtype != VLA_BF16) return fail(VLA_EINVAL, "dtype");
+    if (!A || !W || !gain || !x || !norm_out || !W2 || !out) return fail(VLA_EINVAL, "NULL argument");
+    if (M <= 0 || M > 64 || N <= 0 || N > 2048 || N % 8 || K <= 0 || K % 8 || N2 <= 0)
+      return fail(VLA_EINVAL, "shape: M in 1 .. 64, N a multiple of 8 up to 2048, K a multiple of 8");
+    const int dt = dtype == VLA_BF16 ? DT_BF16 : DT_F32;
+    hipStream_t st = (hipStream_t)stream;
+    HIP_TRY(hipStreamSynchronize(st));
+    DebugTmp t;
+    void *dA = nullptr, *dW = nullptr, *dW2 = nullptr, *dn = nullptr, *ss = nullptr;
+    VLA_TRY(t.operand(A, M, K, dt, &dA));
+    VLA_TRY(t.weight(W, N, K, dt, &dW));
+    VLA_TRY(t.weight(W2, N2, N, dt, &dW2));
+    VLA_TRY(t.alloc(afrag_elems(dt, N) * dsz(dt), &dn));
+    VLA_TRY(t.alloc((size_t)slim_blocks(N) * M * 4, &ss));
+    HIP_TRY(hipDeviceSynchronize());
+    Epi e;
+    e.kind = EPI_RESID;
+    e.resid = x;
+    e.ldr = N;
+    e.colscale = colscale;
+    e.norm_g = gain;
+    e.norm_out = dn;
+    e.rowss = (float*)ss;
+    hipError_t err = launch_gemm(debug_slim(dt, dA, dW, M, N, K, e), Scratch{}, LaunchCaps{}, st);
+    if (err != hipSuccess) return fail(VLA_EHIP, std::string("gemm: ") + hipGetErrorString(err));
+    Epi c;
+    c.kind = EPI_F32;
+    c.out = out;
+    c.ldo = N2;
+    c.rowss = (float*)ss;
+    c.rowss_n = slim_blocks(N);
+    c.rowss_d = N;
+    err = launch_gemm(debug_slim(dt, dn, dW2, M, N2, N, c), Scratch{}, LaunchCaps{}, st);
+    if (err != hipSuccess) return fail(VLA_EHIP, std::string("consumer gemm: ") + hipGetErrorString(err));
+    HIP_TRY(hipStreamSynchronize(st));
+    return t.rows(dn, M, N, dt, norm_out);
+  })
+}
+
+int vla_debug_gemm_ln(int32_t dtype, int32_t M, int32_t N, int32_t K, const float* x, const float* gain,
+                      int32_t gain_plus_one, const float* shift, const void* W, const float* bias, int32_t gelu,
+                      void* out, void* stream) {
+  ABI_GUARD({
+    if (dtype != VLA_F32 && dtype != VLA_BF16) return fail(VLA_EINVAL, "dtype");
+    if (!x || !gain || !W || !out) return fail(VLA_EINVAL, "NULL argument");
+    if (M <= 0 || M > 64 || N <= 0 || K <= 0 || K % 8) return fail(VLA_EINVAL, "shape: M in 1 .. 64, K a multiple of 8");
+    const int dt = dtype == VLA_BF16 ? DT_BF16 : DT_F32;
+    const int kind = gelu ? EPI_GELU : EPI_T;
+    if (!slim_ln_fits(dt, M, N, K, kind)) return fail(VLA_EUNSUPPORTED, "shape: not one that takes the norm as it loads");
+    hipStream_t st = (hipStream_t)stream;
+    HIP_TRY(hipStreamSynchronize(st));
+    DebugTmp t;
+    void *dW = nullptr, *dout = nullptr;
+    VLA_TRY(t.weight(W, N, K, dt, &dW));
+    VLA_TRY(t.alloc(afrag_elems(dt, N) * dsz(dt), &dout));
+    HIP_TRY(hipDeviceSynchronize());
+    Epi e;
+    e.kind = kind;
+    e.out = dout;
+    e.ldo = N;
+    e.bias = bias;
+    e.afrag = 1;
+    GemmDesc g = debug_slim(dt, nullptr, dW, M, N, K, e);
+    g.ln = LnOperand{x, K, gain, gain_plus_one, shift};
+    const hipError_t err = launch_gemm(g, Scratch{}, LaunchCaps{}, st);
+    if (err != hipSuccess) return fail(VLA_EHIP, std::string("gemm over a LayerNorm: ") + hipGetErrorString(err));
+    HIP_TRY(hipStreamSynchronize(st));
+    return t.rows(dout, M, N, dt, out);
   })
 }
 

@@ -19,8 +19,9 @@ def V():
 
 
 # (dtype, M, N, K): row tiles 1, 1 + 1 row, 3 + 2 rows, 4; a last column block
-# of 8; one and two blocks of row sums (N <= and > 1024); K of one piece, of a
-# slab and a piece, at and past a wave's 4, 8, 16 and 24 slabs, and in rounds
+# of 8; K of one piece, of a slab and a piece, at and past a wave's 4, 8, 16 and
+# 24 slabs, and in rounds. resid_norm is the residual update and a norm launch
+# after it; the norm folded into the update has a test file of its own
 @pytest.mark.parametrize("dtype,M,N,K", [
     (1, 1, 8, 8), (1, 16, 40, 40), (1, 17, 1024, 1032), (1, 50, 1024, 2056), (1, 64, 1032, 4104), (1, 18, 2048, 6152),
     (0, 1, 8, 8), (0, 17, 72, 264), (0, 50, 1032, 1544), (0, 64, 128, 3080),
@@ -156,7 +157,8 @@ def cache_layout(k, v):
 # 64 x 64 in the ring of four (one K-tile and a piece, three, four, five; one
 # row and one column past a tile; split K) and, past 512 tiles, in two stages;
 # 128 x 128 with whole and ragged last tiles; the 320-row tile from 257 to 320
-# rows; 256 x 256 plans that run in 128 x 128 tiles or stay; 4-wave GELU
+# rows; 256 x 256 plans that run in 128 x 128 tiles or stay; GELU, whose 256 x 256
+# tiles have four waves
 @pytest.mark.parametrize("kind,M,N,K,pad", [
     ("f32", 33, 8, 8, 0), ("f32", 64, 64, 72, 8), ("f32", 65, 72, 192, 0), ("f32", 129, 200, 256, 8),
     ("f32", 100, 1032, 328, 0), ("f32", 40, 64, 4104, 0), ("f32", 400, 1024, 1024, 64), ("f32", 520, 4168, 136, 0),
