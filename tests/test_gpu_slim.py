@@ -283,6 +283,50 @@ def test_masked_launch_shapes(V, batch):
                 assert torch.equal(run(mode="cu_masked", vlm_cus=vlm, act_cus=act, graphs=graphs), ref), (vlm, act)
 
 
+def test_large_tiles_under_a_workgroup_cap(V):
+    """The 320-row tile (one frame's prefix of 287 rows) and a plan of 256 x 256
+    tiles that runs in 128 x 128 ones (four frames), each with more tiles than
+    the 256 workgroups of the cap: the bits of the uncapped launches."""
+    import gpu_util as g
+    import synth
+    import test_gpu_parity as P
+    cfg = dict(synth.micro(synth.BF16), lm_dim=256, lm_mlp=20480, n_text=270, lm_layers=2, ex_layers=2)
+    P.test_phases_vs_oracle(V, "micro-bf16-wide-lm", cfg)
+    frames = [g.DevFrame(synth.make_frame(cfg, 0, r)) for r in range(4)]
+    noise = torch.stack([f.noise for f in frames])
+    with g.model(cfg, 0) as m:
+        ref = None
+        for kw in (dict(mode="serial"), dict(mode="serial", vlm_batch=4), dict(mode="wg_capped", vlm_wg_cap=1),
+                   dict(mode="wg_capped", vlm_wg_cap=1, vlm_batch=4), dict(mode="wg_capped", vlm_wg_cap=1, graphs=True)):
+            g.say(f"large tiles {kw}")
+            out = torch.full_like(noise, float("nan"))
+            V.vla_pipeline_run(m, [f.c for f in frames], noise, 4, actions=out, **kw)
+            torch.cuda.synchronize()
+            ref = out if ref is None else ref
+            assert bool(torch.isfinite(out).all()) and torch.equal(out, ref), kw
+
+
+def test_attention_parts_in_groups(V):
+    """Action attention at head dim 256: groups of two and four frames split a
+    query tile along the head dim in two, a group of eight does not (200 tiles);
+    the chunks are the same bits."""
+    import gpu_util as g
+    import synth
+    cfg = dict(synth.micro(synth.BF16), head_dim=256, lm_heads=8, chunk_len=50)
+    frames = [g.DevFrame(synth.make_frame(cfg, 0, r)) for r in range(8)]
+    noise = torch.stack([f.noise for f in frames])
+    got = []
+    with g.model(cfg, 0) as m:
+        for batch in (8, 4, 2):
+            g.say(f"attention groups of {batch}")
+            out = torch.full_like(noise, float("nan"))
+            V.vla_pipeline_run(m, [f.c for f in frames], noise, 8, mode="serial", actions=out, act_batch=batch)
+            torch.cuda.synchronize()
+            got.append(out)
+    assert bool(torch.isfinite(got[0]).all())
+    assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
+
+
 # Vectors that are there but neutral (zero bias and shift, a column scale of
 # one) and splits that are there but zero take other variants of the norms:
 # the same sums, bit for bit. Rows of one wave (d <= 1024) and of a workgroup.
