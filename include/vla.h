@@ -291,16 +291,18 @@ int vla_debug_attention(int32_t dtype, int32_t Sq, int32_t nq, int32_t nkv, int3
  *             through the KV-cache layout and are returned row-major
  *  QKV_PLAIN  as QKV_ROPE without the rotation (hd a multiple of 8)
  *  STEP       x fp32 [M][N] <- xs x + dt (v + bias); out [M][N] = T(new x)
- *  RESID_NORM resid fp32 [M][N] += v (split-K partials summed in split
- *             order); out [M][N] = T(RMSNorm(resid) * gain), N <= 2048
+ *  RESID_NORM resid fp32 [M][N] += v (skinny = 0: split-K partials, summed
+ *             in split order by the norm; skinny = 1: by the GEMM itself, a
+ *             norm launch after it); out [M][N] = T(RMSNorm(resid) * gain), N <= 2048
  * bias may be NULL; GEGLU and QKV take none. skinny = 1 runs the action
  * head's kernel (M <= 64): W is converted to MFMA fragment order and A to
  * the row-block operand layout, and operand-type outputs are written in that
  * layout and returned row-major. skinny = 0 runs the tiled kernel with the
  * tile the planner picks for M and N (the launch may deal its sums out in
- * workgroups of another size: the results are the same). plan_out (host, may be NULL) receives
- * the tile's rows and columns (0 and 32 for the skinny kernel) and the
- * split-K factor. Blocking; allocates temporaries. */
+ * workgroups of another size: the results are the same). plan_out (host, may
+ * be NULL) receives the tile's rows and columns (for the skinny kernel the
+ * mark 0 and 32: its tile depends on the epilogue) and the split-K factor
+ * (skinny: 1). Blocking; allocates temporaries. */
 #define VLA_DEBUG_EPI_BIAS 0
 #define VLA_DEBUG_EPI_T 1
 #define VLA_DEBUG_EPI_GELU 2

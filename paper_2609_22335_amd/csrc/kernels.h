@@ -246,8 +246,8 @@ struct GemmPlan {
 };
 
 GemmPlan plan_gemm(const GemmDesc& g);
-// Rows and columns of the tile of plan p (the skinny kernel: 0 rows, 32
-// columns per workgroup).
+// Rows and columns of the tile of plan p (the skinny kernel, whose tile depends
+// on the epilogue and the stream: 0 and 32, a mark).
 void plan_tile(const GemmDesc& g, const GemmPlan& p, int* bm, int* bn);
 hipError_t launch_gemm(const GemmDesc& g, const Scratch& s, const LaunchCaps& caps, hipStream_t st);
 

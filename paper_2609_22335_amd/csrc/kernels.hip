@@ -250,11 +250,6 @@ __device__ __forceinline__ void epi_one(const Epi& e, int m, int n, float v) {
       TT<T>::st((T*)e.out + out_at<T>(e, m, n, e.ldo, e.blk_out), v);
       break;
     }
-    case EPI_RESID: {
-      if (e.bias) v += e.bias[n];
-      e.resid[(size_t)m * e.ldr + n] += v;
-      break;
-    }
     case EPI_GELU: {
       if (e.bias) v += e.bias[n];
       TT<T>::st((T*)e.out + out_at<T>(e, m, n, e.ldo, e.blk_out), gelu_tanh(v));
@@ -338,118 +333,6 @@ __device__ __forceinline__ void epi_pair(const Epi& e, int M, int N, int m, int 
   if (n + 16 < N) epi_one<T, KIND>(e, m, n + 16, v1);
 }
 
-// The epilogue of PER column pairs of one thread (pair k: row m[k], columns
-// n[k] and n[k] + 16, values v0[k], v1[k]), with the arithmetic of epi_pair
-// on each pair. Everything the epilogue reads (bias, rowadd, Euler state,
-// RoPE tables) is loaded for all pairs before the first store: the vector
-// memory counter keeps loads and stores in one issue order, so a load placed
-// after a store waits for that store's write to complete, and one epi_pair
-// after another would serialise on them. Rows m[k] >= M are skipped.
-template <typename T, int PER, int KIND = -1>
-__device__ __forceinline__ void epi_pairs(const Epi& e, int M, int N, const int (&m)[PER],
-                                          const int (&n)[PER], float (&v0)[PER], float (&v1)[PER]) {
-  const int kind = KIND >= 0 ? KIND : e.kind;
-  const bool biased = kind == EPI_F32 || kind == EPI_T || kind == EPI_RESID || kind == EPI_GELU ||
-                      kind == EPI_SWISH || kind == EPI_EULER;
-  if (biased && e.bias) {
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      if (n[k] < N) v0[k] += e.bias[n[k]];
-      if (n[k] + 16 < N) v1[k] += e.bias[n[k] + 16];
-    }
-  }
-  if (kind == EPI_F32 && e.rowadd) {
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      if (m[k] >= M) continue;
-      const float* ra = e.rowadd + (size_t)(m[k] % e.rowadd_period) * e.ldra;
-      if (n[k] < N) v0[k] += ra[n[k]];
-      if (n[k] + 16 < N) v1[k] += ra[n[k] + 16];
-    }
-  }
-  if (kind == EPI_RESID || kind == EPI_EULER) {
-    // read-modify-write operands: the residual stream, or the Euler state x
-    float* base = kind == EPI_RESID ? e.resid : e.x;
-    const int ld = kind == EPI_RESID ? e.ldr : e.ldx;
-    float r0[PER], r1[PER];
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      const bool ok = m[k] < M;
-      r0[k] = ok && n[k] < N ? base[(size_t)m[k] * ld + n[k]] : 0.f;
-      r1[k] = ok && n[k] + 16 < N ? base[(size_t)m[k] * ld + n[k] + 16] : 0.f;
-    }
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      if (m[k] >= M) continue;
-      float* p = base + (size_t)m[k] * ld + n[k];
-      if (kind == EPI_RESID) {
-        if (n[k] < N) p[0] = r0[k] + v0[k];
-        if (n[k] + 16 < N) p[16] = r1[k] + v1[k];
-      } else {
-        if (n[k] < N) {
-          const float xn = __builtin_fmaf(e.dt, v0[k], r0[k] * e.xs);
-          p[0] = xn;
-          TT<T>::st((T*)e.xop + out_at<T>(e, m[k], n[k], e.ldxop, e.blk_xop), xn);
-        }
-        if (n[k] + 16 < N) {
-          const float xn = __builtin_fmaf(e.dt, v1[k], r1[k] * e.xs);
-          p[16] = xn;
-          TT<T>::st((T*)e.xop + out_at<T>(e, m[k], n[k] + 16, e.ldxop, e.blk_xop), xn);
-        }
-      }
-    }
-    return;
-  }
-  if (kind == EPI_QKV_ROPE) {
-    const int hd = e.hd, qcols = e.nq * hd, kcols = e.nkv * hd;
-    float c[PER], sn[PER];
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      c[k] = 1.f;
-      sn[k] = 0.f;
-      if (m[k] < M && n[k] + 16 < N && n[k] < qcols + kcols) {
-        const int rn = n[k] < qcols ? n[k] : n[k] - qcols;
-        const int pp = rn % hd;
-        const int i = 16 * (pp >> 5) + (pp & 15);
-        const size_t t = (size_t)(e.pos0 + epi_key(e, m[k])) * (hd / 2) + i;
-        c[k] = e.rope_cos[t];
-        sn[k] = e.rope_sin[t];
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      if (m[k] >= M || n[k] + 16 >= N) continue;
-      if (n[k] < qcols + kcols) {
-        const bool isq = n[k] < qcols;
-        const int rn = isq ? n[k] : n[k] - qcols;
-        const int head = rn / hd, pp = rn - head * hd;
-        const int i = 16 * (pp >> 5) + (pp & 15);
-        const float a = v0[k] * c[k] - v1[k] * sn[k], b = v1[k] * c[k] + v0[k] * sn[k];
-        if (isq) {
-          T* dst = (T*)e.q + (size_t)m[k] * e.ldq + head * hd;
-          TT<T>::st(dst + i, a);
-          TT<T>::st(dst + i + hd / 2, b);
-        } else {
-          constexpr int DT = sizeof(T) == 2 ? DT_BF16 : DT_F32;
-          const int key = epi_key(e, m[k]);
-          T* dst = (T*)e.k + epi_kblk(e, m[k], e.blk_k);
-          TT<T>::st(dst + kv_kidx(DT, e.kv_nb, hd, head, key, i), a);
-          TT<T>::st(dst + kv_kidx(DT, e.kv_nb, hd, head, key, i + hd / 2), b);
-        }
-      } else {
-        epi_pair<T, KIND>(e, M, N, m[k], n[k], v0[k], v1[k]);  // V columns: stores only
-      }
-    }
-    return;
-  }
-  // the rest only store: bias and rowadd are already in v0 / v1
-  Epi f = e;
-  f.bias = nullptr;
-  f.rowadd = nullptr;
-#pragma unroll
-  for (int k = 0; k < PER; ++k) epi_pair<T, KIND>(f, M, N, m[k], n[k], v0[k], v1[k]);
-}
-
 // ---------------------------------------------------------------------------
 // GEMM: C[M, N] = A[M, K] W[N, K]^T, both operands K-contiguous.
 // 256 threads = 4 waves in a 2 x 2 arrangement; each wave owns a
@@ -514,13 +397,13 @@ struct GemmSmemDL {
 // Waves per SIMD each tile is built for, so that its registers leave room
 // for the workgroups its LDS allows on a CU (160 KB). Direct-load tiles of 4
 // waves: 64 x 64 in two stages (32 KB) four per CU, in the ring of four
-// (64 KB) two; 128 x 128 (64 KB) two; the 320 x 128 (128 KB) and 256 x 256
-// (128 KB) ones alone, with the whole register file. The 8-wave 256 x 256
-// tile runs alone too, two waves per SIMD. Register-staged tiles: bf16 four
-// (40 and 30 KB; 128 x 128, 80 KB, two), fp32, which only the small test models run, three. Without
-// it the compiler may take a few registers more than that leaves (the
-// 128 x 128 GeGLU tile took 260 of 256) and a CU then holds one workgroup
-// fewer.
+// (64 KB) two; 128 x 128 (64 KB) two; the 320 x 128 (144 KB: two stages of A,
+// four of W) and 256 x 256 (128 KB) ones alone, with the whole register file.
+// The 8-wave 256 x 256 tile runs alone too, two waves per SIMD. Register-staged
+// tiles: bf16 four (40 and 30 KB; 128 x 128, 80 KB, two), fp32, which only the
+// small test models run, three. Without it the compiler may take a few
+// registers more than that leaves (the 128 x 128 GeGLU tile took 260 of 256)
+// and a CU then holds one workgroup fewer.
 constexpr int gemm_waves_per_eu(int bm, int waves, bool dl, int esize, int ns) {
   if (!dl) return esize == 4 ? 3 : bm >= 128 ? 2 : 4;
   if (waves != 4) return 2;
@@ -2285,6 +2168,7 @@ static hipError_t run_gemm_64(const GemmDesc& g, const GemmPlan& p, const Scratc
 hipError_t launch_gemm(const GemmDesc& g, const Scratch& s, const LaunchCaps& caps,
                        hipStream_t st) {
   if (g.frag_ks > 0) return launch_slim(g, caps, st);
+  if (g.epi.kind == EPI_RESID) return hipErrorInvalidValue;  // the action head's kernel only
   const GemmPlan p = plan_gemm(g);
   if (g.epi.kind == EPI_PART) {
     if (!g.epi.out || (size_t)p.splits * g.M * g.N > (size_t)g.epi.ldo) return hipErrorInvalidValue;
