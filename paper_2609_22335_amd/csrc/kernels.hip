@@ -1873,7 +1873,8 @@ static hipError_t run_slim_spw(const GemmDesc& g, const LaunchCaps& caps, hipStr
   const int nslab = (g.K + frag_slab(g.dtype) - 1) / frag_slab(g.dtype), pw = (nslab + SLIM_NW - 1) / SLIM_NW;
   const int rt = slim_rt(g, caps.cus);
   if (rt == 4) {
-    if (NB == 2 && caps.cus == 0) return run_slim_t<T, SLIM_NW, 4, NB, 4, KIND, 0>(g, caps, st);
+    if constexpr (NB == 2)
+      if (caps.cus == 0) return run_slim_t<T, SLIM_NW, 4, NB, 4, KIND, 0>(g, caps, st);
     return run_slim_t<T, SLIM_NW, 2, NB, 4, KIND, 0>(g, caps, st);
   }
   if (rt == 2) return run_slim_t<T, SLIM_NW, 4, NB, 2, KIND, 0>(g, caps, st);
